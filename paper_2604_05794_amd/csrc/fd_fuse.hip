@@ -227,14 +227,17 @@ hipError_t launch_learned_refine(const SceneDev& s, const SearchDev& q, const Le
 }
 
 // ---- paper-literal candidates ---------------------------------------------------
-template <typename T, int P, int KT>
-__global__ __launch_bounds__(256) void k_fpmvo(SceneDev s, SearchDev q, FpmvoDev f) {
+// Layers held in registers: 5 (the default of the method) or 16 (the most).
+// The five-layer form is held to two waves per SIMD.
+template <typename T, int P, int KT, int NS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NS <= 5 ? 2 : 1)))
+void k_fpmvo(SceneDev s, SearchDev q, FpmvoDev f) {
   const Group gr = make_group<KT>(q.K);
   const int64_t wave = wave_tile(gridDim.x);
   const int64_t j = wave * gr.G + gr.g;
   if (wave * gr.G >= s.n) return;  // whole wave idle (uniform exit)
   const bool pt_ok = gr.lane_ok && j < s.n;
-  fpmvo_group<T, P, KT>(s, q, f, gr, pt_ok, pt_ok ? j : 0);
+  fpmvo_group<T, P, KT, NS>(s, q, f, gr, pt_ok, pt_ok ? j : 0);
 }
 
 hipError_t launch_fpmvo(const SceneDev& s, const SearchDev& q, const FpmvoDev& f, int dtype,
@@ -243,11 +246,17 @@ hipError_t launch_fpmvo(const SceneDev& s, const SearchDev& q, const FpmvoDev& f
   const int G = kWave / q.K;
   const int64_t nb = (s.n + 4 * (int64_t)G - 1) / (4 * (int64_t)G);
   dim3 grid((unsigned)nb), block(256);
-#define FD_FPMVO_CASE(T, P)                                                     \
-  if (q.K == 5)                                                                 \
-    hipLaunchKernelGGL((k_fpmvo<T, P, 5>), grid, block, 0, st, s, q, f);        \
-  else                                                                          \
-    hipLaunchKernelGGL((k_fpmvo<T, P, 0>), grid, block, 0, st, s, q, f);
+#define FD_FPMVO_NS(T, P, KT)                                                        \
+  if (f.samples <= 5)                                                                \
+    hipLaunchKernelGGL((k_fpmvo<T, P, KT, 5>), grid, block, 0, st, s, q, f);         \
+  else                                                                               \
+    hipLaunchKernelGGL((k_fpmvo<T, P, KT, FD_MAX_FPMVO_SAMPLES>), grid, block, 0, st, s, q, f);
+#define FD_FPMVO_CASE(T, P)                                                          \
+  if (q.K == 5) {                                                                    \
+    FD_FPMVO_NS(T, P, 5)                                                             \
+  } else {                                                                           \
+    FD_FPMVO_NS(T, P, 0)                                                             \
+  }
   if (dtype == 1) {
     switch (patch) {
       case 1: FD_FPMVO_CASE(__half, 1) break;
@@ -266,6 +275,7 @@ hipError_t launch_fpmvo(const SceneDev& s, const SearchDev& q, const FpmvoDev& f
     }
   }
 #undef FD_FPMVO_CASE
+#undef FD_FPMVO_NS
   return hipGetLastError();
 }
 

@@ -219,106 +219,6 @@ __device__ __forceinline__ void build_patch(const SceneDev& s, const SearchDev& 
   }
 }
 
-// The patch in binary64 throughout (texel angles, bilinear weights,
-// normalisation, Jacobian): the paper-literal candidate mode, which scores a
-// handful of candidates per point and compares their costs directly.
-template <int P>
-struct ViewPatch64 {
-  static constexpr int P2 = P * P;
-  double a[P2], b[P2], c[P2];
-  double M[6];
-};
-
-template <typename T, int P>
-__device__ __forceinline__ void build_patch64(const SceneDev& s, const SearchDev& q, int view,
-                                              bool active, double px, double py, double pz,
-                                              ViewPatch64<P>& vp) {
-  constexpr int P2 = P * P, HP = (P - 1) / 2;
-#pragma unroll
-  for (int k = 0; k < P2; ++k) vp.a[k] = vp.b[k] = vp.c[k] = 0.0;
-#pragma unroll
-  for (int k = 0; k < 6; ++k) vp.M[k] = 0.0;
-  if (!active) return;
-  const float* cam = s.cams + 16 * view;
-  Proj pr;
-  project64(cam, px, py, pz, s.W, s.H, q.z_near, pr);
-  const float* R = cam + 4;
-  const double f0 = cam[0], f1 = cam[1];
-  vp.M[0] = f0 * (pr.Z * R[0] - pr.X * R[6]);
-  vp.M[1] = f0 * (pr.Z * R[1] - pr.X * R[7]);
-  vp.M[2] = f0 * (pr.Z * R[2] - pr.X * R[8]);
-  vp.M[3] = f1 * (pr.Z * R[3] - pr.Y * R[6]);
-  vp.M[4] = f1 * (pr.Z * R[4] - pr.Y * R[7]);
-  vp.M[5] = f1 * (pr.Z * R[5] - pr.Y * R[8]);
-  const size_t plane = (size_t)s.W * s.H;
-  const T* th = (const T*)s.theta + plane * view;
-  const T* cf = (const T*)s.conf + plane * view;
-  const double x0 = floor(pr.u), y0 = floor(pr.v);
-  const double fx = pr.u - x0, fy = pr.v - y0;
-  const int ix = (int)x0 - HP, iy = (int)y0 - HP;
-  // One patch row per pass (the loop is not unrolled: each sample takes
-  // four sine/cosine evaluations), appended at the end of the arrays after
-  // the earlier rows move up by one row, so that every array index is a
-  // constant and the patch stays in registers (indexing by the row made it
-  // a private array in memory).
-  for (int b = 0; b < P; ++b) {
-    double ra[P], rb[P], rc[P];
-#pragma unroll
-    for (int a = 0; a < P; ++a) {
-      double cb = 0.0, mx = 0.0, my = 0.0;
-#pragma unroll
-      for (int jy = 0; jy < 2; ++jy)
-#pragma unroll
-        for (int jx = 0; jx < 2; ++jx) {
-          const double w = (jx ? fx : 1.0 - fx) * (jy ? fy : 1.0 - fy);
-          const double t = tex_load_nb<T>(th, s.W, s.H, ix + a + jx, iy + b + jy);
-          const double c = tex_load_nb<T>(cf, s.W, s.H, ix + a + jx, iy + b + jy);
-          double sn, cs;
-          sincos(2.0 * t, &sn, &cs);
-          cb += w * c;
-          mx += w * c * cs;
-          my += w * c * sn;
-        }
-      const double n = sqrt(mx * mx + my * my);
-      const double al = 0.5 * cb * cb;
-      ra[a] = n > 0.0 ? al : 0.0;
-      rb[a] = n > 0.0 ? al * mx / n : 0.0;
-      rc[a] = n > 0.0 ? 2.0 * al * my / n : 0.0;
-    }
-#pragma unroll
-    for (int k = 0; k < P2 - P; ++k) {
-      vp.a[k] = vp.a[k + P];
-      vp.b[k] = vp.b[k + P];
-      vp.c[k] = vp.c[k + P];
-    }
-#pragma unroll
-    for (int a = 0; a < P; ++a) {
-      vp.a[P2 - P + a] = ra[a];
-      vp.b[P2 - P + a] = rb[a];
-      vp.c[P2 - P + a] = rc[a];
-    }
-  }
-}
-
-template <int P>
-__device__ __forceinline__ double eval_patch64(const ViewPatch64<P>& vp, double dx, double dy,
-                                               double dz) {
-  constexpr int P2 = P * P;
-  const double rx = __builtin_fma(vp.M[0], dx, __builtin_fma(vp.M[1], dy, vp.M[2] * dz));
-  const double ry = __builtin_fma(vp.M[3], dx, __builtin_fma(vp.M[4], dy, vp.M[5] * dz));
-  const double xx = rx * rx;
-  const double n2 = __builtin_fma(ry, ry, xx);
-  const bool on = n2 > 0.0;
-  const double inv = 1.0 / (on ? n2 : 1.0);
-  const double c2 = __builtin_fma(-ry, ry, xx) * inv;
-  const double s2 = (rx * ry) * inv;
-  double m = 0.0;
-#pragma unroll
-  for (int k = 0; k < P2; ++k)
-    m = fmax(m, __builtin_fma(vp.b[k], c2, __builtin_fma(vp.c[k], s2, vp.a[k])));
-  return (on && m > 0.0) ? sqrt(m) : 0.0;
-}
-
 // max_p C_p |cos(phi(d) - theta_p)| for this lane's view (0 if the tangent
 // projects to a point or the lane has no view), binary32: the lattice stage.
 // With r = M d, n2 = |r|^2:
@@ -856,50 +756,58 @@ __device__ __forceinline__ void learned_group(const SceneDev& s, const SearchDev
 // same one), and the fused candidate with the largest view sum (lowest J,
 // first of equals) is the result.  Positions, candidates, the medoid
 // weights, the patch and its score are binary64.
-template <typename T, int P, int KT>
+// The patch is never held: the candidates depend on its centre sample only,
+// so they are fused first and the samples are then formed row by row and
+// folded into each layer's running maximum (NS >= S layers held in
+// registers).  Bound by binary64 arithmetic, most of it the texels' sines
+// and cosines (over a hundred instructions each): every texel of the
+// (P + 1)^2 footprint takes them once, where evaluating them per sample took
+// 4 P^2 (100 against 36 + 4 for P = 5).  150,001 points, 64 views of 1024^2
+// binary16, P = 5, S = 5, the whole call: 713 us with the patch held and a
+// sine and cosine per sample, 544 us with the texels shared (330 registers,
+// one wave per SIMD), 435 us with the patch streamed (229, two waves).
+template <typename T, int P, int KT, int NS>
 __device__ __forceinline__ void fpmvo_group(const SceneDev& s, const SearchDev& q,
                                             const FpmvoDev& f, const Group& gr, bool pt_ok,
                                             int64_t j) {
+  constexpr int HP = (P - 1) / 2;
   const uint32_t i = pt_ok ? s.perm[j] : 0u;
   const int keff = pt_ok ? (int)s.kcount[j] : 0;
   const bool slot_ok = pt_ok && gr.slot < keff;
   const int view = slot_ok ? (int)s.views[FD_TOPK_SLOTS * j + gr.slot] : 0;
   const double px = s.pts[3 * (size_t)i], py = s.pts[3 * (size_t)i + 1],
                pz = s.pts[3 * (size_t)i + 2];
-  ViewPatch64<P> vp;
-  build_patch64<T, P>(s, q, view, slot_ok, px, py, pz, vp);
+  const size_t plane = (size_t)s.W * s.H;
+  const T* thm = (const T*)s.theta + plane * view;
+  const T* cfm = (const T*)s.conf + plane * view;
 
   // Eq. (1): the orientation t of the centre sample (the bilinear,
-  // confidence-weighted doubled-angle mean at u, recomputed here in binary64:
-  // it places the offset pixel, a discrete choice) and the unit offset
-  // (cos t, sin t), t in (-pi/2, pi/2]; the centre confidence is the medoid
-  // weight of Eq. (6)
+  // confidence-weighted doubled-angle mean at u, in binary64: it places the
+  // offset pixel, a discrete choice) and the unit offset (cos t, sin t), t
+  // in (-pi/2, pi/2]; the centre confidence is the medoid weight of Eq. (6)
   const float* cam = s.cams + 16 * view;
-  Proj pr;
+  Proj pr{};
   const bool in_view = slot_ok && project64(cam, px, py, pz, s.W, s.H, q.z_near, pr);
+  const double x0 = floor(pr.u), y0 = floor(pr.v);
+  const double fx = pr.u - x0, fy = pr.v - y0;
+  const int ix = (int)x0, iy = (int)y0;
   double w = 0.0, ct = 1.0, st = 0.0;
   bool vok = false;
   if (in_view) {
-    const size_t plane = (size_t)s.W * s.H;
-    const T* thm = (const T*)s.theta + plane * view;
-    const T* cfm = (const T*)s.conf + plane * view;
-    const double x0 = floor(pr.u), y0 = floor(pr.v);
-    const double fx = pr.u - x0, fy = pr.v - y0;
-    const int ix = (int)x0, iy = (int)y0;
     double mx = 0.0, my = 0.0;
     for (int b = 0; b < 2; ++b)
       for (int a = 0; a < 2; ++a) {
         const double wt = (a ? fx : 1.0 - fx) * (b ? fy : 1.0 - fy);
         const double th = tex_load_nb<T>(thm, s.W, s.H, ix + a, iy + b);
         const double c = tex_load_nb<T>(cfm, s.W, s.H, ix + a, iy + b);
+        double sn, cs;
+        sincos(2.0 * th, &sn, &cs);
         w += wt * c;
-        mx += wt * c * cos(2.0 * th);
-        my += wt * c * sin(2.0 * th);
+        mx += wt * c * cs;
+        my += wt * c * sn;
       }
     vok = sqrt(mx * mx + my * my) > 0.0;
-    const double t = 0.5 * atan2(my, mx);
-    ct = cos(t);
-    st = sin(t);
+    sincos(0.5 * atan2(my, mx), &st, &ct);
   }
   const double ux = (in_view ? pr.u : 0.0) + (double)f.lambda * ct;
   const double uy = (in_view ? pr.v : 0.0) + (double)f.lambda * st;
@@ -916,8 +824,23 @@ __device__ __forceinline__ void fpmvo_group(const SceneDev& s, const SearchDev& 
   const float* tc = cam + 13;
   const double S1 = f.samples > 1 ? (double)(f.samples - 1) : 1.0;
 
-  double Sb = -INFINITY, bxd = 0.0, byd = 0.0, bzd = 0.0;
-  for (int sl = 0; sl < f.samples; ++sl) {
+  // r = J_pi d up to a positive factor, as in build_patch
+  const double f0 = cam[0], f1 = cam[1];
+  const double M[6] = {f0 * (pr.Z * R[0] - pr.X * R[6]), f0 * (pr.Z * R[1] - pr.X * R[7]),
+                       f0 * (pr.Z * R[2] - pr.X * R[8]), f1 * (pr.Z * R[3] - pr.Y * R[6]),
+                       f1 * (pr.Z * R[4] - pr.Y * R[7]), f1 * (pr.Z * R[5] - pr.Y * R[8])};
+  // per layer: the lane whose candidate was fused (-1: none), the candidate,
+  // this view's doubled image angle of it (on: it has one) and the maximum
+  // over the samples so far
+  int lead[NS];
+  bool on[NS];
+  double lx[NS], ly[NS], lz[NS], c2[NS], s2[NS], m[NS];
+#pragma unroll
+  for (int sl = 0; sl < NS; ++sl) {
+    lead[sl] = -1;
+    on[sl] = false;
+    lx[sl] = ly[sl] = lz[sl] = c2[sl] = s2[sl] = m[sl] = 0.0;
+    if (sl >= f.samples) continue;  // uniform
     const double zs =
         D + (f.samples > 1 ? -(double)f.delta + 2.0 * (double)f.delta * (double)sl / S1 : 0.0);
     const double xc0 = (ux - (double)cam[2]) * zs / (double)cam[0] - (double)tc[0];
@@ -958,15 +881,76 @@ __device__ __forceinline__ void fpmvo_group(const SceneDev& s, const SearchDev& 
     }
     // the same in every lane of the group; the shuffles below run in every lane
     const int src = gr.base + (bj < 0 ? 0 : bj);
-    const double fx = __shfl(dx, src, kWave), fy = __shfl(dy, src, kWave),
-                 fz = __shfl(dz, src, kWave);
-    // Eq. (12): patch consistency of the fused candidate
-    const double Sv = group_sum_t<KT>(eval_patch64<P>(vp, fx, fy, fz), gr.base, gr.K);
-    if (bj >= 0 && Sv > Sb) {
+    lead[sl] = bj;
+    lx[sl] = __shfl(dx, src, kWave);
+    ly[sl] = __shfl(dy, src, kWave);
+    lz[sl] = __shfl(dz, src, kWave);
+    const double rx = __builtin_fma(M[0], lx[sl], __builtin_fma(M[1], ly[sl], M[2] * lz[sl]));
+    const double ry = __builtin_fma(M[3], lx[sl], __builtin_fma(M[4], ly[sl], M[5] * lz[sl]));
+    const double xx = rx * rx;
+    const double n2 = __builtin_fma(ry, ry, xx);
+    on[sl] = slot_ok && n2 > 0.0;
+    const double inv = 1.0 / (on[sl] ? n2 : 1.0);
+    c2[sl] = __builtin_fma(-ry, ry, xx) * inv;
+    s2[sl] = (rx * ry) * inv;
+  }
+
+  // Eqs. (9)-(11): the samples of the patch, a texel row at a time
+  double rc[P + 1], rx[P + 1], ry[P + 1];  // C, cos 2theta, sin 2theta
+  auto load_row = [&](int y) {
+#pragma unroll
+    for (int a = 0; a <= P; ++a) {
+      const double t = tex_load_nb<T>(thm, s.W, s.H, ix - HP + a, y);
+      rc[a] = tex_load_nb<T>(cfm, s.W, s.H, ix - HP + a, y);
+      sincos(2.0 * t, &ry[a], &rx[a]);
+    }
+  };
+  load_row(iy - HP);
+#pragma unroll 1
+  for (int b = 0; b < P; ++b) {
+    double pc[P + 1], qx[P + 1], qy[P + 1];  // the row above
+#pragma unroll
+    for (int a = 0; a <= P; ++a) {
+      pc[a] = rc[a];
+      qx[a] = rx[a];
+      qy[a] = ry[a];
+    }
+    load_row(iy - HP + b + 1);
+#pragma unroll
+    for (int a = 0; a < P; ++a) {
+      double cb = 0.0, mx = 0.0, my = 0.0;
+#pragma unroll
+      for (int jy = 0; jy < 2; ++jy)
+#pragma unroll
+        for (int jx = 0; jx < 2; ++jx) {
+          const double wt = (jx ? fx : 1.0 - fx) * (jy ? fy : 1.0 - fy);
+          const double c = jy ? rc[a + jx] : pc[a + jx];
+          cb += wt * c;
+          mx += wt * c * (jy ? rx[a + jx] : qx[a + jx]);
+          my += wt * c * (jy ? ry[a + jx] : qy[a + jx]);
+        }
+      const double n = sqrt(mx * mx + my * my);
+      const double al = 0.5 * cb * cb;
+      const double va = n > 0.0 ? al : 0.0;
+      const double vb = n > 0.0 ? al * mx / n : 0.0;
+      const double vc = n > 0.0 ? 2.0 * al * my / n : 0.0;
+#pragma unroll
+      for (int sl = 0; sl < NS; ++sl)
+        m[sl] = fmax(m[sl], __builtin_fma(vb, c2[sl], __builtin_fma(vc, s2[sl], va)));
+    }
+  }
+
+  // Eq. (12): patch consistency of each layer's fused candidate
+  double Sb = -INFINITY, bxd = 0.0, byd = 0.0, bzd = 0.0;
+#pragma unroll
+  for (int sl = 0; sl < NS; ++sl) {
+    if (sl >= f.samples) continue;  // uniform
+    const double Sv = group_sum_t<KT>((on[sl] && m[sl] > 0.0) ? sqrt(m[sl]) : 0.0, gr.base, gr.K);
+    if (lead[sl] >= 0 && Sv > Sb) {
       Sb = Sv;
-      bxd = fx;
-      byd = fy;
-      bzd = fz;
+      bxd = lx[sl];
+      byd = ly[sl];
+      bzd = lz[sl];
     }
   }
   if (pt_ok && gr.slot == 0) {

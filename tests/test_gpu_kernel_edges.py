@@ -38,3 +38,41 @@ def test_paper_candidate_layers(samples, patch, top_k):
     orc = oracle.Oracle(sc.cams, sc.theta, sc.conf, depth=sc.depth, **kw)
     do, co = orc.fpmvo(pts, **fp)
     assert_parity(compare(orc, pts, d.cpu().numpy(), c.cpu().numpy(), do, co))
+
+
+@pytest.mark.parametrize("dims,max_steps,bend,mode", [
+    ((1, 1, 1), 1, -2.0, 0), ((2, 5, 3), 63, -2.0, 1), ((4, 4, 4), 64, 0.5, 2), ((9, 3, 130), 62, -2.0, 0),
+    ((40, 40, 40), 127, -2.0, 1), ((40, 40, 40), 130, 0.9, 2), ((17, 16, 15), 65, 1.0, 0)])
+def test_growing_bit_for_bit(dims, max_steps, bend, mode):
+    """Traces identical to the oracle's on grids smaller and larger than the
+    blocks that a wave loads, at lengths around the 64 vertices it stores at
+    once, with seeds on voxel faces and outside the grid; bend 1.0: a voxel's
+    orientation may fail the bend test against itself."""
+    nat = _native()
+    rng = np.random.default_rng(sum(dims) + max_steps)
+    nx, ny, nz = dims
+    d = rng.normal(size=(nz, ny, nx, 3)) * 0.35 + np.array([0.3, -0.5, 0.8])
+    d /= np.linalg.norm(d, axis=-1, keepdims=True)
+    d = (d * rng.choice([-1.0, 1.0], size=(nz, ny, nx, 1))).astype(np.float32)
+    d[rng.uniform(size=(nz, ny, nx)) < 0.01] = 0.0
+    occ = (rng.uniform(size=(nz, ny, nx)) > 0.02).astype(np.uint32)
+    coh = rng.uniform(0.1, 1.0, size=(nz, ny, nx)).astype(np.float32)
+    grid = (np.array([-0.013, 0.002, -0.3], np.float32), np.float32(0.0031), np.array(dims, np.int32))
+    n = 301
+    seeds = rng.uniform(-0.1, 1.1, size=(n, 3)) * np.array(dims) * 0.0031 + grid[0]
+    seeds[:60] = np.round((seeds[:60] - grid[0]) / 0.0031) * np.float32(0.0031) + grid[0]
+    seeds = seeds.astype(np.float32)
+    sdirs = rng.normal(size=(n, 3)).astype(np.float32)
+    cr = torch.from_numpy(rng.integers(0, 3, size=occ.size).astype(np.int32)).to(DEV)
+    kw = dict(step=7e-4, max_steps=max_steps, min_coherence=0.12, max_bend_cos=bend, voxel_cap=9, batch=100)
+    o = oracle.grow(dict(occ=occ, dir=d, coherence=coh), grid, seeds, sdirs if mode == 0 else None,
+                    crossings=cr.cpu().numpy().view(np.uint32).copy(), seed_mode=mode, centre=(0.0, 0.0, 0.0), **kw)
+    v, nv, last = nat.grow_strands(_t(occ.view(np.int32)), _t(d), _t(coh), *grid, _t(seeds), _t(sdirs) if mode == 0 else None,
+                                   crossings=cr, seed_mode=mode, **kw)
+    torch.cuda.synchronize()
+    v, nv = v.cpu().numpy(), nv.cpu().numpy()
+    assert np.array_equal(nv, o["n_verts"])
+    for i in range(n):
+        assert np.array_equal(v[i, :nv[i]], o["verts"][i, :nv[i]]), i
+    assert np.array_equal(last.cpu().numpy(), o["last_dir"])
+    assert np.array_equal(cr.cpu().numpy().view(np.uint32), o["crossings"])

@@ -18,8 +18,8 @@
 
 #include <cstdio>
 #include <cstring>
+#include <cmath>
 #include <new>
-#include <utility>
 
 #include "../../include/fusedir.h"
 #include "fd_api_internal.hpp"
@@ -75,10 +75,14 @@ __device__ __forceinline__ f32x4 mfma(const bf16x8& a, const bf16x8& b, const f3
 // ---- packing: float master -> bfloat16 matrix-core layouts ------------------------
 // Wt[n][k] (k contiguous) for every layer; k of layer 1 padded to 128 and n of
 // layer 4 padded to 16 with zeros; biases copied to float arrays (b4 padded).
+// W2 and W3 also as they are, [k][n] (n contiguous: the k index of the
+// input-gradient products).
 struct Packed {
   uint16_t* w1t;  // DH x D0P
   uint16_t* w2t;  // DH x DH
   uint16_t* w3t;  // DH x DH
+  uint16_t* w2n;  // DH x DH
+  uint16_t* w3n;  // DH x DH
   uint16_t* w4t;  // DOP x DH
   float* bias;    // b1 | b2 | b3 | b4(16)
 };
@@ -93,6 +97,8 @@ __global__ void k_mlp_pack(const float* __restrict__ m, Packed p) {
     const int n = i / DH, k = i % DH;
     p.w2t[i] = f2bf(m[OFF_W2 + k * DH + n]);
     p.w3t[i] = f2bf(m[OFF_W3 + k * DH + n]);
+    p.w2n[i] = f2bf(m[OFF_W2 + i]);
+    p.w3n[i] = f2bf(m[OFF_W3 + i]);
   }
   if (i < DOP * DH) {
     const int n = i / DH, k = i % DH;
@@ -240,345 +246,519 @@ __global__ __launch_bounds__(kFwdThreads, 2) void k_mlp_fwd(const uint16_t* __re
   }
 }
 
-// ---- training: generic bfloat16 matrix product and elementwise kernels -------------
-// C[m][n] = sum_k A(m, k) B(k, n), A(m, k) = a[m * sam + k * sak],
-// B(k, n) = b[k * sbk + n * sbn], each operand contiguous along k (sak = 1,
-// sbk = 1) or along m / n (sam = 1, sbn = 1); N % 64 == 0, K % 32 == 0 (per
-// K slice), rows m >= M read as zero.  Columns >= n_real and rows >=
-// m_real are not stored.  k in ascending order per slice: deterministic.
-// Epilogue:
-//   EPI_STORE      c[m * ldc + n] = acc
-//   EPI_BIAS_GELU  z = acc + bias[n]; zf[m*ldc+n] = z; h[m*ldh+n] = bf16(gelu(z))
-//   EPI_GELU_BACK  d = acc * gelu'(zf[m*ldc+n]); dq[m*ldh+n] = bf16(d); df[tile][n] =
-//                  sum of d over the tile's rows (the next bias gradient's partials)
-enum { EPI_STORE = 0, EPI_BIAS_GELU = 1, EPI_GELU_BACK = 2 };
+// ---- training ------------------------------------------------------------------------
+// A step is three launches.  At batches of a few thousand rows the products
+// are microseconds of matrix-core work, so what bounds a step is how often
+// the chain of dependent stages goes through memory and a launch: as one
+// kernel per product and per reduction it was 23 launches, 163 us for batch
+// 4096; now 50 us (k_train_rows 30, k_train_wgrad 10, k_train_finish 10), and
+// 107 -> 35 us for batch 64, 1149 -> 493 us for 65536.
+//   k_train_rows    a workgroup owns 16 or 32 rows and takes them
+//                   through the forward pass, the loss and the backward
+//                   pass; everything on the way stays in LDS and registers.
+//                   It writes what sums over the batch need, transposed
+//                   (batch index contiguous): activations and gradients in
+//                   bfloat16 for the weight-gradient products, gradients in
+//                   float for the bias sums.
+//   k_train_wgrad   the three weight-gradient products, split over the batch.
+//   k_train_finish  every parameter's sum over the batch in a fixed order,
+//                   then the Adam update and the bfloat16 copies.
+// The shape and order of every sum depend on the batch size only (not on the
+// rows a workgroup takes): a step is deterministic.
 
-struct GemmArgs {
-  const uint16_t* a;
-  int64_t sam, sak;
-  const uint16_t* b;
-  int64_t sbk, sbn;
-  int M, N, K, m_real, n_real;
-  int epi;
-  float* c;  // EPI_STORE: output; EPI_BIAS_GELU: z out; EPI_GELU_BACK: z in
-  int64_t ldc;
-  const float* bias;
-  float* df;     // EPI_GELU_BACK: per 64-row tile column sums of the gradient (tiles x N)
-  uint16_t* hq;  // bf16 out
-  int64_t ldh;
-  int ksplit;    // > 1: K in ksplit slices, fp32 partial tiles to part (EPI_STORE only)
-  float* part;   // ksplit x M x N
+constexpr int kRowTile = 64;   // rows of a bias sum's partial (b1, b2); batches are padded to it
+constexpr int kRowChunk = 32;  // rows of a partial sum (output layer, b3)
+constexpr int kMaxSplit = 16;  // batch slices of a weight-gradient product
+constexpr int kOutGrad = DH * DO + DO;  // dW4 then db4, contiguous in the parameters
+constexpr int kOutLanes = 8;   // lanes per row of the output layer
+
+struct TrainDev {
+  const uint16_t* feats;  // B x D0
+  const float* tgt;       // B x 3
+  int B, Bp;              // rows; rounded up to kRowTile
+  Packed pk;
+  uint16_t* xT;           // D0P x Bp
+  uint16_t* hT[3];        // DH x Bp: activations
+  uint16_t* dT[3];        // DH x Bp: gradients of the pre-activations
+  float* dzT[3];          // DH x Bp: the same in float
+  float* dyT;             // DO x Bp: gradient of the output
+  float* lrow;            // B: loss of each row
 };
 
-// Workgroup tile 64 x 64 (four waves; wave w takes output columns
-// [16w, 16w + 16) of all 64 rows: four 16 x 16 MFMA tiles).  K is taken in
-// stages of up to kGemmKS: every global load of a stage is issued first
-// (16 bytes per thread and 32-k step), then stored to LDS with k contiguous
-// (rows padded by 8 elements) — a k-contiguous operand as it is, an m- or
-// n-contiguous one transposed with 2-byte stores — and after one barrier
-// the products of the whole stage run from LDS.
-constexpr int kGemmT = 64, kGemmK = 32, kGemmKS = 256, kGemmLd = kGemmKS + 8;
+// The workgroup's eight waves take 32 columns each of a (16 MT) x 256
+// product: acc[mt][nt] holds D[4 g + r][c16] of rows 16 mt + ..., columns
+// 32 w + 16 nt + c16.
+constexpr int kTrainThreads = 512;
+
+// All of a wave's weight fragments of one layer (K / 32 steps), loaded at
+// once: one wait per layer instead of one per step.  wt: [column][k], k
+// contiguous.
+template <int K>
+__device__ __forceinline__ void load_wfrag(const uint16_t* __restrict__ wt, int w, int c16, int g,
+                                           bf16x8 (&b)[K / 32][2]) {
+#pragma unroll
+  for (int q = 0; q < K / 32; ++q)
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+      b[q][nt] = *(const bf16x8*)(wt + (size_t)(32 * w + 16 * nt + c16) * K + 32 * q + 8 * g);
+}
+
+template <int K, int MT>
+__device__ __forceinline__ void row_gemm(const uint16_t* act, int c16, int g,
+                                         const bf16x8 (&b)[K / 32][2], f32x4 (&acc)[MT][2]) {
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int q = 0; q < K / 32; ++q)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const bf16x8 a = *(const bf16x8*)(act + (16 * mt + c16) * ACT_LD + 32 * q + 8 * g);
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = mfma(a, b[q][nt], acc[mt][nt]);
+    }
+}
+
+// Four rows' values of one column, as bfloat16, to LDS (row-major) and to
+// the transposed copy.
+__device__ __forceinline__ void put_rows4(uint16_t* act, uint16_t* tT, int64_t ldt, int row, int col,
+                                          const float (&v)[4]) {
+  const uint32_t lo = pack_bf16x2(v[0], v[1]), hi = pack_bf16x2(v[2], v[3]);
+  act[row * ACT_LD + col] = (uint16_t)lo;
+  act[(row + 1) * ACT_LD + col] = (uint16_t)(lo >> 16);
+  act[(row + 2) * ACT_LD + col] = (uint16_t)hi;
+  act[(row + 3) * ACT_LD + col] = (uint16_t)(hi >> 16);
+  *(uint2*)(tT + (int64_t)col * ldt + row) = make_uint2(lo, hi);
+}
+
+// z = acc + bias, h = gelu(z) to LDS and transposed; z kept.
+template <int MT>
+__device__ __forceinline__ void row_forward(uint16_t* act, uint16_t* hT, int64_t ldt,
+                                            const float* __restrict__ bias, int w, int c16, int g,
+                                            const f32x4 (&acc)[MT][2], f32x4 (&z)[MT][2]) {
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) {
+    const int col = 32 * w + 16 * nt + c16;
+    const float bb = bias[col];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      float h[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        z[mt][nt][r] = acc[mt][nt][r] + bb;
+        h[r] = gelu(z[mt][nt][r]);
+      }
+      put_rows4(act, hT, ldt, 16 * mt + 4 * g, col, h);
+    }
+  }
+}
+
+// d = v gelu'(z) (rows >= rows: 0) to LDS and transposed, in bfloat16 and
+// float; v(mt, nt, r) is the gradient of the activation.
+template <int MT, typename V>
+__device__ __forceinline__ void row_backward(uint16_t* act, uint16_t* dT, float* dzT, int64_t ldt,
+                                             int rows, int w, int c16, int g, const V& v,
+                                             const f32x4 (&z)[MT][2]) {
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) {
+    const int col = 32 * w + 16 * nt + c16;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const int row = 16 * mt + 4 * g;
+      float d[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        d[r] = v(mt, nt, r) * gelu_grad(z[mt][nt][r]);
+        if (row + r >= rows) d[r] = 0.0f;
+      }
+      put_rows4(act, dT, ldt, row, col, d);
+      *(float4*)(dzT + (int64_t)col * ldt + row) = make_float4(d[0], d[1], d[2], d[3]);
+    }
+  }
+}
+
+template <int RT>
+__global__ __launch_bounds__(kTrainThreads, 2) void k_train_rows(TrainDev a) {
+  constexpr int MT = RT / 16;
+  __shared__ __attribute__((aligned(16))) uint16_t act[RT * ACT_LD];
+  __shared__ float sdy[RT][4];
+  const int t = threadIdx.x, lane = t & 63, g = lane >> 4, c16 = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int64_t row0 = (int64_t)blockIdx.x * RT;
+  const int rows = max(0, min(RT, a.B - (int)row0));  // 0: only the padding's zeros are written
+  const int64_t ldt = a.Bp;
+  f32x4 acc[MT][2], z1[MT][2], z2[MT][2], z3[MT][2];
+  bf16x8 wf1[D0P / 32][2], wf[DH / 32][2];
+
+  // input rows -> act[:, 0:128) (k >= 112 and rows >= B zero), and transposed
+  load_wfrag<D0P>(a.pk.w1t, w, c16, g, wf1);
+  for (int e = t; e < RT * (D0P / 8); e += kTrainThreads) {
+    const int r = e / (D0P / 8), kb = (e % (D0P / 8)) * 8;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (r < rows && kb < D0) v = *(const uint4*)(a.feats + (row0 + r) * D0 + kb);
+    *(uint4*)(act + r * ACT_LD + kb) = v;
+  }
+  __syncthreads();
+  for (int e = t; e < D0P * (RT / 8); e += kTrainThreads) {
+    const int k = e & (D0P - 1), r0 = 8 * (e / D0P);
+    uint32_t v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      v[q] = (uint32_t)act[(r0 + 2 * q) * ACT_LD + k] |
+             ((uint32_t)act[(r0 + 2 * q + 1) * ACT_LD + k] << 16);
+    *(uint4*)(a.xT + (int64_t)k * ldt + row0 + r0) = make_uint4(v[0], v[1], v[2], v[3]);
+  }
+
+  // forward
+  row_gemm<D0P, MT>(act, c16, g, wf1, acc);
+  load_wfrag<DH>(a.pk.w2t, w, c16, g, wf);
+  __syncthreads();  // every wave has read this layer's input
+  row_forward<MT>(act, a.hT[0] + row0, ldt, a.pk.bias, w, c16, g, acc, z1);
+  __syncthreads();
+  row_gemm<DH, MT>(act, c16, g, wf, acc);
+  load_wfrag<DH>(a.pk.w3t, w, c16, g, wf);
+  __syncthreads();
+  row_forward<MT>(act, a.hT[1] + row0, ldt, a.pk.bias + DH, w, c16, g, acc, z2);
+  __syncthreads();
+  row_gemm<DH, MT>(act, c16, g, wf, acc);
+  load_wfrag<DH>(a.pk.w3n, w, c16, g, wf);
+  __syncthreads();
+  row_forward<MT>(act, a.hT[2] + row0, ldt, a.pk.bias + 2 * DH, w, c16, g, acc, z3);
+  __syncthreads();
+
+  // Output layer, loss and its gradient, eight lanes per row (lane j takes k
+  // in [32 j, 32 j + 32) in order; the eight partial sums are added by a
+  // fixed shuffle tree): y = h3 W4 + b4 (float, W4 as bfloat16 values),
+  // u = y/|y|, loss_b = 1 - (u.t)^2, dL/dy = (gr - u (u.gr)) / |y| with
+  // gr = -2 (u.t) t / B.
+  static_assert(RT * kOutLanes <= kTrainThreads, "one row per eight threads");
+  if (t < RT * kOutLanes) {  // whole waves
+    const int b = t / kOutLanes, j = t % kOutLanes;
+    float part[3] = {0.0f, 0.0f, 0.0f};
+    const int k0 = j * (DH / kOutLanes);
+#pragma unroll
+    for (int q = 0; q < DH / kOutLanes; q += 8) {
+      const uint4 hv = *(const uint4*)(act + b * ACT_LD + k0 + q);
+      const uint32_t hw[4] = {hv.x, hv.y, hv.z, hv.w};
+#pragma unroll
+      for (int n = 0; n < 3; ++n) {
+        const uint4 wv = *(const uint4*)(a.pk.w4t + n * DH + k0 + q);
+        const uint32_t ww[4] = {wv.x, wv.y, wv.z, wv.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const uint16_t he = (uint16_t)(hw[e >> 1] >> (16 * (e & 1)));
+          const uint16_t we = (uint16_t)(ww[e >> 1] >> (16 * (e & 1)));
+          part[n] += bf2f(he) * bf2f(we);
+        }
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < 3; ++n)
+#pragma unroll
+      for (int off = 1; off < kOutLanes; off <<= 1) part[n] += __shfl_xor(part[n], off, 64);
+    if (j == 0) {
+      float dy[3] = {0.0f, 0.0f, 0.0f};
+      if (b < rows) {
+        float y[3];
+#pragma unroll
+        for (int n = 0; n < 3; ++n) y[n] = part[n] + a.pk.bias[3 * DH + n];
+        const float nrm = sqrtf(y[0] * y[0] + y[1] * y[1] + y[2] * y[2]);
+        float u[3], tt[3], ut = 0.0f;
+#pragma unroll
+        for (int n = 0; n < 3; ++n) {
+          u[n] = y[n] / nrm;
+          tt[n] = a.tgt[3 * (row0 + b) + n];
+          ut += u[n] * tt[n];
+        }
+        a.lrow[row0 + b] = 1.0f - ut * ut;
+        float gg[3], ug = 0.0f;
+#pragma unroll
+        for (int n = 0; n < 3; ++n) {
+          gg[n] = -2.0f * ut * tt[n] / (float)a.B;
+          ug += u[n] * gg[n];
+        }
+#pragma unroll
+        for (int n = 0; n < 3; ++n) dy[n] = (gg[n] - u[n] * ug) / nrm;
+      }
+#pragma unroll
+      for (int n = 0; n < 3; ++n) {
+        sdy[b][n] = dy[n];
+        a.dyT[n * ldt + row0 + b] = dy[n];
+      }
+    }
+  }
+  __syncthreads();
+
+  // dz3 = (dy W4^T) gelu'(z3) (W4 as bfloat16 values), then the input
+  // gradients of layers 3 and 2
+  {
+    float w4[2][3];
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+      for (int n = 0; n < 3; ++n) w4[nt][n] = bf2f(a.pk.w4t[n * DH + 32 * w + 16 * nt + c16]);
+    row_backward<MT>(
+        act, a.dT[2] + row0, a.dzT[2] + row0, ldt, rows, w, c16, g,
+        [&](int mt, int nt, int r) {
+          float s = 0.0f;
+#pragma unroll
+          for (int n = 0; n < 3; ++n) s += sdy[16 * mt + 4 * g + r][n] * w4[nt][n];
+          return s;
+        },
+        z3);
+  }
+  __syncthreads();
+  const auto from_acc = [&](int mt, int nt, int r) { return acc[mt][nt][r]; };
+  row_gemm<DH, MT>(act, c16, g, wf, acc);
+  load_wfrag<DH>(a.pk.w2n, w, c16, g, wf);
+  __syncthreads();
+  row_backward<MT>(act, a.dT[1] + row0, a.dzT[1] + row0, ldt, rows, w, c16, g, from_acc, z2);
+  __syncthreads();
+  row_gemm<DH, MT>(act, c16, g, wf, acc);
+  __syncthreads();
+  row_backward<MT>(act, a.dT[0] + row0, a.dzT[0] + row0, ldt, rows, w, c16, g, from_acc, z1);
+}
+
+// Weight gradients: dW_l[k][n] = sum_b h_{l-1}[b][k] d_l[b][n], as 64 x 64
+// tiles over K slices of the batch; both operands are contiguous along the
+// batch.  Every load of a stage (up to kGemmKS rows of the batch) is issued
+// first, then stored to LDS (rows padded by 8 elements), and after one
+// barrier the products of the stage run from LDS, k ascending.
+constexpr int kGemmT = 64, kGemmK = 32, kGemmKS = 128, kGemmLd = kGemmKS + 8;
 
 // Operand staging registers as a native vector type (the uint4 struct
 // copied between an array and LDS made the compiler keep the array in
 // private memory).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-template <bool AK, bool BK>
-__device__ __forceinline__ void gemm_load_step(const GemmArgs& g, int m0, int n0, int k0, int t,
-                                               u32x4& va, u32x4& vb) {
-  if (AK) {  // thread t: row t / 4, k 8 (t % 4) .. + 7
-    const int r = t >> 2, kq = (t & 3) * 8;
-    va = m0 + r < g.M ? *(const u32x4*)(g.a + (int64_t)(m0 + r) * g.sam + k0 + kq)
-                      : u32x4{0u, 0u, 0u, 0u};
-  } else {   // thread t: k t / 8, rows 8 (t % 8) .. + 7 (M is a multiple of 64 here)
-    const int k = t >> 3, mq = (t & 7) * 8;
-    va = *(const u32x4*)(g.a + (int64_t)(k0 + k) * g.sak + m0 + mq);
-  }
-  if (BK) {
-    const int r = t >> 2, kq = (t & 3) * 8;
-    vb = *(const u32x4*)(g.b + (int64_t)(n0 + r) * g.sbn + k0 + kq);
-  } else {
-    const int k = t >> 3, nq = (t & 7) * 8;
-    vb = *(const u32x4*)(g.b + (int64_t)(k0 + k) * g.sbk + n0 + nq);
-  }
+constexpr int kTilesN = DH / kGemmT;                     // 4
+constexpr int kTiles1 = D0P / kGemmT * kTilesN;          // layer 1: 8
+constexpr int kTilesH = DH / kGemmT * kTilesN;           // layers 2, 3: 16
+constexpr int kWgradTiles = kTiles1 + 2 * kTilesH;       // 40
+// first float of each layer's partial products (slice-major within a layer)
+constexpr int64_t split_off(int l, int S) {
+  return l == 0 ? 0 : (int64_t)S * (D0P * DH + (l - 1) * DH * DH);
 }
 
-template <bool AK, bool BK>
-__device__ __forceinline__ void gemm_store_step(uint16_t (*As)[kGemmLd], uint16_t (*Bs)[kGemmLd],
-                                                int kk, int t, const u32x4& va, const u32x4& vb) {
-  if (AK) {
-    *(u32x4*)&As[t >> 2][kk + (t & 3) * 8] = va;
-  } else {
-    const int k = t >> 3, mq = (t & 7) * 8;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) As[mq + j][kk + k] = (uint16_t)(va[j >> 1] >> (16 * (j & 1)));
-  }
-  if (BK) {
-    *(u32x4*)&Bs[t >> 2][kk + (t & 3) * 8] = vb;
-  } else {
-    const int k = t >> 3, nq = (t & 7) * 8;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) Bs[nq + j][kk + k] = (uint16_t)(vb[j >> 1] >> (16 * (j & 1)));
-  }
-}
-
-// Column sums over the tile's 64 rows of the values v[mt][r] (row
-// 16 mt + 4 gr + r, column c16 of the wave's 16): rows in order within a
-// lane, then the four row groups gr in order (the same for every tile).
-__device__ __forceinline__ float gemm_colsum(const float (&v)[4][4], int lane) {
-  float s = 0.0f;
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) s += v[mt][r];
-  // lanes c16, c16 + 16, c16 + 32, c16 + 48 hold row groups 0..3
-  const float s1 = __shfl(s, (lane & 15) + 16, 64), s2 = __shfl(s, (lane & 15) + 32, 64),
-              s3 = __shfl(s, (lane & 15) + 48, 64), s0 = __shfl(s, lane & 15, 64);
-  return ((s0 + s1) + s2) + s3;
-}
-
-template <bool AK, bool BK>
-__global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
+__global__ __launch_bounds__(256) void k_train_wgrad(TrainDev a, int S, float* __restrict__ split) {
   __shared__ __attribute__((aligned(16))) uint16_t As[kGemmT][kGemmLd];
   __shared__ __attribute__((aligned(16))) uint16_t Bs[kGemmT][kGemmLd];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, gr = lane >> 4, c16 = lane & 15;
-  const int m0 = blockIdx.x * kGemmT, n0 = blockIdx.y * kGemmT;
+  int tile = blockIdx.x;
+  const int l = tile < kTiles1 ? 0 : (tile < kTiles1 + kTilesH ? 1 : 2);
+  tile -= l == 0 ? 0 : (l == 1 ? kTiles1 : kTiles1 + kTilesH);
+  const int m0 = tile / kTilesN * kGemmT, n0 = tile % kTilesN * kGemmT;
+  const int M = l == 0 ? D0P : DH;
+  const uint16_t* A = l == 0 ? a.xT : a.hT[l - 1];
+  const uint16_t* Bm = a.dT[l];
   f32x4 acc[4];
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt) acc[mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  const int kslice = g.K / g.ksplit;
-  const int kz0 = blockIdx.z * kslice, kz1 = kz0 + kslice;
+  const int kslice = a.B / S;
+  const int kz0 = blockIdx.y * kslice, kz1 = kz0 + kslice;
+  const int lr = t >> 2, lk = (t & 3) * 8;  // thread t: row t / 4, k 8 (t % 4) .. + 7
+  const uint16_t* ap = A + (int64_t)(m0 + lr) * a.Bp + lk;
+  const uint16_t* bp = Bm + (int64_t)(n0 + lr) * a.Bp + lk;
   for (int ks = kz0; ks < kz1; ks += kGemmKS) {
     const int kn = min(kGemmKS, kz1 - ks);  // a multiple of 32
     u32x4 va[kGemmKS / kGemmK], vb[kGemmKS / kGemmK];
 #pragma unroll
     for (int q = 0; q < kGemmKS / kGemmK; ++q)
-      if (q * kGemmK < kn) gemm_load_step<AK, BK>(g, m0, n0, ks + q * kGemmK, t, va[q], vb[q]);
+      if (q * kGemmK < kn) {
+        va[q] = *(const u32x4*)(ap + ks + q * kGemmK);
+        vb[q] = *(const u32x4*)(bp + ks + q * kGemmK);
+      }
     if (ks > kz0) __syncthreads();  // the previous stage's products are done
 #pragma unroll
     for (int q = 0; q < kGemmKS / kGemmK; ++q)
-      if (q * kGemmK < kn) gemm_store_step<AK, BK>(As, Bs, q * kGemmK, t, va[q], vb[q]);
+      if (q * kGemmK < kn) {
+        *(u32x4*)&As[lr][q * kGemmK + lk] = va[q];
+        *(u32x4*)&Bs[lr][q * kGemmK + lk] = vb[q];
+      }
     __syncthreads();
-#pragma unroll 2
     for (int kk = 0; kk < kn; kk += kGemmK) {
       const bf16x8 b = *(const bf16x8*)&Bs[16 * w + c16][kk + 8 * gr];
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) {
-        const bf16x8 a = *(const bf16x8*)&As[16 * mt + c16][kk + 8 * gr];
-        acc[mt] = mfma(a, b, acc[mt]);
+        const bf16x8 x = *(const bf16x8*)&As[16 * mt + c16][kk + 8 * gr];
+        acc[mt] = mfma(x, b, acc[mt]);
       }
     }
   }
-  // acc[mt] holds D[4 gr + r][c16] of the tile (rows 16 mt + ..., columns 16 w + ...)
-  const int n = n0 + 16 * w + c16;
-  if (g.ksplit > 1) {  // partial tile of this K slice; k_gemm_reduce finishes
+  float* out = split + split_off(l, S) + (int64_t)blockIdx.y * M * DH;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+  for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + 16 * mt + 4 * gr + r;
-        if (m < g.M) g.part[((size_t)blockIdx.z * g.M + m) * g.N + n] = acc[mt][r];
+    for (int r = 0; r < 4; ++r)
+      out[(int64_t)(m0 + 16 * mt + 4 * gr + r) * DH + n0 + 16 * w + c16] = acc[mt][r];
+}
+
+// Parameter i's gradient, and with it the Adam update (Kingma & Ba 2015) of
+// the float master weights; returns the parameter's new value.
+struct AdamDev {
+  float* w;
+  float* m;
+  float* v;
+  float* grad;  // gradient out (no update), or NULL: update
+  float lr, b1, b2, eps, bc1, bc2;
+};
+
+__device__ __forceinline__ float adam_step(const AdamDev& o, int i, float gi) {
+  if (o.grad) {
+    o.grad[i] = gi;
+    return 0.0f;
+  }
+  const float mi = o.b1 * o.m[i] + (1.0f - o.b1) * gi;
+  const float vi = o.b2 * o.v[i] + (1.0f - o.b2) * gi * gi;
+  o.m[i] = mi;
+  o.v[i] = vi;
+  const float x = o.w[i] - o.lr * (mi / o.bc1) / (sqrtf(vi / o.bc2) + o.eps);
+  o.w[i] = x;
+  return x;
+}
+
+// The workgroups of k_train_finish: 16 x 64 tiles of the hidden layers'
+// weights (their K slices summed in slice order), then one wave per entry of
+// the output layer and of the biases (partial sums over kRowChunk or
+// kRowTile rows; lane l adds the partials l, l + 64, ... in order, then a
+// fixed shuffle tree), then one workgroup for the loss.
+constexpr int kFinTiles1 = D0 / 16 * kTilesN, kFinTilesH = DH / 16 * kTilesN;
+constexpr int kFinTiles = kFinTiles1 + 2 * kFinTilesH;
+constexpr int kFinEntries = kOutGrad + 3 * DH;
+constexpr int kFinWaves = (kFinEntries + 3) / 4;
+static_assert(D0 % 16 == 0, "whole tiles");
+
+__global__ __launch_bounds__(256) void k_train_finish(TrainDev a, int S,
+                                                      const float* __restrict__ split, AdamDev o,
+                                                      float* __restrict__ loss) {
+  const int t = threadIdx.x;
+  int blk = blockIdx.x;
+  if (blk < kFinTiles) {
+    __shared__ uint16_t tr[64][16];
+    const int l = blk < kFinTiles1 ? 0 : (blk < kFinTiles1 + kFinTilesH ? 1 : 2);
+    blk -= l == 0 ? 0 : (l == 1 ? kFinTiles1 : kFinTiles1 + kFinTilesH);
+    const int k0 = blk / kTilesN * 16, n = blk % kTilesN * 64 + (t & 63);
+    const int M = l == 0 ? D0P : DH;
+    const float* part = split + split_off(l, S);
+    const int off = l == 0 ? OFF_W1 : (l == 1 ? OFF_W2 : OFF_W3);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int k = k0 + (t >> 6) + 4 * e;
+      float v = 0.0f;
+      if (S == kMaxSplit) {
+        float x[kMaxSplit];
+#pragma unroll
+        for (int z = 0; z < kMaxSplit; ++z) x[z] = part[((int64_t)z * M + k) * DH + n];
+#pragma unroll
+        for (int z = 0; z < kMaxSplit; ++z) v += x[z];
+      } else if (S > 1) {
+        for (int z = 0; z < S; ++z) v += part[((int64_t)z * M + k) * DH + n];
+      } else {
+        v = part[(int64_t)k * DH + n];
       }
+      const float x = adam_step(o, off + k * DH + n, v);
+      if (!o.grad) {
+        const uint16_t h = f2bf(x);
+        tr[t & 63][k - k0] = h;
+        if (l > 0) (l == 1 ? a.pk.w2n : a.pk.w3n)[k * DH + n] = h;
+      }
+    }
+    if (o.grad) return;  // uniform
+    __syncthreads();
+    uint16_t* wt = l == 0 ? a.pk.w1t : (l == 1 ? a.pk.w2t : a.pk.w3t);
+    const int nn = t >> 2, kq = (t & 3) * 4;
+    *(uint2*)(wt + (int64_t)(blk % kTilesN * 64 + nn) * M + k0 + kq) = *(const uint2*)&tr[nn][kq];
     return;
   }
-  float dsum[4][4];
+  blk -= kFinTiles;
+  if (blk < kFinWaves) {
+    const int e = 4 * blk + (t >> 6), lane = t & 63;
+    if (e >= kFinEntries) return;  // wave-uniform
+    const bool outw = e < kOutGrad;
+    const int l = outw ? 3 : (e - kOutGrad) / DH, n = outw ? e : (e - kOutGrad) % DH;
+    float s = 0.0f;
+    if (outw) {
+      // dW4[k][m] = sum_b h3[b][k] dy[b][m], db4[m] = sum_b dy[b][m]: chunks
+      // of kRowChunk rows, rows in order (B is a multiple of kRowChunk)
+      const bool bias = n >= DH * DO;
+      const int k = bias ? 0 : n / DO, m = bias ? n - DH * DO : n % DO;
+      const uint16_t* h = a.hT[2] + (int64_t)k * a.Bp;
+      const float* dy = a.dyT + (int64_t)m * a.Bp;
+      for (int b0 = lane * kRowChunk; b0 < a.B; b0 += 64 * kRowChunk) {
+        float4 y[kRowChunk / 4];
+        uint4 hv[kRowChunk / 8];
 #pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
+        for (int q = 0; q < kRowChunk / 4; ++q) y[q] = *(const float4*)(dy + b0 + 4 * q);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int m = m0 + 16 * mt + 4 * gr + r;
-      dsum[mt][r] = 0.0f;
-      if (m >= g.m_real || m >= g.M || n >= g.n_real) continue;
-      const float v = acc[mt][r];
-      if (g.epi == EPI_STORE) {
-        g.c[m * g.ldc + n] = v;
-      } else if (g.epi == EPI_BIAS_GELU) {
-        const float z = v + g.bias[n];
-        g.c[m * g.ldc + n] = z;
-        g.hq[m * g.ldh + n] = f2bf(gelu(z));
-      } else {
-        const float d = v * gelu_grad(g.c[m * g.ldc + n]);
-        dsum[mt][r] = d;
-        g.hq[m * g.ldh + n] = f2bf(d);
+        for (int q = 0; q < kRowChunk / 8; ++q) hv[q] = *(const uint4*)(h + b0 + 8 * q);
+        float c = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kRowChunk / 4; ++q) {
+          const float v[4] = {y[q].x, y[q].y, y[q].z, y[q].w};
+          const uint32_t hw[2] = {q & 1 ? hv[q / 2].z : hv[q / 2].x, q & 1 ? hv[q / 2].w : hv[q / 2].y};
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float x = bf2f((uint16_t)(hw[r >> 1] >> (16 * (r & 1))));
+            c += bias ? v[r] : x * v[r];
+          }
+        }
+        s += c;
+      }
+    } else if (l == 2) {  // b3: chunks of kRowChunk rows, rows in order
+      const float* d = a.dzT[2] + (int64_t)n * a.Bp;
+      for (int b0 = lane * kRowChunk; b0 < a.B; b0 += 64 * kRowChunk) {
+        float4 y[kRowChunk / 4];
+#pragma unroll
+        for (int q = 0; q < kRowChunk / 4; ++q) y[q] = *(const float4*)(d + b0 + 4 * q);
+        float c = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kRowChunk / 4; ++q) c = (((c + y[q].x) + y[q].y) + y[q].z) + y[q].w;
+        s += c;
+      }
+    } else {
+      // b1, b2: tiles of kRowTile rows, as four sums over the rows
+      // 16 mt + 4 q + r (q = 0..3) in order, added in the order of q
+      const float* d = a.dzT[l] + (int64_t)n * a.Bp;
+      for (int b0 = lane * kRowTile; b0 < a.Bp; b0 += 64 * kRowTile) {
+        float c[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          c[q] = 0.0f;
+#pragma unroll
+          for (int mt = 0; mt < kRowTile / 16; ++mt) {
+            const float4 y = *(const float4*)(d + b0 + 16 * mt + 4 * q);
+            c[q] = (((c[q] + y.x) + y.y) + y.z) + y.w;
+          }
+        }
+        s += ((c[0] + c[1]) + c[2]) + c[3];
       }
     }
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane != 0) return;
+    const int i = outw ? OFF_W4 + n : (l == 0 ? OFF_B1 : (l == 1 ? OFF_B2 : OFF_B3)) + n;
+    const float x = adam_step(o, i, s);
+    if (o.grad) return;
+    if (!outw)
+      a.pk.bias[l * DH + n] = x;
+    else if (n < DH * DO)
+      a.pk.w4t[n % DO * DH + n / DO] = f2bf(x);
+    else
+      a.pk.bias[3 * DH + n - DH * DO] = x;
+    return;
   }
-  if (g.epi == EPI_GELU_BACK) {
-    // the bias gradient's partial over this tile's rows (float d), for
-    // k_col_finish to sum over the row tiles in order
-    const float cs = gemm_colsum(dsum, lane);
-    if (gr == 0) g.df[(size_t)blockIdx.x * g.N + n] = cs;
-  }
-}
-
-// The K slices of a split GEMM summed in slice order (deterministic), stored.
-__global__ void k_gemm_reduce(const float* __restrict__ part, int S, int M, int N, int m_real,
-                              int n_real, float* __restrict__ c, int64_t ldc) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= M * N) return;
-  const int m = i / N, n = i % N;
-  if (m >= m_real || n >= n_real) return;
-  float v = 0.0f;
-  for (int z = 0; z < S; ++z) v += part[((size_t)z * M + m) * N + n];
-  c[m * ldc + n] = v;
-}
-
-// feats (B x 112 bf16) -> X (B x 128 bf16, zero padded)
-__global__ void k_pad_input(const uint16_t* __restrict__ f, int B, uint16_t* __restrict__ x) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * D0P) return;
-  const int r = i / D0P, k = i % D0P;
-  x[i] = k < D0 ? f[r * D0 + k] : 0;
-}
-
-// Output layer forward + loss + its gradient, eight lanes per row (lane j
-// takes k in [32 j, 32 j + 32) in order; the eight partial sums are added
-// by a fixed shuffle tree):
-// y = h3 W4 + b4 (float, W4 as bfloat16 values), u = y/|y|, loss_b = 1 - (u.t)^2,
-// dL/dy = (g - u (u.g)) / |y| with g = -2 (u.t) t / B.
-constexpr int kOutLanes = 8;
-__global__ __launch_bounds__(256) void k_out_loss(const uint16_t* __restrict__ h3,
-                                                  const uint16_t* __restrict__ w4t,
-                                                  const float* __restrict__ bias4,
-                                                  const float* __restrict__ tgt, int B,
-                                                  float* __restrict__ dy,
-                                                  float* __restrict__ loss_row) {
-  const int b = (int)((blockIdx.x * blockDim.x + threadIdx.x) / kOutLanes);
-  const int j = (int)(threadIdx.x % kOutLanes);
-  const int bb = b < B ? b : B - 1;  // every lane takes part in the shuffles
-  float part[3] = {0.0f, 0.0f, 0.0f};
-  const int k0 = j * (DH / kOutLanes);
-#pragma unroll
-  for (int q = 0; q < DH / kOutLanes; q += 8) {
-    const uint4 hv = *(const uint4*)(h3 + (size_t)bb * DH + k0 + q);
-    const uint32_t hw[4] = {hv.x, hv.y, hv.z, hv.w};
-#pragma unroll
-    for (int n = 0; n < 3; ++n) {
-      const uint4 wv = *(const uint4*)(w4t + n * DH + k0 + q);
-      const uint32_t ww[4] = {wv.x, wv.y, wv.z, wv.w};
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint16_t he = (uint16_t)(hw[e >> 1] >> (16 * (e & 1)));
-        const uint16_t we = (uint16_t)(ww[e >> 1] >> (16 * (e & 1)));
-        part[n] += bf2f(he) * bf2f(we);
-      }
-    }
-  }
-#pragma unroll
-  for (int n = 0; n < 3; ++n)
-#pragma unroll
-    for (int off = 1; off < kOutLanes; off <<= 1) part[n] += __shfl_xor(part[n], off, 64);
-  if (j != 0 || b >= B) return;
-  float y[3];
-#pragma unroll
-  for (int n = 0; n < 3; ++n) y[n] = part[n] + bias4[n];
-  const float nrm = sqrtf(y[0] * y[0] + y[1] * y[1] + y[2] * y[2]);
-  float u[3], t[3], ut = 0.0f;
-  for (int n = 0; n < 3; ++n) {
-    u[n] = y[n] / nrm;
-    t[n] = tgt[3 * b + n];
-    ut += u[n] * t[n];
-  }
-  loss_row[b] = 1.0f - ut * ut;
-  float gg[3], ug = 0.0f;
-  for (int n = 0; n < 3; ++n) {
-    gg[n] = -2.0f * ut * t[n] / (float)B;
-    ug += u[n] * gg[n];
-  }
-  for (int n = 0; n < 3; ++n) dy[3 * b + n] = (gg[n] - u[n] * ug) / nrm;
-}
-
-// Output-layer weight gradient (float): dW4[k][n] = sum_b h3[b][k] dy[b][n],
-// db4[n] = sum_b dy[b][n].  Deterministic two-pass form: thread i of chunk c
-// sums the kRowChunk rows of its chunk in order (k_outw_partial), then each
-// entry sums its chunk partials in a fixed order (k_col_finish).
-constexpr int kRowChunk = 32;
-constexpr int kMaxSplit = 16;  // K slices of a weight-gradient GEMM
-constexpr int kOutGrad = DH * DO + DO;  // dW4 then db4, contiguous in the parameters
-
-__global__ void k_outw_partial(const uint16_t* __restrict__ h3, const float* __restrict__ dy,
-                               int B, float* __restrict__ part) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int c = blockIdx.y;
-  if (i >= kOutGrad) return;
-  const int b0 = c * kRowChunk, b1 = min(B, b0 + kRowChunk);
-  float s = 0.0f;
-  if (i < DH * DO) {
-    const int k = i / DO, n = i % DO;
-    for (int b = b0; b < b1; ++b) s += bf2f(h3[b * DH + k]) * dy[3 * b + n];
-  } else {
-    const int n = i - DH * DO;
-    for (int b = b0; b < b1; ++b) s += dy[3 * b + n];
-  }
-  part[(size_t)c * kOutGrad + i] = s;
-}
-
-// dz3 = (dy W4^T) * gelu'(z3) (W4 as bfloat16 values); float and bfloat16 copies.
-__global__ void k_out_back(const float* __restrict__ dy, const uint16_t* __restrict__ w4t,
-                           const float* __restrict__ z3, int B, float* __restrict__ dz,
-                           uint16_t* __restrict__ dzq) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * DH) return;
-  const int b = i / DH, k = i % DH;
-  float s = 0.0f;
-  for (int n = 0; n < 3; ++n) s += dy[3 * b + n] * bf2f(w4t[n * DH + k]);
-  const float d = s * gelu_grad(z3[i]);
-  dz[i] = d;
-  dzq[i] = f2bf(d);
-}
-
-// bias gradient: grad[off + n] = sum_b dz[b][n] (float), as partial sums
-// over chunks of kRowChunk rows in order, then the partials in a fixed order.
-__global__ void k_col_partial(const float* __restrict__ dz, int B, int N,
-                              float* __restrict__ part) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  const int c = blockIdx.y;
-  if (n >= N) return;
-  const int b0 = c * kRowChunk, b1 = min(B, b0 + kRowChunk);
-  float s = 0.0f;
-  for (int b = b0; b < b1; ++b) s += dz[(size_t)b * N + n];
-  part[(size_t)c * N + n] = s;
-}
-
-// One wave per entry: lane l sums partials l, l + 64, ... in order, then a
-// fixed shuffle tree (deterministic).
-__global__ void k_col_finish(const float* __restrict__ part, int chunks, int N,
-                             float* __restrict__ out) {
-  const int n = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const int lane = (int)(threadIdx.x & 63u);
-  if (n >= N) return;  // wave-uniform
-  float s = 0.0f;
-  for (int c = lane; c < chunks; c += 64) s += part[(size_t)c * N + n];
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (lane == 0) out[n] = s;
-}
-
-__global__ void k_sum_rows(const float* __restrict__ v, int B, float* __restrict__ out) {
+  // mean loss: thread t sums rows t, t + 256, ... in order, then a fixed tree
+  if (!loss) return;
   __shared__ float red[256];
   float s = 0.0f;
-  for (int i = threadIdx.x; i < B; i += 256) s += v[i];
-  red[threadIdx.x] = s;
+  for (int i = t; i < a.B; i += 256) s += a.lrow[i];
+  red[t] = s;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+  for (int off = 128; off > 0; off >>= 1) {
+    if (t < off) red[t] += red[t + off];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = red[0] / (float)B;
-}
-
-// Adam (Kingma & Ba 2015) on the float master weights.
-__global__ void k_adam(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
-                       const float* __restrict__ g, int n, float lr, float b1, float b2, float eps,
-                       float bc1, float bc2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.0f - b1) * gi;
-  const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  w[i] -= lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
+  if (t == 0) loss[0] = red[0] / (float)a.B;
 }
 
 __global__ void k_init_params(float* __restrict__ w, uint64_t seed) {
@@ -617,19 +797,11 @@ struct fd_mlp {
   Packed pk{};
   float learned_step0 = 0.0f;
   float fallback_cost = INFINITY;
-  // training workspace
+  // training workspace, sized for cap_batch rows
   int cap_batch = 0;
-  uint16_t* x = nullptr;                 // B x 128
-  float* z[3] = {nullptr, nullptr, nullptr};  // B x 256 pre-activations
-  uint16_t* h[3] = {nullptr, nullptr, nullptr};  // B x 256 bf16 activations
-  float* dy = nullptr;                   // B x 3
-  float* lrow = nullptr;                 // B
-  float* dz = nullptr;                   // B x 256
-  uint16_t* dzq = nullptr;               // B x 256
-  float* part = nullptr;                 // chunk partial sums of the gradients
-  float* split = nullptr;                // K-slice partial tiles of the weight gradients
-  float* grad = nullptr;                 // N_PARAMS
-  float* loss = nullptr;                 // 1
+  uint16_t* acts = nullptr;  // transposed activations and gradients, bfloat16
+  float* grads = nullptr;    // transposed gradients in float, row losses
+  float* split = nullptr;    // partial weight-gradient products
 };
 
 namespace {
@@ -640,66 +812,28 @@ int mlp_pack(fd_mlp* m, hipStream_t st) {
   return e == hipSuccess ? FD_OK : hip_error(e, "mlp pack");
 }
 
+constexpr int kActCols = D0P + 6 * DH;     // xT, hT[3], dT[3]
+constexpr int kGradCols = 3 * DH + DO + 1;  // dzT[3], dyT, lrow
+
 int ensure_train_ws(fd_mlp* m, int B) {
   if (m->cap_batch >= B) return FD_OK;
-  auto fr = [](void* p) {
-    if (p) (void)hipFree(p);
-  };
-  fr(m->x);
-  for (int l = 0; l < 3; ++l) {
-    fr(m->z[l]);
-    fr(m->h[l]);
-  }
-  fr(m->dy);
-  fr(m->lrow);
-  fr(m->dz);
-  fr(m->dzq);
-  fr(m->part);
-  fr(m->split);
-  hipError_t e = hipSuccess;
-  size_t Bs = (size_t)B;
-  e = hipMalloc(&m->x, Bs * D0P * 2);
-  for (int l = 0; l < 3 && e == hipSuccess; ++l) {
-    e = hipMalloc(&m->z[l], Bs * DH * 4);
-    if (e == hipSuccess) e = hipMalloc(&m->h[l], Bs * DH * 2);
-  }
-  if (e == hipSuccess) e = hipMalloc(&m->dy, Bs * 3 * 4);
-  if (e == hipSuccess) e = hipMalloc(&m->lrow, Bs * 4);
-  if (e == hipSuccess) e = hipMalloc(&m->dz, Bs * DH * 4);
-  if (e == hipSuccess) e = hipMalloc(&m->dzq, Bs * DH * 2);
+  void* old[] = {m->acts, m->grads, m->split};
+  for (void* q : old)
+    if (q) (void)hipFree(q);
+  m->acts = nullptr;
+  m->grads = m->split = nullptr;
+  m->cap_batch = 0;
+  const size_t Bp = (size_t)(B + kRowTile - 1) / kRowTile * kRowTile;
+  hipError_t e = hipMalloc(&m->acts, Bp * kActCols * 2);
+  if (e == hipSuccess) e = hipMalloc(&m->grads, Bp * kGradCols * 4);
   if (e == hipSuccess)
-    e = hipMalloc(&m->part, (Bs / kRowChunk + 1) * (size_t)kOutGrad * 4);  // >= tiles x DH
-  if (e == hipSuccess) e = hipMalloc(&m->split, (size_t)kMaxSplit * DH * DH * 4);
-  if (e != hipSuccess) {
-    m->cap_batch = 0;
-    return hip_error(e, "mlp training workspace");
-  }
+    e = hipMalloc(&m->split, (size_t)kMaxSplit * (D0P + 2 * DH) * DH * 4);
+  if (e != hipSuccess) return hip_error(e, "mlp training workspace");
   m->cap_batch = B;
   return FD_OK;
 }
 
-int launch_gemm(const GemmArgs& g, hipStream_t st) {
-  const bool ak = g.sak == 1, bk = g.sbk == 1;
-  if ((!ak && g.sam != 1) || (!bk && g.sbn != 1) || g.N % kGemmT || (!ak && g.M % kGemmT) ||
-      (g.K / g.ksplit) % kGemmK)
-    return set_error(FD_E_INVAL, "mlp gemm: unsupported operand layout or shape");
-  dim3 grid((g.M + kGemmT - 1) / kGemmT, g.N / kGemmT, g.ksplit);
-  if (ak && bk)
-    hipLaunchKernelGGL((k_gemm_bf16<true, true>), grid, dim3(256), 0, st, g);
-  else if (ak)
-    hipLaunchKernelGGL((k_gemm_bf16<true, false>), grid, dim3(256), 0, st, g);
-  else if (bk)
-    hipLaunchKernelGGL((k_gemm_bf16<false, true>), grid, dim3(256), 0, st, g);
-  else
-    hipLaunchKernelGGL((k_gemm_bf16<false, false>), grid, dim3(256), 0, st, g);
-  if (g.ksplit > 1)
-    hipLaunchKernelGGL(k_gemm_reduce, dim3((g.M * g.N + 255) / 256), dim3(256), 0, st, g.part,
-                       g.ksplit, g.M, g.N, g.m_real, g.n_real, g.c, g.ldc);
-  hipError_t e = hipGetLastError();
-  return e == hipSuccess ? FD_OK : hip_error(e, "mlp gemm");
-}
-
-// K slices for a weight-gradient GEMM over a batch of B rows: up to
+// Batch slices of the weight-gradient products over B rows: up to
 // kMaxSplit, each at least 256 rows and a whole number of 32-row steps.
 int wgrad_split(int B) {
   int S = 1;
@@ -707,114 +841,41 @@ int wgrad_split(int B) {
   return S;
 }
 
-GemmArgs gemm_args() {
-  GemmArgs g;
-  std::memset(&g, 0, sizeof g);
-  g.ksplit = 1;
-  return g;
-}
-
-// forward with saved activations + loss + full gradient into m->grad
-int loss_grad(fd_mlp* m, const uint16_t* feats, const float* tgt, int B, hipStream_t st) {
+// Loss (may be NULL) and, by o, the full gradient or the Adam update.
+int train_pass(fd_mlp* m, const uint16_t* feats, const float* tgt, int B, const AdamDev& o,
+               float* loss, hipStream_t st) {
   int r;
   if ((r = ensure_train_ws(m, B))) return r;
-  hipLaunchKernelGGL(k_pad_input, dim3((B * D0P + 255) / 256), dim3(256), 0, st, feats, B, m->x);
-  const uint16_t* wts[3] = {m->pk.w1t, m->pk.w2t, m->pk.w3t};
-  // hidden layers: z_l = h_{l-1} W_l + b_l, h_l = bf16(gelu(z_l))
-  for (int l = 0; l < 3; ++l) {
-    GemmArgs g = gemm_args();
-    const int K = l == 0 ? D0P : DH;
-    g.a = l == 0 ? m->x : m->h[l - 1];
-    g.sam = K;
-    g.sak = 1;
-    g.b = wts[l];  // B(k, n) = Wt[n][k]
-    g.sbk = 1;
-    g.sbn = K;
-    g.M = B;
-    g.N = DH;
-    g.K = K;
-    g.m_real = B;
-    g.n_real = DH;
-    g.epi = EPI_BIAS_GELU;
-    g.c = m->z[l];
-    g.ldc = DH;
-    g.bias = m->pk.bias + l * DH;
-    g.hq = m->h[l];
-    g.ldh = DH;
-    if ((r = launch_gemm(g, st))) return r;
-  }
-  hipLaunchKernelGGL(k_out_loss, dim3((B * kOutLanes + 255) / 256), dim3(256), 0, st, m->h[2],
-                     m->pk.w4t, m->pk.bias + 3 * DH, tgt, B, m->dy, m->lrow);
-  hipLaunchKernelGGL(k_sum_rows, dim3(1), dim3(256), 0, st, m->lrow, B, m->loss);
-  const int chunks = (B + kRowChunk - 1) / kRowChunk;
-  hipLaunchKernelGGL(k_outw_partial, dim3((kOutGrad + 255) / 256, chunks), dim3(256), 0, st,
-                     m->h[2], m->dy, B, m->part);
-  hipLaunchKernelGGL(k_col_finish, dim3((kOutGrad + 3) / 4), dim3(256), 0, st, m->part, chunks,
-                     kOutGrad, m->grad + OFF_W4);
-  hipLaunchKernelGGL(k_out_back, dim3((B * DH + 255) / 256), dim3(256), 0, st, m->dy,
-                     m->pk.w4t, m->z[2], B, m->dz, m->dzq);
-  const int offW[3] = {OFF_W1, OFF_W2, OFF_W3}, offB[3] = {OFF_B1, OFF_B2, OFF_B3};
-  const int tiles = (B + kGemmT - 1) / kGemmT;
-  for (int l = 2; l >= 0; --l) {
-    // bias gradient of layer l: sums of the float dz over the batch, as row
-    // chunk partials (k_out_back's dz for the last hidden layer, the
-    // previous input-gradient product's tile partials for the others)
-    if (l == 2)
-      hipLaunchKernelGGL(k_col_partial, dim3(1, chunks), dim3(DH), 0, st, m->dz, B, DH, m->part);
-    hipLaunchKernelGGL(k_col_finish, dim3(DH / 4), dim3(256), 0, st, m->part,
-                       l == 2 ? chunks : tiles, DH, m->grad + offB[l]);
-    // weight gradient: dW_l[k][n] = sum_b h_{l-1}[b][k] dzq[b][n]
-    {
-      GemmArgs g = gemm_args();
-      const int Kin = l == 0 ? D0P : DH;
-      g.a = l == 0 ? m->x : m->h[l - 1];  // A(m = k_in, k = b)
-      g.sam = 1;
-      g.sak = Kin;
-      g.b = m->dzq;  // B(k = b, n) = dzq[b][n]
-      g.sbk = DH;
-      g.sbn = 1;
-      g.M = Kin;
-      g.N = DH;
-      g.K = B;
-      g.m_real = l == 0 ? D0 : DH;
-      g.n_real = DH;
-      g.epi = EPI_STORE;
-      g.c = m->grad + offW[l];
-      g.ldc = DH;
-      g.ksplit = wgrad_split(B);
-      g.part = m->split;
-      if ((r = launch_gemm(g, st))) return r;
-    }
-    if (l == 0) break;
-    // dz_{l-1} = (dzq W_l^T) * gelu'(z_{l-1})
-    {
-      GemmArgs g = gemm_args();
-      const int Kin = DH;  // rows of W_l for l >= 1
-      g.a = m->dzq;        // A(m = b, k = out) = dzq[b][out]
-      g.sam = DH;
-      g.sak = 1;
-      g.b = wts[l];  // B(k = out, n = in) = W_l[in][out] = Wt[out][in]
-      g.sbk = Kin;
-      g.sbn = 1;
-      g.M = B;
-      g.N = Kin;
-      g.K = DH;
-      g.m_real = B;
-      g.n_real = Kin;
-      g.epi = EPI_GELU_BACK;
-      g.c = m->z[l - 1];
-      g.ldc = DH;
-      // the new bfloat16 gradient goes to h[l] (no longer needed: h[l]'s
-      // weight gradient is done), its bias-gradient partials to part
-      g.df = m->part;
-      g.hq = m->h[l];
-      g.ldh = DH;
-      if ((r = launch_gemm(g, st))) return r;
-    }
-    std::swap(m->dzq, m->h[l]);
-  }
+  TrainDev a;
+  a.feats = feats;
+  a.tgt = tgt;
+  a.B = B;
+  a.Bp = (B + kRowTile - 1) / kRowTile * kRowTile;
+  a.pk = m->pk;
+  uint16_t* p = m->acts;
+  a.xT = p;
+  p += (size_t)D0P * a.Bp;
+  for (int l = 0; l < 3; ++l, p += (size_t)DH * a.Bp) a.hT[l] = p;
+  for (int l = 0; l < 3; ++l, p += (size_t)DH * a.Bp) a.dT[l] = p;
+  float* f = m->grads;
+  for (int l = 0; l < 3; ++l, f += (size_t)DH * a.Bp) a.dzT[l] = f;
+  a.dyT = f;
+  a.lrow = f + (size_t)DO * a.Bp;
+  const int S = wgrad_split(B);
+  // Rows per workgroup.  Its time is mostly its chain of layers, and each
+  // workgroup reads all weights: 16 rows while every compute unit (256) then
+  // has at most one workgroup, 32 from there on.  A step of batch 4096: 50
+  // (16 rows) / 59 us (32); 6144: 78 / 63; 8192: 84 / 68; 65536: 645 / 493.
+  // 64 rows (registers spill): 112 us at 4096, 146 against 120 at 16384.
+  if (a.Bp <= 16 * 256)
+    hipLaunchKernelGGL(k_train_rows<16>, dim3(a.Bp / 16), dim3(kTrainThreads), 0, st, a);
+  else
+    hipLaunchKernelGGL(k_train_rows<32>, dim3(a.Bp / 32), dim3(kTrainThreads), 0, st, a);
+  hipLaunchKernelGGL(k_train_wgrad, dim3(kWgradTiles, S), dim3(256), 0, st, a, S, m->split);
+  hipLaunchKernelGGL(k_train_finish, dim3(kFinTiles + kFinWaves + 1), dim3(256), 0, st, a, S,
+                     m->split, o, loss);
   hipError_t e = hipGetLastError();
-  return e == hipSuccess ? FD_OK : hip_error(e, "mlp backward");
+  return e == hipSuccess ? FD_OK : hip_error(e, "mlp training");
 }
 
 }  // namespace
@@ -841,11 +902,11 @@ extern "C" int fd_mlp_create(fd_mlp** out, uint64_t seed) {
   hipError_t e = hipMalloc(&m->master, N_PARAMS * 4);
   if (e == hipSuccess) e = hipMalloc(&m->adam_m, N_PARAMS * 4);
   if (e == hipSuccess) e = hipMalloc(&m->adam_v, N_PARAMS * 4);
-  if (e == hipSuccess) e = hipMalloc(&m->grad, N_PARAMS * 4);
-  if (e == hipSuccess) e = hipMalloc(&m->loss, 4);
   if (e == hipSuccess) e = hipMalloc(&m->pk.w1t, DH * D0P * 2);
   if (e == hipSuccess) e = hipMalloc(&m->pk.w2t, DH * DH * 2);
   if (e == hipSuccess) e = hipMalloc(&m->pk.w3t, DH * DH * 2);
+  if (e == hipSuccess) e = hipMalloc(&m->pk.w2n, DH * DH * 2);
+  if (e == hipSuccess) e = hipMalloc(&m->pk.w3n, DH * DH * 2);
   if (e == hipSuccess) e = hipMalloc(&m->pk.w4t, DOP * DH * 2);
   if (e == hipSuccess) e = hipMalloc(&m->pk.bias, (3 * DH + DOP) * 4);
   if (e != hipSuccess) {
@@ -872,9 +933,8 @@ extern "C" int fd_mlp_create(fd_mlp** out, uint64_t seed) {
 extern "C" void fd_mlp_destroy(fd_mlp* m) {
   if (!m) return;
   (void)hipDeviceSynchronize();
-  void* bufs[] = {m->master, m->adam_m, m->adam_v, m->grad, m->loss, m->pk.w1t, m->pk.w2t,
-                  m->pk.w3t, m->pk.w4t, m->pk.bias, m->x, m->dy, m->lrow, m->dz, m->dzq,
-                  m->part, m->split, m->z[0], m->z[1], m->z[2], m->h[0], m->h[1], m->h[2]};
+  void* bufs[] = {m->master, m->adam_m, m->adam_v, m->pk.w1t, m->pk.w2t, m->pk.w3t, m->pk.w2n,
+                  m->pk.w3n, m->pk.w4t, m->pk.bias, m->acts, m->grads, m->split};
   for (void* p : bufs)
     if (p) (void)hipFree(p);
   delete m;
@@ -1015,11 +1075,9 @@ extern "C" int fd_mlp_loss_grad(fd_mlp* m, const void* feats, const float* tgt, 
   int r;
   if ((r = check_train(m, feats, tgt, batch, "fd_mlp_loss_grad"))) return r;
   if (!grad) return set_error(FD_E_INVAL, "fd_mlp_loss_grad: grad is NULL");
-  hipStream_t st = (hipStream_t)stream;
-  if ((r = loss_grad(m, (const uint16_t*)feats, tgt, batch, st))) return r;
-  hipError_t e = hipMemcpyAsync(grad, m->grad, N_PARAMS * 4, hipMemcpyDeviceToDevice, st);
-  if (e == hipSuccess && loss) e = hipMemcpyAsync(loss, m->loss, 4, hipMemcpyDeviceToDevice, st);
-  return e == hipSuccess ? FD_OK : hip_error(e, "fd_mlp_loss_grad");
+  AdamDev o{};
+  o.grad = grad;
+  return train_pass(m, (const uint16_t*)feats, tgt, batch, o, loss, (hipStream_t)stream);
 }
 
 extern "C" int fd_mlp_train_step(fd_mlp* m, const void* feats, const float* tgt, int32_t batch,
@@ -1027,17 +1085,12 @@ extern "C" int fd_mlp_train_step(fd_mlp* m, const void* feats, const float* tgt,
   int r;
   if ((r = check_train(m, feats, tgt, batch, "fd_mlp_train_step"))) return r;
   if (!opt) return set_error(FD_E_INVAL, "fd_mlp_train_step: opt is NULL");
-  hipStream_t st = (hipStream_t)stream;
-  if ((r = loss_grad(m, (const uint16_t*)feats, tgt, batch, st))) return r;
-  m->step += 1;
-  const double bc1 = 1.0 - std::pow((double)opt->beta1, (double)m->step);
-  const double bc2 = 1.0 - std::pow((double)opt->beta2, (double)m->step);
-  hipLaunchKernelGGL(k_adam, dim3((N_PARAMS + 255) / 256), dim3(256), 0, st, m->master, m->adam_m,
-                     m->adam_v, m->grad, N_PARAMS, opt->lr, opt->beta1, opt->beta2, opt->eps,
-                     (float)bc1, (float)bc2);
-  if ((r = mlp_pack(m, st))) return r;
-  hipError_t e = hipSuccess;
-  if (loss) e = hipMemcpyAsync(loss, m->loss, 4, hipMemcpyDeviceToDevice, st);
-  if (e == hipSuccess) e = hipGetLastError();
-  return e == hipSuccess ? FD_OK : hip_error(e, "fd_mlp_train_step");
+  const int64_t step = m->step + 1;
+  const double bc1 = 1.0 - std::pow((double)opt->beta1, (double)step);
+  const double bc2 = 1.0 - std::pow((double)opt->beta2, (double)step);
+  const AdamDev o{m->master,  m->adam_m,  m->adam_v, nullptr,    opt->lr,
+                  opt->beta1, opt->beta2, opt->eps,  (float)bc1, (float)bc2};
+  if ((r = train_pass(m, (const uint16_t*)feats, tgt, batch, o, loss, (hipStream_t)stream))) return r;
+  m->step = step;
+  return FD_OK;
 }

@@ -76,3 +76,42 @@ def test_growing_bit_for_bit(dims, max_steps, bend, mode):
         assert np.array_equal(v[i, :nv[i]], o["verts"][i, :nv[i]]), i
     assert np.array_equal(last.cpu().numpy(), o["last_dir"])
     assert np.array_equal(cr.cpu().numpy().view(np.uint32), o["crossings"])
+
+
+@pytest.mark.parametrize("batch", [32, 96, 4096, 4128, 8224])
+def test_training_batches(batch):
+    """Gradients against the bfloat16 oracle (tolerances of the gradient
+    test) at a padded row tile, the last batch of 16-row workgroups, the
+    first of 32-row ones and a batch that cannot be split; then an Adam step,
+    after which the matrix-core copies of the weights have to be the master
+    weights'."""
+    nat = _native()
+    rng = np.random.default_rng(batch)
+    parts = []
+    for (W, b) in oracle.mlp_split(np.zeros(oracle.mlp_n_params())):
+        parts += [rng.normal(0, 1.0 / np.sqrt(W.shape[0]), W.size), rng.normal(0, 0.1, b.size)]
+    p = np.concatenate(parts).astype(np.float32)
+    x = oracle.round_bf16(rng.normal(0, 1, (batch, 112)).astype(np.float32))
+    t = rng.normal(size=(batch, 3))
+    t = (t / np.linalg.norm(t, axis=1, keepdims=True)).astype(np.float32)
+    net = nat.MLP(seed=0)
+    net.set_params(p)
+    xd = _t(x).to(torch.bfloat16)
+    loss, grad = net.loss_grad(xd, _t(t))
+    g = grad.cpu().numpy().astype(np.float64)
+    lo, go = oracle.mlp_loss_grad(p.astype(np.float64), x, t, bf16=True)
+    assert abs(float(loss.item()) - lo) <= 1e-3 * max(1.0, abs(lo))
+    off = 0
+    for (W, b) in oracle.mlp_split(np.zeros(oracle.mlp_n_params())):
+        for size in (W.size, b.size):
+            r = go[off:off + size]
+            assert np.linalg.norm(g[off:off + size] - r) <= 1e-2 * np.linalg.norm(r), off
+            off += size
+    step_loss = torch.empty(1, device=DEV)
+    net.train_step(xd, _t(t), lr=1e-3, loss=step_loss)
+    assert float(step_loss.item()) == float(loss.item())
+    other = nat.MLP(seed=1)
+    other.set_params(net.get_params())
+    assert torch.equal(net.forward(xd), other.forward(xd))
+    a, b = net.loss_grad(xd, _t(t)), other.loss_grad(xd, _t(t))
+    assert torch.equal(a[1], b[1]) and torch.equal(a[0], b[0])

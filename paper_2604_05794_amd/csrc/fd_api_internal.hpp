@@ -63,6 +63,7 @@ struct fd_context {
   float* gabor_bank = nullptr;
   size_t cap_gabor_bank = 0;
   uint64_t gabor_sig = 0;
+  float gabor_margin[2] = {};  // of the bank (choice_margin)
   float* gabor_raw = nullptr;
   size_t cap_gabor_raw = 0;
   uint32_t* gabor_max = nullptr;

@@ -3,12 +3,12 @@
 // its reading is documented with fd_orientation_maps in fusedir.h).
 //
 // k_gabor_mfma: the filter bank is a dense contraction over the taps, run on
-// the fp32 matrix cores.  Persistent workgroups of four waves hold the bank
-// in LDS and walk 16 x 32 pixel tiles, each staged in LDS with its radius-R
-// halo; the epilogue takes the argmax orientation and the raw confidence, and
-// the workgroup's largest raw confidence goes to the frame maximum (an
-// integer atomic on the bits of a non-negative float).  k_gabor_norm divides
-// by that maximum.
+// the binary16 matrix cores with both factors split in two.  Persistent
+// workgroups of eight waves hold the bank in LDS and walk 16 x 64 pixel
+// tiles, each staged in LDS with its radius-R halo; the epilogue takes the
+// argmax orientation and the raw confidence, and the workgroup's largest raw
+// confidence goes to the frame maximum (an integer atomic on the bits of a
+// non-negative float).  k_gabor_norm divides by that maximum.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -77,54 +77,157 @@ __global__ __launch_bounds__(256) void k_gabor_norm(const float* __restrict__ ra
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr int kRowsPerWave = 8;
-constexpr int kMfmaRows = 4 * kRowsPerWave;  // tile rows: four waves
-constexpr int kTw = kTile + 2 * kMaxRadius;  // LDS tile row stride for every radius
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// The filter bank as a matrix product on the fp32 matrix cores: for a row
-// of 16 pixels, F[orientation][pixel] = sum_tap G[orientation][tap] I[pixel + tap]
-// in steps of 4 taps (v_mfma_f32_16x16x4f32: A = 16 orientations x 4 bank
-// taps, B = the 4 x 16 image patch gathered from the LDS tile).  Persistent
-// workgroups keep the bank in LDS, zero-padded to whole 4-tap steps and
-// 16-orientation tiles and laid out [tap / 4][orientation tile][tap % 4][16]
-// so that a wave's A operand is 64 consecutive words; they walk pixel tiles
-// 16 wide and 32 high, wave w owning rows 8w .. 8w + 7, so each bank read
-// feeds 8 matrix operations.  The tile rows are kTw words apart for every
-// radius: the 8 row reads of a step take immediate offsets and pair up.  The
-// matrix cores only reach their peak when little else is issued beside them,
-// so the per-step bookkeeping is kept small: the position of the step's first
-// tap is wave-uniform (scalar registers) and a lane's tap is at most one row
-// further.  In the result lane (g, c) = (lane / 16, lane % 16) holds
-// orientations 16 nt + 4 g + r (r < 4) of pixel c: the argmax (first of
-// equals) and the confidence sum run over those 4 NT values in the lane, then
-// across the four 16-lane groups; the squared bin distances come from a
-// small LDS table.
-// FULL: n_orient fills the NT orientation tiles (no per-lane validity
-// tests).  Three waves per SIMD is what the LDS allows (three workgroups per
-// CU at radius 8); the register bound keeps the compiler to it.
-template <typename TO, int NT, bool FULL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_gabor_mfma(const float* __restrict__ frames, int W,
-                                                    int H, int R, int NO,
-                                                    const float* __restrict__ bank,
-                                                    int64_t n_tiles, int tiles_x,
-                                                    int64_t tiles_per_frame,
-                                                    void* __restrict__ theta_out,
-                                                    float* __restrict__ raw,
-                                                    uint32_t* __restrict__ frame_max) {
-  extern __shared__ float lds[];
-  __shared__ float wmax[256 / 64];
-  constexpr int NJ = 16 * NT;
-  const int w2 = 2 * R + 1, taps = w2 * w2, kpad = (taps + 3) & ~3, tw = kTile + 2 * R;
-  const int th = kMfmaRows + 2 * R;  // tile rows with the halo
-  float* sbank = lds;              // kpad x NJ
-  float* tile = lds + kpad * NJ;   // th x kTw
-  for (int e = threadIdx.x; e < kpad * NJ; e += blockDim.x) {
-    const int t = e / NJ, j = e - t * NJ;
-    const int dst = (t >> 2) * 4 * NJ + (j >> 4) * 64 + (t & 3) * 16 + (j & 15);
-    sbank[dst] = (t < taps && j < NO) ? bank[(size_t)t * NO + j] : 0.0f;
+constexpr int kThreads = 512;
+constexpr int kWaves = kThreads / 64;
+constexpr int kRowsPerWave = 8;
+constexpr int kTileRows = kWaves * kRowsPerWave;  // 64
+constexpr float kBankScale = 16384.0f;            // 2^14: |g| <= 2 stays below 2^15
+
+// The taps of the (2R + 1)^2 window in groups of 8, two groups per matrix
+// operation: 8 columns of a row (columns 8c .. 8c + 7, rows 0 .. 2R and one
+// of padding, so that an operation takes two rows of one c), then the columns
+// that are left over.  A leftover of 1 or 3 columns takes groups of 8 rows of
+// one column where that is fewer groups than another (padded) c.
+struct Taps {
+  int w;        // window edge
+  int cols;     // column groups c
+  int steps;    // matrix steps (16 taps)
+  int rows8;    // groups of 8 rows in a column
+  int left;     // leftover columns in groups of rows
+
+  __host__ __device__ explicit Taps(int R) {
+    w = 2 * R + 1;
+    rows8 = (w + 7) / 8;
+    left = w % 8;
+    if (left * rows8 >= w) left = 0;
+    cols = (w - left + 7) / 8;
+    steps = (cols * (w + 1) + left * rows8 + 1) / 2;
+  }
+  // tap i (0..7) of group q: its row and column, false if it is padding
+  __host__ __device__ bool tap(int q, int i, int* dy, int* dx) const {
+    const int v = q - cols * (w + 1);
+    if (v < 0) {
+      *dy = q % (w + 1);
+      *dx = 8 * (q / (w + 1)) + i;
+    } else {
+      *dy = 8 * (v % rows8) + i;
+      *dx = 8 * cols + v / rows8;
+    }
+    return *dy < w && *dx < w;
+  }
+};
+
+// LDS of a workgroup, in 4-byte words.  The tile is 64 pixel rows of 16
+// with the window's halo (and the rows that padded taps touch), RS pixels a
+// row, split in two binary16 halves (high and low), each in an even and an
+// odd copy (the odd one a pixel further) so that 8 pixels from any column
+// start on a word.  The even and odd copies lie 8 banks apart and rows 16 or
+// 20, so that the 64 lanes of a read (two pixel rows, 8 words each from
+// either copy, and the same a tap row further) touch no bank twice.
+struct GaborLds {
+  int RS, th, plane, bank, planes, d2, total;
+  __host__ __device__ explicit GaborLds(int R) {
+    const Taps t(R);
+    RS = R <= 8 ? 32 : 40;
+    th = kTileRows + 8 * t.rows8;
+    plane = ((th * RS / 2 + 63) & ~63) + 8;
+    bank = 0;
+    planes = t.steps * 2 * 64 * 4;
+    d2 = planes + 4 * plane;
+    total = d2 + 64;
+  }
+};
+
+// The filter bank as a matrix product on the matrix cores,
+// F[orientation][pixel] = sum_tap G[orientation][tap] I[pixel + tap]: 32
+// orientations x 16 taps times 16 taps x 32 pixels per operation
+// (v_mfma_f32_32x32x16_f16, accumulated in float).  Both factors are split
+// into a high and a low binary16 half (22 bits: v = h + l + r, |r| <= 2^-22
+// |v|; the tile scaled by a power of two so that its largest pixel is near
+// 2^14, the bank by 2^14), and three products h l + l h + h h stand for one:
+// 16 times the rate of the binary32 matrix operation, a third of it used.
+// The operation rounds its sum twice per 16 taps (each half of its taps, as
+// measured), the binary32 one once per tap, so the responses are nearer to
+// the exact ones than a binary32 sum in order.
+//
+// Persistent workgroups of eight waves keep the split bank in LDS and walk
+// pixel tiles 16 wide and 64 high, wave w owning rows 8w .. 8w + 7 as four
+// groups of 32 pixels (two rows).  A step takes two tap rows, so what group q
+// reads at one step group q - 1 reads at the next: the image operands stay in
+// registers and move down by one group, and only the last group's is loaded
+// (reading all four made the LDS the bound).  In the result lane (h, n) = (lane / 32, lane % 32)
+// holds orientations 8 q + 4 h + r (q, r < 4) of pixel n: the argmax (first
+// of equals) and the confidence sum run over those 16 values in the lane,
+// then across the two halves; the squared bin distances come from a small
+// LDS table.
+//
+// The choice of the orientation.  Where two responses nearly agree the
+// rounding of the sum decides, so the choice is defined by one sum: binary32
+// fused multiply-adds over all taps in order (which the 16x16x4 binary32
+// matrix operation evaluates).  A pixel whose best response leads by less
+// than the two sums can differ (their rounding bounds: choice_margin) is
+// summed again that way; its confidence is then taken from that sum.  Those
+// pixels, a hundredth of a frame or two, wait in LDS until there are 16 for
+// each wave.  In a constant, non-zero region every response is rounding and
+// every pixel's the same: one of a wave's 128 pixels waits and stands for
+// all (kFixAll).  Where most of a wave's pixels wait (smooth regions without
+// any noise) the wave sums its rows at once (dense).
+// Bound by the matrix operations (half of their issue slots; the clock drops
+// to 1.8 GHz under them) and the epilogue's 630 vector instructions a tile
+// and wave.  64 frames of 1024 x 1024, radius 8, 32 orientations, on the maps
+// of rendered hair: 10.4 -> 4.6 ms (binary32 operations only before; 4.2 ms
+// without a second sum); 16 frames of noise 2.82 -> 1.30 ms, of a constant
+// 2.61 -> 1.85 ms, of a linear ramp without noise (every pixel summed twice,
+// the worst case) 2.65 -> 4.5 ms.
+// FULL: 32 orientations (no validity tests).
+constexpr int kFixRound = 16 * kWaves;
+constexpr int kFixCap = kFixRound + kTile * kTileRows;  // a round less one, plus a tile's
+constexpr int kDense = 48;  // more waiting pixels of a wave's 128: all summed at once
+constexpr int kFixAll = 1 << 30;  // a pixel index stays below 2^30
+
+// Per bank, in units of 2^-24: the rounding bounds of both sums for a window
+// whose pixels lie within `half` of `mid`, per unit of mid and half.
+struct GaborMargin {
+  float mid, half;
+};
+
+template <typename TO, int RS, bool FULL>
+__global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
+    const float* __restrict__ frames, int W, int H, int R, int NO, const float* __restrict__ bank,
+    GaborMargin margin, Taps taps8, GaborLds L, int n_tiles, int tiles_x, int tiles_per_frame,
+    void* __restrict__ theta_out, float* __restrict__ raw, uint32_t* __restrict__ frame_max) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+  __shared__ float wred[kWaves];
+  __shared__ int wlost[kWaves];  // the wave staged a non-zero pixel as 0
+  __shared__ int2 fix[kFixCap];  // (frame, pixel) to be summed again
+  __shared__ int n_fix;
+  constexpr int kLoads = (kTileRows + 32) * RS / kThreads + 1;
+  const int w2 = 2 * R + 1, taps = w2 * w2, tw = kTile + 2 * R;
+  float* d2tab = (float*)(lds + L.d2);
+  const int lane = (int)(threadIdx.x & 63u);
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int g = lane >> 4, c16 = lane & 15, hf = lane >> 5;
+  // the split bank, [step][high, low][lane] 8 taps of orientation lane % 32
+  for (int e = threadIdx.x; e < taps8.steps * 64; e += kThreads) {
+    const int st = e >> 6, l = e & 63, m = l & 31;
+    f16x8 hi, lo;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      int dy, dx;
+      const bool on = taps8.tap(2 * st + (l >> 5), i, &dy, &dx) && m < NO;
+      const float v = on ? bank[(size_t)(dy * w2 + dx) * NO + m] * kBankScale : 0.0f;
+      hi[i] = (_Float16)v;
+      lo[i] = (_Float16)(v - (float)hi[i]);
+    }
+    *(f16x8*)(lds + L.bank + (st * 2 * 64 + l) * 4) = hi;
+    *(f16x8*)(lds + L.bank + ((st * 2 + 1) * 64 + l) * 4) = lo;
   }
   // d2tab[NO + k] = squared line distance of two bins k apart (|k| < NO)
-  float* d2tab = tile + kTw * th;  // 64
   if (threadIdx.x < 64) {
     const int k = abs((int)threadIdx.x - NO);
     float v = 0.0f;
@@ -134,115 +237,432 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     }
     d2tab[threadIdx.x] = v;
   }
-  const int lane = (int)(threadIdx.x & 63u), w = (int)(threadIdx.x >> 6);
-  const int g = lane >> 4, c16 = lane & 15;
+  if (threadIdx.x == 0) n_fix = 0;
   const size_t plane = (size_t)W * H;
-  for (int64_t tid = blockIdx.x; tid < n_tiles; tid += gridDim.x) {
-    const int64_t f = tid / tiles_per_frame;
-    const int64_t rem = tid - f * tiles_per_frame;
-    const int ty = (int)(rem / tiles_x), tx = (int)(rem - (int64_t)ty * tiles_x);
-    const int x0 = tx * kTile, y0 = ty * kMfmaRows;
-    const float* img = frames + plane * f;
-    __syncthreads();  // the bank is in place; the previous tile is no longer read
-    for (int e = threadIdx.x; e < kTw * th; e += blockDim.x) {
-      const int yy = e / kTw, xx = e - yy * kTw;
-      const int x = x0 + xx - R, y = y0 + yy - R;
-      tile[e] = (xx < tw && x >= 0 && x < W && y >= 0 && y < H) ? img[(size_t)y * W + x] : 0.0f;
+
+  // Orientation and raw confidence of one pixel whose responses 2 or 4 lanes
+  // hold, lane part `p0` the orientations p0 + step * (k / 4) + k % 4.
+  auto choose = [&](auto& fv, int p0, int step, int first_xor, float mg, int& jb, float& conf,
+                    bool& near) {
+    constexpr int K = sizeof(fv) / sizeof(float);
+    float fb = -1.0f, f2 = -1.0f;  // the largest and the second largest
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (!FULL && p0 + step * (k / 4) + k % 4 >= NO) fv[k] = -1.0f;
+      f2 = __builtin_amdgcn_fmed3f(fv[k], fb, f2);
+      fb = fmaxf(fb, fv[k]);
     }
-    __syncthreads();
-    f32x4 acc[kRowsPerWave][NT];
+    for (int off = first_xor; off < 64; off <<= 1) {
+      const float o1 = __shfl_xor(fb, off, 64), o2 = __shfl_xor(f2, off, 64);
+      f2 = fmaxf(fminf(fb, o1), fmaxf(f2, o2));
+      fb = fmaxf(fb, o1);
+    }
+    jb = 1 << 30;  // the first that equals the largest
 #pragma unroll
-    for (int p = 0; p < kRowsPerWave; ++p)
+    for (int k = K - 1; k >= 0; --k) jb = fv[k] == fb ? p0 + step * (k / 4) + k % 4 : jb;
+    for (int off = first_xor; off < 64; off <<= 1) jb = min(jb, __shfl_xor(jb, off, 64));
+    jb = jb < NO ? jb : 0;  // (no response equals a NaN)
+    float s = 0.0f;
+    const float* d2 = d2tab + (NO + p0 - jb);
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[p][nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    const float* base = tile + kRowsPerWave * w * kTw + c16 + g;
-    const float* bk = sbank + lane;
-    // wave-uniform (row offset, column) of tap k0; a lane's tap k0 + g is at
-    // most one row further (g < 4 <= w2 + 1 and the column stays < w2)
-    int s_off = 0, s_dx = 0;
-    for (int k0 = 0; k0 < kpad; k0 += 4) {
-      const int wrap = g >= w2 - s_dx ? kTw - w2 : 0;
-      const int off = k0 + g < taps ? s_off + wrap : -g;
-      float a[NT];
+    for (int k = 0; k < K; ++k) {
+      const int o = step * (k / 4) + k % 4;
+      const float e = FULL || p0 + o < NO ? fv[k] - fb : 0.0f;
+      s = __builtin_fmaf(d2[o], e * e, s);
+    }
+    for (int off = first_xor; off < 64; off <<= 1) s += __shfl_xor(s, off, 64);
+    conf = sqrtf(s);
+    near = !(fb - f2 >= mg);
+  };
+  // The waiting pixels fix[first .. first + count), 16 per wave, summed over
+  // all taps in order from the frame itself.
+  auto fix_round = [&](int first, int count) {
+    if (16 * w >= count) return;  // wave-uniform
+    const bool on = 16 * w + c16 < count;
+    int2 q = fix[first + (on ? 16 * w + c16 : 0)];
+    const bool all = q.y & kFixAll;
+    q.y &= kFixAll - 1;
+    const float* img = frames + plane * (size_t)q.x;
+    const int py = q.y / W, px = q.y - py * W;
+    f32x4 acc[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
+    int y = py - R, x = px - R + g;
+    const int right = px + R;
+    if (x > right) {  // w2 = 3
+      x -= w2;
+      ++y;
+    }
+    // orientations and taps past the last read it; such responses are not
+    // looked at and such taps multiply 0
+    const float* b0 = bank + (FULL ? c16 : min(c16, NO - 1));
+    const int b1 = FULL ? 16 : min(16 + c16, NO - 1) - min(c16, NO - 1);
+    constexpr int kAhead = 8;  // steps whose loads are in flight together
+    for (int k0 = 0; k0 < taps; k0 += 4 * kAhead) {
+      float v[kAhead], a[kAhead][2];
+      bool in[kAhead];
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) a[nt] = bk[k0 * NJ + 64 * nt];
-      const float* src = base + off;
+      for (int u = 0; u < kAhead; ++u) {
+        const int t = k0 + 4 * u + g;
+        in[u] = t < taps && (unsigned)x < (unsigned)W && (unsigned)y < (unsigned)H;
+        v[u] = img[in[u] ? (uint32_t)(y * W + x) : 0u];
+        const float* bt = b0 + (uint32_t)(min(t, taps - 1) * NO);
+        a[u][0] = bt[0];
+        a[u][1] = bt[b1];
+        x += 4;
+        if (x > right) { x -= w2; ++y; }
+        if (x > right) { x -= w2; ++y; }
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const float vu = in[u] ? v[u] : 0.0f;
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+          acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][nt], vu, acc[nt], 0, 0, 0);
+      }
+    }
+    int jb;
+    float wv;
+    float fv[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) fv[k] = fabsf(acc[k / 4][k % 4]);
+    bool near;
+    choose(fv, 4 * g, 16, 16, 0.0f, jb, wv, near);
+    const float th = (float)jb * (kPi / NO);
+    if (g == 0 && on) {
+      const size_t i = plane * (size_t)q.x + q.y;
+      store_map<TO>(theta_out, i, th);
+      raw[i] = wv;
+      // few of these pixels raise their frame's maximum (a NaN none)
+      const uint32_t top = __float_as_uint(fmaxf(wv, 0.0f));
+      if (top > __atomic_load_n(&frame_max[q.x], __ATOMIC_RELAXED)) atomicMax(&frame_max[q.x], top);
+    }
+    // a pixel that stands for its wave's: 64 lanes store them
+    for (uint64_t b = __ballot(all && on && g == 0); b; b &= b - 1) {
+      const int l = __ffsll((unsigned long long)b) - 1;
+      const size_t at = plane * (size_t)__shfl(q.x, l, 64);
+      const int x0 = __shfl(px, l, 64), y0 = __shfl(py, l, 64);
+      const float tl = __shfl(th, l, 64), wl = __shfl(wv, l, 64);
+      for (int dy = g; dy < kRowsPerWave; dy += 4)
+        if (x0 + c16 < W && y0 + dy < H) {
+          const size_t i = at + (size_t)(y0 + dy) * W + (x0 + c16);
+          store_map<TO>(theta_out, i, tl);
+          raw[i] = wl;
+        }
+    }
+  };
+  // The same sum for all 128 pixels of a wave (8 rows from (x0, y0)) whose
+  // window lies in the frame, one bank operand for its rows; returns the
+  // lane's largest confidence.
+  auto dense = [&](int f, int x0, int y0) {
+    const float* img = frames + plane * (size_t)f + (size_t)(y0 - R) * W + (x0 - R);
+    f32x4 acc[kRowsPerWave][2];
+#pragma unroll
+    for (int p = 0; p < kRowsPerWave; ++p) acc[p][0] = acc[p][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const float* b0 = bank + (FULL ? c16 : min(c16, NO - 1));
+    const int b1 = FULL ? 16 : min(16 + c16, NO - 1) - min(c16, NO - 1);
+    const int px = x0 + c16;
+    int dx = g;
+    uint32_t at = (uint32_t)(c16 + g);
+    if (dx >= w2) {  // w2 = 3
+      dx -= w2;
+      at += (uint32_t)(W - w2);
+    }
+    for (int k0 = 0; k0 < taps; k0 += 4) {
+      const bool on = k0 + g < taps;  // past the last tap: pixel 0
+      const float* bt = b0 + (uint32_t)((on ? k0 + g : 0) * NO);
+      const float a0 = bt[0], a1 = bt[b1];
+      const uint32_t ot = on ? at : (uint32_t)c16;
+      float v[kRowsPerWave];
+#pragma unroll
+      for (int p = 0; p < kRowsPerWave; ++p) v[p] = (img + (size_t)p * W)[ot];
 #pragma unroll
       for (int p = 0; p < kRowsPerWave; ++p) {
-        const float v = src[p * kTw];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          acc[p][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[nt], v, acc[p][nt], 0, 0, 0);
+        v[p] = on ? v[p] : 0.0f;
+        acc[p][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, v[p], acc[p][0], 0, 0, 0);
+        acc[p][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, v[p], acc[p][1], 0, 0, 0);
       }
-      // issue order: the step's LDS reads (the bank, then the row pairs),
-      // then its matrix operations
-      __builtin_amdgcn_sched_group_barrier(0x100, 5, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, kRowsPerWave * NT, 0);
-      s_dx += 4;
-      s_off += 4;
-      if (s_dx >= w2) { s_dx -= w2; s_off += kTw - w2; }
-      if (s_dx >= w2) { s_dx -= w2; s_off += kTw - w2; }
+      dx += 4;
+      at += 4;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const bool wrap = dx >= w2;
+        dx -= wrap ? w2 : 0;
+        at += wrap ? (uint32_t)(W - w2) : 0u;
+      }
     }
-    // per pixel: argmax |F_j| (first of equals), then the spread of the
-    // responses around it
     float m = 0.0f;
 #pragma unroll
     for (int p = 0; p < kRowsPerWave; ++p) {
-      float fv[NT][4];
-      float fb = -1.0f;
-      int jb = 0;
+      float fv[8], wv;
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int j = 16 * nt + 4 * g + r;  // increasing in the lane
-          fv[nt][r] = (FULL || j < NO) ? fabsf(acc[p][nt][r]) : -1.0f;
-          if (fv[nt][r] > fb) {
-            fb = fv[nt][r];
-            jb = j;
-          }
-        }
-#pragma unroll
-      for (int off = 16; off < 64; off <<= 1) {
-        const float of = __shfl_xor(fb, off, 64);
-        const int oj = __shfl_xor(jb, off, 64);
-        if (of > fb || (of == fb && oj < jb)) {
-          fb = of;
-          jb = oj;
-        }
-      }
-      float s = 0.0f;
-      const float* d2 = d2tab + (NO + 4 * g - jb);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int j = 16 * nt + 4 * g + r;
-          if (FULL || j < NO) {
-            const float e = fv[nt][r] - fb;
-            s = __builtin_fmaf(d2[16 * nt + r], e * e, s);
-          }
-        }
-      s += __shfl_xor(s, 16, 64);
-      s += __shfl_xor(s, 32, 64);
-      const float wv = sqrtf(s);
-      const int x = x0 + c16, y = y0 + kRowsPerWave * w + p;
-      if (g == 0 && x < W && y < H) {
-        const size_t i = plane * f + (size_t)y * W + x;
+      for (int k = 0; k < 8; ++k) fv[k] = fabsf(acc[p][k / 4][k % 4]);
+      int jb;
+      bool near;
+      choose(fv, 4 * g, 16, 16, 0.0f, jb, wv, near);
+      if (g == 0 && px < W && y0 + p < H) {
+        const size_t i = plane * (size_t)f + (size_t)(y0 + p) * W + px;
         store_map<TO>(theta_out, i, (float)jb * (kPi / NO));
         raw[i] = wv;
         m = fmaxf(m, wv);
       }
     }
+    return m;
+  };
+
+  // A tile's pixels, kLoads a thread; the loads are unconditional (outside
+  // the frame at its first pixel, then dropped), so that they go out together.
+  uint32_t keep = 0;  // bit u: tv[u] is a pixel of the frame
+  const int lx = (int)threadIdx.x % RS, ly = (int)threadIdx.x / RS;
+  auto load_tile = [&](int f, int x0, int y0, float (&tv)[kLoads]) {
+    const float* img = frames + plane * (size_t)f;
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const int e = (int)threadIdx.x + u * kThreads;
+      const int xx = RS == 32 ? lx : e % RS, yy = RS == 32 ? ly + u * (kThreads / 32) : e / RS;
+      const int x = x0 + xx - R, y = y0 + yy - R;
+      const bool in = xx < tw && yy < kTileRows + 2 * R && (unsigned)x < (unsigned)W &&
+                      (unsigned)y < (unsigned)H;
+      uint32_t at = in ? (uint32_t)(y * W + x) : 0u;
+      asm volatile("" : "+v"(at));  // keeps the load out of a branch
+      const float v = img[at];
+      tv[u] = v;
+      keep = (keep & ~(1u << u)) | (in ? 1u << u : 0u);
+    }
+  };
+  float tv[kLoads];
+  int f = 0, x0 = 0, y0 = 0;  // of the tile in tv
+  auto place = [&](int tid) {
+    f = tid / tiles_per_frame;
+    const int rem = tid - f * tiles_per_frame, r = rem / tiles_x;
+    // a workgroup's tiles are shifted against each other, so that no workgroup
+    // gets nothing but tiles of a frame's edge (whose pixels often wait)
+    y0 = (r + f) % (tiles_per_frame / tiles_x) * kTileRows;
+    x0 = (rem - r * tiles_x + r + f) % tiles_x * kTile;
+  };
+  if ((int)blockIdx.x < n_tiles) {
+    place(blockIdx.x);
+    load_tile(f, x0, y0, tv);
+  }
+  for (int tid = blockIdx.x; tid < n_tiles; tid += gridDim.x) {
+    const int cf = f, cx0 = x0, cy0 = y0;  // this tile (f, x0, y0 go on to the next)
+    const float* img = frames + plane * (size_t)cf;
+    float mx = 0.0f;
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      tv[u] = keep >> u & 1u ? tv[u] : 0.0f;
+      mx = fmaxf(mx, fabsf(tv[u]));
+    }
+    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    __syncthreads();  // the bank is in place; the previous tile is no longer read
+    if (lane == 0) wred[w] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) mx = fmaxf(mx, wred[k]);
+    // the power of two that takes mx to [2^13, 2^14) (within the normal range)
+    const int ex = min(max((int)(__float_as_uint(mx) >> 23) - 127, -99), 127);
+    const float scale = __uint_as_float((uint32_t)(13 - ex + 127) << 23);
+    const float unscale = __uint_as_float((uint32_t)(ex - 13 - 14 + 127) << 23);
+    bool lost = false;
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const int e = (int)threadIdx.x + u * kThreads;
+      if (e < L.th * RS) {
+        const float v = tv[u] * scale;
+        const _Float16 h = (_Float16)v;
+        const _Float16 l = (_Float16)(v - (float)h);
+        lost |= tv[u] != 0.0f && h == (_Float16)0.0f;
+        _Float16* pl = (_Float16*)(lds + L.planes);
+        pl[e] = h;
+        pl[4 * L.plane + e] = l;
+        if (e > 0) {  // the odd copies: word k holds pixels 2k + 1, 2k + 2
+          pl[2 * L.plane + e - 1] = h;
+          pl[6 * L.plane + e - 1] = l;
+        }
+      }
+    }
+    lost = __ballot(lost) != 0;
+    if (lane == 0) wlost[w] = lost;
+    __syncthreads();
+    // the next tile's pixels, on their way during the products
+    if (tid + (int)gridDim.x < n_tiles) {
+      place(tid + gridDim.x);
+      load_tile(f, x0, y0, tv);
+    }
+    f32x16 acc[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[q][r] = 0.0f;
+    {
+      const uint32_t* ab = lds + L.bank + lane * 4;
+      // this lane's pixel of group 0, a tap row further in the upper half, in
+      // the copy of its column's parity
+      const int row = kRowsPerWave * w + ((lane >> 4) & 1);
+      const uint32_t* pb =
+          lds + L.planes + (c16 & 1) * L.plane + ((row + hf) * RS + c16 - (c16 & 1)) / 2;
+      const int n2 = (w2 + 1) / 2;  // steps of a column group
+      f16x8 bh[4], bl[4];           // group q's operands at step s: slot (q + s) % 4
+      auto load_b = [&](int slot, const uint32_t* sh) {
+        const uint32_t* sl = sh + 2 * L.plane;
+        bh[slot] = __builtin_bit_cast(f16x8, (u32x4){sh[0], sh[1], sh[2], sh[3]});
+        bl[slot] = __builtin_bit_cast(f16x8, (u32x4){sl[0], sl[1], sl[2], sl[3]});
+      };
+      for (int c = 0; c < taps8.cols; ++c) {
+        const uint32_t* src = pb + 4 * c;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) load_b(q, src + q * RS);
+        for (int s0 = 0; s0 < n2; s0 += 4) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (s0 + u >= n2) break;  // uniform
+            load_b((u + 3) & 3, src + (s0 + u + 3) * RS);
+            const f16x8 ah = *(const f16x8*)ab;
+            const f16x8 al = *(const f16x8*)(ab + 256);
+            ab += 512;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[(q + u) & 3], acc[q], 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[(q + u) & 3], acc[q], 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[(q + u) & 3], acc[q], 0, 0, 0);
+          }
+        }
+      }
+      // groups of 8 rows of one column
+      const _Float16* vb = (const _Float16*)(lds + L.planes) + row * RS + c16 + 8 * taps8.cols;
+      for (int v0 = 0; v0 < taps8.left * taps8.rows8; v0 += 2) {
+        const f16x8 ah = *(const f16x8*)ab;
+        const f16x8 al = *(const f16x8*)(ab + 256);
+        ab += 512;
+        // a padding group past the last one reads the last one
+        const int v = min(v0 + hf, taps8.left * taps8.rows8 - 1);
+        const _Float16* src = vb + v / taps8.rows8 + 8 * (v % taps8.rows8) * RS;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            bh[q][i] = src[(2 * q + i) * RS];
+            bl[q][i] = src[4 * L.plane + (2 * q + i) * RS];
+          }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[q], acc[q], 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[q], acc[q], 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[q], acc[q], 0, 0, 0);
+      }
+    }
+    // The range of the pixels that the wave's rows read, from the high
+    // halves (which are within 2^-11 of them).
+    f16x2 lo2 = {(_Float16)INFINITY, (_Float16)INFINITY}, hi2 = -lo2;
+    for (int e = lane; e < (kRowsPerWave + 2 * R) * (RS / 2); e += 64) {
+      const bool on = e % (RS / 2) < tw / 2;
+      const f16x2 v = __builtin_bit_cast(f16x2, lds[L.planes + kRowsPerWave * w * (RS / 2) + e]);
+      lo2 = on ? __builtin_elementwise_min(lo2, v) : lo2;
+      hi2 = on ? __builtin_elementwise_max(hi2, v) : hi2;
+    }
+    float lo = fminf((float)lo2[0], (float)lo2[1]), hi = fmaxf((float)hi2[0], (float)hi2[1]);
+    for (int off = 32; off > 0; off >>= 1) {
+      lo = fminf(lo, __shfl_xor(lo, off, 64));
+      hi = fmaxf(hi, __shfl_xor(hi, off, 64));
+    }
+    // in units of the scaled responses
+    float mg = kBankScale * (margin.mid * fabsf(0.5f * (hi + lo)) +
+                                   margin.half * (0.5f * (hi - lo) +
+                                                  0x1p-10f * fmaxf(fabsf(hi), fabsf(lo))));
+    // A window far below the tile's largest pixel has lost bits to the split's
+    // smallest step (2^-24, as 2^-22 of a pixel of 1/4): summed again.
+    const float top = fmaxf(fabsf(hi), fabsf(lo));
+    if (top < 1.0f) {  // uniform
+      int any = top > 0.0f;
+#pragma unroll
+      for (int k = 0; k < kWaves; ++k) any |= wlost[k];
+      if (any) mg = INFINITY;
+    }
+    // per pixel: argmax |F_j| (first of equals), then the spread of the
+    // responses around it
+    int jbs[4];
+    float wvs[4];
+    uint32_t near_q = 0;  // this lane's pixel of group q waits (bit q)
+    int n_near = 0;       // pixels of the wave that wait
+    const int prow = cy0 + kRowsPerWave * w + ((lane >> 4) & 1), pcol = cx0 + c16;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float fv[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) fv[k] = fabsf(acc[q][k]);  // in scaled units
+      bool near;
+      choose(fv, 4 * hf, 8, 32, mg, jbs[q], wvs[q], near);
+      wvs[q] *= unscale;
+      near = near && lane < 32 && pcol < W && prow + 2 * q < H;
+      n_near += __popcll(__ballot(near));
+      near_q |= near ? 1u << q : 0u;
+    }
+    float m = 0.0f;
+    // one value all over the window of the wave's pixels: then no part of it
+    // is outside the frame, which reads as 0 (and 0 everywhere is no choice)
+    bool flat = n_near > 1 && lo == hi && lo != 0.0f;
+    if (flat) {  // uniform; the high halves agree: the pixels themselves?
+      const float* win = img + (size_t)(cy0 + kRowsPerWave * w - R) * W + (cx0 - R);
+      const float v0 = win[0];
+      bool same = true;
+      for (int r0 = 0; r0 < kRowsPerWave + 2 * R; r0 += 8) {
+        float v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {  // rows and columns past the window read its last
+          const int r = min(r0 + 2 * u + hf, kRowsPerWave + 2 * R - 1);
+          v[u] = win[(size_t)r * W + min(lane & 31, tw - 1)];
+          if (RS > 32) same &= win[(size_t)r * W + min(32 + (lane & 31), tw - 1)] == v0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) same &= v[u] == v0;
+      }
+      flat = __ballot(same) == ~0ull;
+    }
+    if (flat) {
+      if (lane == 0)
+        fix[atomicAdd(&n_fix, 1)] =
+            make_int2(cf, ((cy0 + kRowsPerWave * w) * W + cx0) | kFixAll);
+    } else if (n_near > kDense && cx0 >= R && cx0 + kTile + R <= W &&
+               cy0 + kRowsPerWave * w >= R && cy0 + kRowsPerWave * (w + 1) + R <= H) {  // uniform
+      m = dense(cf, cx0, cy0 + kRowsPerWave * w);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int y = prow + 2 * q;
+        if (near_q >> q & 1u) {
+          fix[atomicAdd(&n_fix, 1)] = make_int2(cf, y * W + pcol);
+        } else if (lane < 32 && pcol < W && y < H) {
+          const size_t i = plane * (size_t)cf + (size_t)y * W + pcol;
+          store_map<TO>(theta_out, i, (float)jbs[q] * (kPi / NO));
+          raw[i] = wvs[q];
+          m = fmaxf(m, wvs[q]);
+        }
+      }
+    }
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    if (lane == 0) wmax[w] = m;
+    __syncthreads();  // wred and the waiting pixels
+    if (lane == 0) wred[w] = m;
+    int waiting = n_fix;
     __syncthreads();
     if (threadIdx.x == 0) {
-      float bm = wmax[0];
-      for (int k = 1; k < (int)(blockDim.x >> 6); ++k) bm = fmaxf(bm, wmax[k]);
-      atomicMax(&frame_max[f], __float_as_uint(bm));  // bm >= 0: bits order as values
+      float bm = wred[0];
+      for (int k = 1; k < kWaves; ++k) bm = fmaxf(bm, wred[k]);
+      atomicMax(&frame_max[cf], __float_as_uint(bm));  // bm >= 0: bits order as values
+    }
+    if (waiting >= kFixRound) {  // uniform: whole rounds, from the end of the list
+      for (; waiting >= kFixRound; waiting -= kFixRound)
+        fix_round(waiting - kFixRound, kFixRound);
+      if (threadIdx.x == 0) n_fix = waiting;  // read again after the next barriers
     }
   }
+  __syncthreads();
+  if (n_fix > 0) fix_round(0, n_fix);
 }
 
 uint64_t fnv1(uint64_t h, const void* p, size_t n) {
@@ -276,27 +696,73 @@ std::vector<float> make_bank(const fd_gabor_params* p) {
   return out;
 }
 
+// Twice the most by which the two sums of one response can differ, for a
+// window of pixels I = mid + v, |v| <= half, per unit of |mid| and of half.
+// A rounding is at most 2^-24 of the running sum, which is bounded by
+// |mid| |sum of the taps so far| + half (sum of their magnitudes so far).
+// Sum in order: one rounding per tap (the bound is taken at the start of a
+// 4-tap step, the step's own magnitudes on top).  Split sum: three matrix
+// operations per 16 taps, each rounding twice and cutting off as much again
+// where it aligns its products; the parts that the splits drop are within 3
+// 2^-22 of the magnitudes (and, for pixels or taps far below the largest,
+// 2^-36 of the largest, which is within 2^14 of the window's: else the pixel is
+// summed again without a look at the margin).  First order, one percent on top for the rest.
+GaborMargin choice_margin(const std::vector<float>& bank, int N, int R) {
+  const Taps tp(R);
+  const int w = tp.w, taps = w * w;
+  double most_p = 0.0, most_g = 0.0;
+  for (int j = 0; j < N; ++j) {
+    double P = 0.0, G = 0.0, sp = 0.0, sg = 0.0;
+    for (int k = 0; k < taps; ++k) {
+      if (k % 4 == 0) {
+        sp += 4.0 * std::fabs(P);
+        sg += 4.0 * G;
+      }
+      P += bank[(size_t)k * N + j];
+      G += std::fabs((double)bank[(size_t)k * N + j]);
+    }
+    const double all = G;
+    P = G = 0.0;
+    for (int st = 0; st < tp.steps; ++st) {
+      sp += 3 * 4.0 * std::fabs(P);
+      sg += 3 * 4.0 * G;
+      for (int q = 2 * st; q < 2 * st + 2; ++q)
+        for (int i = 0; i < 8; ++i) {
+          int dy, dx;
+          if (!tp.tap(q, i, &dy, &dx)) continue;
+          P += bank[(size_t)(dy * w + dx) * N + j];
+          G += std::fabs((double)bank[(size_t)(dy * w + dx) * N + j]);
+        }
+    }
+    const double rest = all * (4 + 3 * 4 + 3 * 4 + 4) + taps;
+    most_p = std::max(most_p, sp + rest);
+    most_g = std::max(most_g, sg + rest);
+  }
+  const double u = 2.0 * 1.01 / 16777216.0;
+  return GaborMargin{(float)(u * most_p), (float)(u * most_g)};
+}
+
 template <typename TO>
 hipError_t launch_gabor(const float* frames, int n, int W, int H, int R, int N, const float* bank,
-                        void* theta, float* raw, uint32_t* fmax, hipStream_t st) {
-  const int tiles_x = (W + kTile - 1) / kTile, tiles_y = (H + kMfmaRows - 1) / kMfmaRows;
-  const int64_t per_frame = (int64_t)tiles_x * tiles_y, n_tiles = per_frame * n;
-  const int taps = (2 * R + 1) * (2 * R + 1), kpad = (taps + 3) & ~3;
-  const int th = kMfmaRows + 2 * R;
-  const int nt = N > 16 ? 2 : 1;
-  const size_t lds = sizeof(float) * ((size_t)kpad * 16 * nt + (size_t)kTw * th + 64);
-  // N = 16 and 32 fill their orientation tiles: no per-lane validity tests
-  const auto kern = nt == 2    ? k_gabor_mfma<TO, 2, true>
-                    : N == 16 ? k_gabor_mfma<TO, 1, true>
-                              : k_gabor_mfma<TO, 1, false>;
+                        const float* margin, void* theta, float* raw, uint32_t* fmax,
+                        hipStream_t st) {
+  const int tiles_x = (W + kTile - 1) / kTile, tiles_y = (H + kTileRows - 1) / kTileRows;
+  const int64_t per_frame = (int64_t)tiles_x * tiles_y;
+  const int n_tiles = (int)(per_frame * n);  // n <= FD_MAX_VIEWS, n W H <= 2^34: below 2^30
+  const GaborLds L(R);
+  const size_t lds = 4 * (size_t)L.total;
+  const auto kern = R <= 8 ? (N == 32 ? k_gabor_mfma<TO, 32, true> : k_gabor_mfma<TO, 32, false>)
+                           : (N == 32 ? k_gabor_mfma<TO, 40, true> : k_gabor_mfma<TO, 40, false>);
   hipError_t e = hipFuncSetAttribute((const void*)kern,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  // persistent: each workgroup loads the bank once; several resident per CU
-  const int per_cu = (int)std::max<size_t>(1, (160 * 1024) / (lds + 1024));
-  const int64_t grid = std::min<int64_t>(n_tiles, (int64_t)256 * std::min(per_cu, 4));
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, st, frames, W, H, R, N, bank,
-                     n_tiles, tiles_x, per_frame, theta, raw, fmax);
+  // persistent: each workgroup splits the bank once; two resident per CU
+  // where the LDS allows it
+  const int per_cu = 2 * (lds + 8 * kFixCap + 512) <= 160 * 1024 ? 2 : 1;
+  const int grid = std::min(n_tiles, 256 * per_cu);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), lds, st, frames, W, H, R, N, bank,
+                     GaborMargin{margin[0], margin[1]}, Taps(R), L, n_tiles, tiles_x,
+                     (int)per_frame, theta, raw, fmax);
   return hipGetLastError();
 }
 
@@ -368,6 +834,9 @@ extern "C" int fd_orientation_maps(const float* frames, int32_t n_frames, int32_
     e = hipMemcpy(c->gabor_bank, bank.data(), bank.size() * sizeof(float),
                   hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_error(e, "filter bank upload");
+    const GaborMargin mg = choice_margin(bank, p->n_orient, p->radius);
+    c->gabor_margin[0] = mg.mid;
+    c->gabor_margin[1] = mg.half;
     c->gabor_sig = sig;
   }
   const size_t plane = (size_t)width * height, total = plane * (size_t)n_frames;
@@ -384,9 +853,11 @@ extern "C" int fd_orientation_maps(const float* frames, int32_t n_frames, int32_
   StageTimer tg(c, FD_STAGE_GABOR, st);
   e = p->out_dtype == FD_F16
           ? launch_gabor<__half>(frames, n_frames, width, height, p->radius, p->n_orient,
-                                 c->gabor_bank, theta_out, c->gabor_raw, c->gabor_max, st)
+                                 c->gabor_bank, c->gabor_margin, theta_out, c->gabor_raw, c->gabor_max,
+                                 st)
           : launch_gabor<float>(frames, n_frames, width, height, p->radius, p->n_orient,
-                                c->gabor_bank, theta_out, c->gabor_raw, c->gabor_max, st);
+                                c->gabor_bank, c->gabor_margin, theta_out, c->gabor_raw,
+                                c->gabor_max, st);
   if (e != hipSuccess) return hip_error(e, "orientation kernel");
   tg.stop();
   StageTimer tn(c, FD_STAGE_GABOR_NORM, st);

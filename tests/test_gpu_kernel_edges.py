@@ -115,3 +115,42 @@ def test_training_batches(batch):
     assert torch.equal(net.forward(xd), other.forward(xd))
     a, b = net.loss_grad(xd, _t(t)), other.loss_grad(xd, _t(t))
     assert torch.equal(a[1], b[1]) and torch.equal(a[0], b[0])
+
+
+@pytest.mark.parametrize("radius", range(1, 13))
+def test_orientation_maps_radii_and_ranges(radius):
+    """Every tap layout at sizes around the 16 x 64 tile, on frames of any
+    scale: noise, a constant (responses are rounding), one pixel 2^40 times
+    the others (below what the split halves hold), and non-finite pixels,
+    which stay in their window.  Responses and confidences within the bounds
+    of the orientation-map tests; the orientation is that of the binary32 sum
+    over the taps in order, also where rounding decides."""
+    import test_gpu_gabor as G
+    rng = np.random.default_rng(radius)
+    kw = dict(n_orient=(8, 16, 32)[radius % 3], radius=radius)
+    h, w = 64 + radius % 3 - 1, 32 + (radius // 3) % 3 - 1
+    base = rng.uniform(0.0, 1.0, (h, w))
+    frames = np.stack([255.0 * base, 1e-3 * base, np.full((h, w), 0.7), base, base - 0.5]).astype(np.float32)
+    frames[3] *= 2.0**-20
+    frames[3, 40, 20] = 2.0**20
+    frames[4, :, :8] *= 2.0**-30
+    th, cf = G._gpu(frames, **kw)
+    # the parameters as the entry point holds them
+    bank = oracle.gabor_bank(**{k: v if k in kw else float(np.float32(v)) for k, v in G._bank_kw(kw).items()})
+    for v in range(5):
+        G._check_frame(frames[v], th[v], cf[v], bank, max_tie_frac=1.0)
+        pad = np.pad(frames[v], radius).astype(np.longdouble)
+        acc = np.zeros((kw["n_orient"], h, w), np.float32)
+        for dy in range(2 * radius + 1):
+            for dx in range(2 * radius + 1):
+                tap = bank[:, dy, dx].astype(np.float32).astype(np.longdouble)
+                acc = (tap[:, None, None] * pad[dy:dy + h, dx:dx + w] + acc).astype(np.float32)
+        assert np.array_equal(np.rint(th[v] * kw["n_orient"] / np.pi), np.abs(acc).argmax(0))
+    for bad in (np.nan, np.inf):
+        f = frames[4].copy()
+        f[30, 9] = bad
+        tb, cb = G._gpu(f[None], **kw)
+        inside = np.zeros((h, w), bool)
+        inside[max(0, 30 - radius):31 + radius, max(0, 9 - radius):10 + radius] = True
+        assert np.array_equal(tb[0][~inside], th[4][~inside])
+        assert np.isnan(cb[0][inside]).all() and np.isfinite(cb[0][~inside]).all()

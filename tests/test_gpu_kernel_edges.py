@@ -154,3 +154,25 @@ def test_orientation_maps_radii_and_ranges(radius):
         inside[max(0, 30 - radius):31 + radius, max(0, 9 - radius):10 + radius] = True
         assert np.array_equal(tb[0][~inside], th[4][~inside])
         assert np.isnan(cb[0][inside]).all() and np.isfinite(cb[0][~inside]).all()
+
+
+@pytest.mark.parametrize("dims,n", [((1, 1, 1), 1), ((1, 1, 1), 24), ((1, 1, 1), 25), ((1, 1, 1), 33), ((2, 1, 1), 48),
+                                    ((2, 1, 1), 1003), ((3, 3, 3), 27 * 24), ((3, 3, 3), 27 * 40), ((64, 64, 1), 9000),
+                                    ((17, 241, 1), 5000), ((16, 16, 16), 4096 * 30)])
+def test_volume_slots_and_lanes(dims, n):
+    """Around the 24 points a voxel at which a voxel gets eight lanes, counts
+    that leave a remainder, one block of voxels more or less than whole.  The
+    bounds of the volume tests."""
+    import test_gpu_volume as V
+    rng = np.random.default_rng(n)
+    h = np.float32(0.01)
+    pts = (rng.uniform(0.0, 1.0, (n, 3)) * np.array(dims) * 0.0099999).astype(np.float32)
+    d = rng.normal(size=(n, 3)) + np.array([2.0, 0.5, -1.0])
+    d = (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32)
+    w = rng.uniform(-0.1, 1.1, n).astype(np.float32)
+    grid = (np.zeros(3, np.float32), h, np.array(dims, np.int32))
+    o, *out, _, _ = V._compare(pts, d, *grid, np.clip(w, 0.0, 1.0))
+    assert o["inside"] == n
+    # weights outside [0, 1] act as the nearest (the oracle takes them as they are)
+    for a, b in zip(out, V._gpu(pts, d, *grid, w)):
+        assert np.array_equal(a, b)

@@ -194,14 +194,30 @@ __global__ __launch_bounds__(kBlock) void k_b_topk(BatchDev b, SearchDev q) {
   topk_point<T, KS>(sc, q, j);
 }
 
+// The rows of a workgroup's points, all of one scene: block_point's j (below 0
+// where the scene has ended), whose first lane has the wave's first point.
+static_assert(kBlock == kFeatureBlock, "one set of lists per workgroup");
+template <typename T>
+__device__ __forceinline__ void block_rows(const BatchDev& b, int s, const SceneDev& sc,
+                                           int64_t blk, FrontalLists& lists,
+                                           const int (&id)[kSlots],
+                                           uint16_t* __restrict__ feats) {
+  const int64_t j0 = (blk - b.blk_off[s]) * kBlock + (threadIdx.x & ~(uint32_t)(kWave - 1));
+  wave_feature_rows<T>(sc, lists, id, j0, sc.n, b.pt_off[s] + j0, feats);
+}
+
 template <typename T, int KS>
 __global__ __launch_bounds__(kBlock) void k_b_topk_features(BatchDev b, SearchDev q,
                                                             uint16_t* __restrict__ feats) {
+  __shared__ FrontalLists lists;
   int s;
-  const int64_t j = block_point(b, &s, xcd_tile(gridDim.x));
-  if (j < 0) return;
+  const int64_t blk = xcd_tile(gridDim.x), j = block_point(b, &s, blk);
   const SceneDev sc = load_scene(b.tab, s);
-  topk_features_point<T, KS>(sc, q, j, b.pt_off[s], feats);
+  int id[kSlots];
+#pragma unroll
+  for (int k = 0; k < kSlots; ++k) id[k] = -1;
+  if (j >= 0) topk_features_point<T, KS>(sc, q, j, id);
+  block_rows<T>(b, s, sc, blk, lists, id, feats);
 }
 
 // The same for batches whose scenes have at most kMaskViews views, in two
@@ -222,13 +238,16 @@ void k_b_vis_m(BatchDev b, SearchDev q, uint16_t* __restrict__ feats) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_b_frontal_row_m(BatchDev b,
-                                                            uint16_t* __restrict__ feats) {
+__global__ __launch_bounds__(kBlock) void k_b_frontal_row_m(BatchDev b, uint16_t* feats) {
+  __shared__ FrontalLists lists;
   int s;
-  const int64_t j = block_point(b, &s, xcd_tile(gridDim.x));
-  if (j < 0) return;
+  const int64_t blk = xcd_tile(gridDim.x), j = block_point(b, &s, blk);
   const SceneDev sc = load_scene(b.tab, s);
-  frontal_row_masked<T, kMaskViews / 32>(sc, sc.cam64, j, b.pt_off[s] + j, feats);
+  int id[kSlots];
+#pragma unroll
+  for (int k = 0; k < kSlots; ++k) id[k] = -1;
+  if (j >= 0) frontal_masked<kMaskViews / 32>(sc, sc.cam64, j, b.pt_off[s] + j, feats, id);
+  block_rows<T>(b, s, sc, blk, lists, id, feats);
 }
 
 // Persistent search.  Without a list, the items are the scenes' points in

@@ -15,9 +15,9 @@
 namespace fd {
 
 constexpr int kSlots = FD_FEATURE_SLOTS;
-// Scenes with at most this many views take the three-pass form
-// (vis_topk_masked, then frontal_row_masked), their visibility bits passed
-// between the two through the feature row.
+// Scenes with at most this many views select their views in two passes
+// (vis_topk_masked, then frontal_masked), the visibility bits passed between
+// the two through the feature row.
 constexpr int kMaskViews = 128;
 constexpr float kInvPi = 0.318309886183790671538f;
 
@@ -71,21 +71,78 @@ __device__ __forceinline__ void frontal_insert(double (&sc)[kSlots], int (&id)[k
   }
 }
 
-// Per slot of the frontal list: the observed orientation as
-// (q_x, q_y) = |m| (cos 2psi, sin 2psi) (m the bilinear confidence-weighted
-// doubled-angle vector, psi the angle of the plane it back-projects to, in a
-// frame tied to the line of sight), the bilinear confidence C, the unit
-// point->camera direction and 1; empty slots are 0.  Written as 112
-// bfloat16 to feats row `row`.  These are values, not decisions (the slot
-// views are chosen in binary64 beforehand), and they are rounded to
-// bfloat16 (relative step 2^-8), so apart from the sample position
-// (binary64) they are formed in binary32 with the hardware reciprocal,
-// square root and sine / cosine (errors ~1e-6 relative).
-// One slot of the row, without branches (the slot's view is v; a slot
-// that is empty passes valid = false, reads view 0 and yields zeros), so
-// that the loads of neighbouring slots can be in flight together.  tab is
-// the scene's camera table (kCam64 slots per view; global memory or a copy
-// in LDS).  PAIRS: the scene allows texel-pair loads (binary16).
+// The same list with the view's index in the low kBits bits of its key, so
+// that an entry is one binary64 value and a step of the insertion a maximum
+// and a minimum (8 cycles a wave, where comparing and moving a key and an
+// index apart takes 28).  Keys that differ above those bits are ordered as
+// the whole keys are; `top` keeps the largest entry that left the list, and
+// settled() tells whether every neighbouring pair (the last one with `top`)
+// differs there.  Where it does not the caller makes the list again with
+// frontal_insert (cameras at the same place, or keys within 2^-45 or 2^-36).
+// kBits: 7 for scenes of at most 128 views, else 16.
+template <int kBits>
+struct FrontalList {
+  static constexpr uint32_t kMask = (1u << kBits) - 1u;
+  static constexpr double kEmpty = -1e300;  // below every key that is taken
+  double e[kSlots], top;
+  bool odd;  // a key that the packing does not hold
+
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k) e[k] = kEmpty;
+    top = kEmpty;
+    odd = false;
+  }
+  __device__ __forceinline__ void insert(double key, int v) {
+    odd |= !(fabs(key) < 1e299);
+    const uint64_t b = __builtin_bit_cast(uint64_t, key + 0.0);  // -0 as 0
+    double x = __builtin_bit_cast(double, (b & ~(uint64_t)kMask) | (uint32_t)v);
+    if (x > e[kSlots - 1]) {
+#pragma unroll
+      for (int k = 0; k < kSlots; ++k) {
+        double hi, lo;  // (no operand is a NaN: nothing to quiet)
+        asm("v_max_f64 %0, %1, %2" : "=v"(hi) : "v"(e[k]), "v"(x));
+        asm("v_min_f64 %0, %1, %2" : "=v"(lo) : "v"(e[k]), "v"(x));
+        e[k] = hi;
+        x = lo;
+      }
+    }
+    top = __builtin_fmax(top, x);
+  }
+  __device__ __forceinline__ bool settled() const {
+    bool ok = !odd;
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k) {
+      const double n = k + 1 < kSlots ? e[k + 1 < kSlots ? k + 1 : k] : top;
+      ok = ok && (e[k] == kEmpty || (__builtin_bit_cast(uint64_t, e[k]) >> kBits) !=
+                                        (__builtin_bit_cast(uint64_t, n) >> kBits));
+    }
+    return ok;
+  }
+  __device__ __forceinline__ void views(int (&id)[kSlots]) const {
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k)
+      id[k] = e[k] == kEmpty ? -1 : (int)((uint32_t)__builtin_bit_cast(uint64_t, e[k]) & kMask);
+  }
+};
+
+// The list with whole keys: each_view(take) calls take(key, view) for the
+// views in increasing order.
+template <typename F>
+__device__ __forceinline__ void list_whole_keys(const F& each_view, int (&id)[kSlots]) {
+  double sc[kSlots];
+#pragma unroll
+  for (int k = 0; k < kSlots; ++k) {
+    sc[k] = -INFINITY;
+    id[k] = -1;
+  }
+  each_view([&](double key, int v) { frontal_insert(sc, id, key, v); });
+}
+
+// A slot of a feature row, without branches (a slot that is empty passes
+// valid = false, reads view 0 and yields zeros).  tab is the scene's camera
+// table (kCam64 slots per view).  PAIRS: the scene allows texel-pair loads
+// (binary16).
 template <typename T, bool PAIRS>
 __device__ __forceinline__ void feature_slot(const SceneDev& s, const double* __restrict__ tab,
                                              double px, double py, double pz, int v, bool valid,
@@ -235,97 +292,118 @@ __device__ __forceinline__ void feature_slot(const SceneDev& s, const double* __
   f[6] = valid ? 1.0f : 0.0f;
 }
 
+// The frontal lists of a wave's points on their way to the lanes that form the
+// slots: in LDS, 16 bits a slot (0xffff: empty), nine words a point (every
+// lane's list starts at another bank).
+constexpr int kFeatureBlock = 256;  // threads of the kernels that write rows
+constexpr int kListWords = kSlots / 2 + 1;
+struct FrontalLists {
+  uint32_t w[kFeatureBlock / kWave][kWave * kListWords];
+};
+
 // Per slot of the frontal list: the observed orientation as
 // (q_x, q_y) = |m| (cos 2psi, sin 2psi) (m the bilinear confidence-weighted
 // doubled-angle vector, psi the angle of the plane it back-projects to, in a
 // frame tied to the line of sight), the bilinear confidence C, the unit
 // point->camera direction and 1; empty slots are 0.  Written as 112
-// bfloat16 to feats row `row`.  These are values, not decisions (the slot
-// views are chosen in binary64 beforehand), and they are rounded to
-// bfloat16 (relative step 2^-8), so apart from the sample position
-// (binary64) they are formed in binary32 with the hardware reciprocal,
-// square root and sine / cosine (errors ~1e-6 relative).
-template <typename T, bool PAIRS>
-__device__ __forceinline__ void write_feature_row_t(const SceneDev& s,
-                                                    const double* __restrict__ tab, double px,
-                                                    double py, double pz,
-                                                    const int (&id)[kSlots], int64_t row,
-                                                    uint16_t* __restrict__ feats) {
-  // slots in pairs, whose 14 values convert to 7 packed bfloat16 pairs and
-  // are stored at once (rows are 224 bytes, so every pair starts on a
-  // 4-byte boundary); one pair is processed per pass, the views of the
-  // next pair moved to the front of the list
-  static_assert(kSlots % 2 == 0, "slots are converted in pairs");
-  uint32_t* dst = (uint32_t*)(feats + (size_t)row * (7 * kSlots));
-  int idr[kSlots];
+// bfloat16 to the point's row.  These are values,
+// not decisions (the slot views are chosen in binary64 beforehand), and they
+// are rounded to bfloat16 (relative step 2^-8), so apart from the sample
+// position (binary64) they are formed in binary32 with the hardware
+// reciprocal, square root and sine / cosine (errors ~1e-6 relative).
+//
+// Called by whole waves: lane l < PW has the list id of point j0 + l (if that
+// is below n), the points' rows follow one another from row0.  One lane per
+// slot, the 16 of a point side by side, four points at a time.  A slot's
+// texels and camera record are gathers; a lane that took a point's slots in
+// turn held another view than most of its 64 neighbours, where four
+// neighbouring points share most of theirs.  Two lanes' 14 values make seven
+// words, four of them stored by the even one (rows are 224 bytes, so every
+// pair starts on a 4-byte boundary).
+// 60,000 points of 64 views, binary32 maps: the call 171 -> 128 us, with the
+// list and the grouped depth texels; 2M points of up to 128 views: list and
+// rows 1344 -> 1020 us (a kernel of the list alone 330, of the rows alone
+// 760: the loads of the rows).  Going through a wave's views one by one, the
+// lanes that have it together, measured 620 where this measures 160 (a
+// serial chain of scalar and vector loads per view).
+template <typename T, int PW = kWave>
+__device__ __forceinline__ void wave_feature_rows(const SceneDev& s, FrontalLists& lists,
+                                                  const int (&id)[kSlots], int64_t j0, int64_t n,
+                                                  int64_t row0, uint16_t* __restrict__ feats) {
+  const int lane = (int)(threadIdx.x & (kWave - 1));
+  uint32_t* const w = lists.w[threadIdx.x / kWave];
 #pragma unroll
-  for (int k = 0; k < kSlots; ++k) idr[k] = id[k];
+  for (int k = 0; k < kSlots; k += 2)
+    w[lane * kListWords + k / 2] = ((uint32_t)id[k] & 0xffffu) | ((uint32_t)id[k + 1] << 16);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const int slot = lane % kSlots;
+  const bool odd = slot & 1;
 #pragma unroll 1
-  for (int kp = 0; kp < kSlots; kp += 2) {
-    float f0[7], f1[7];
-    feature_slot<T, PAIRS>(s, tab, px, py, pz, max(idr[0], 0), idr[0] >= 0, f0);
-    feature_slot<T, PAIRS>(s, tab, px, py, pz, max(idr[1], 0), idr[1] >= 0, f1);
-    float f2[14];
-#pragma unroll
-    for (int e = 0; e < 7; ++e) {
-      f2[e] = f0[e];
-      f2[7 + e] = f1[e];
-    }
-#pragma unroll
-    for (int e = 0; e < 7; ++e) dst[7 * (kp / 2) + e] = feat_bf16x2(f2[2 * e], f2[2 * e + 1]);
-#pragma unroll
-    for (int k = 0; k + 2 < kSlots; ++k) idr[k] = idr[k + 2];
+  for (int p = lane / kSlots; p < PW; p += kWave / kSlots) {
+    if (j0 + p >= n) break;  // the same for a point's lanes
+    const uint32_t i = s.perm ? s.perm[j0 + p] : (uint32_t)(j0 + p);
+    const double px = s.pts[3 * (size_t)i], py = s.pts[3 * (size_t)i + 1],
+                 pz = s.pts[3 * (size_t)i + 2];
+    const uint32_t v = (w[p * kListWords + slot / 2] >> (odd ? 16 : 0)) & 0xffffu;
+    const bool valid = v != 0xffffu;
+    float f[7];
+    if (sizeof(T) == 2 && s.pairs)
+      feature_slot<T, true>(s, s.cam64, px, py, pz, valid ? (int)v : 0, valid, f);
+    else
+      feature_slot<T, false>(s, s.cam64, px, py, pz, valid ? (int)v : 0, valid, f);
+    const float f7 = __shfl_xor(f[0], 1, kWave);  // the odd slot's first, in the even lane
+    uint32_t* const dst = (uint32_t*)(feats + (size_t)(row0 + p) * (7 * kSlots)) +
+                          7 * (slot >> 1) + (odd ? 4 : 0);
+    dst[0] = feat_bf16x2(odd ? f[1] : f[0], odd ? f[2] : f[1]);
+    dst[1] = feat_bf16x2(odd ? f[3] : f[2], odd ? f[4] : f[3]);
+    dst[2] = feat_bf16x2(odd ? f[5] : f[4], odd ? f[6] : f[5]);
+    if (!odd) dst[3] = feat_bf16x2(f[6], f7);
   }
 }
 
-template <typename T>
-__device__ __forceinline__ void write_feature_row(const SceneDev& s, const double* __restrict__ tab,
-                                                  double px, double py, double pz,
-                                                  const int (&id)[kSlots], int64_t row,
-                                                  uint16_t* __restrict__ feats) {
-  if (sizeof(T) == 2 && s.pairs)
-    write_feature_row_t<T, true>(s, tab, px, py, pz, id, row, feats);
-  else
-    write_feature_row_t<T, false>(s, tab, px, py, pz, id, row, feats);
-}
-
-// One lane per point: the kSlots most frontal eligible views, then their
-// feature row (processing-order index j when by_j, else the point index,
-// plus row_base).
+// One lane per point: the kSlots most frontal eligible views.
 template <typename T>
 __device__ __forceinline__ void features_point(const SceneDev& s, double z_near, int64_t j,
-                                               int by_j, int64_t row_base,
-                                               uint16_t* __restrict__ feats) {
+                                               int (&id)[kSlots]) {
   const uint32_t i = s.perm ? s.perm[j] : (uint32_t)j;
   const double px = s.pts[3 * (size_t)i], py = s.pts[3 * (size_t)i + 1],
                pz = s.pts[3 * (size_t)i + 2];
-  double sc[kSlots];
-  int id[kSlots];
-#pragma unroll
-  for (int k = 0; k < kSlots; ++k) {
-    sc[k] = -INFINITY;
-    id[k] = -1;
-  }
   const size_t plane = (size_t)s.W * s.H;
   const T* depth = (const T*)s.depth;
   const double bx = px - (double)s.hc[0], by = py - (double)s.hc[1], bz = pz - (double)s.hc[2];
-  for (int v = 0; v < s.V; ++v) {
-    ProjT pr;
-    const bool ok = project_tab(s.cam64 + kCam64 * v, px, py, pz, s.W, s.H, z_near, pr);
-    if (!visible_at<T>(depth ? depth + plane * v : nullptr, s.W, ok, pr, (double)s.vis_tau))
-      continue;
-    frontal_insert(sc, id, frontal_key(s.cam64 + kCam64 * v, px, py, pz, bx, by, bz), v);
-  }
-  write_feature_row<T>(s, s.cam64, px, py, pz, id, row_base + (by_j ? j : (int64_t)i), feats);
+  // views in groups, the depth texels of a group issued together
+  constexpr int kGroup = 4;
+  auto each_view = [&](auto&& take) {
+    for (int v0 = 0; v0 < s.V; v0 += kGroup) {
+      bool seen[kGroup];
+#pragma unroll
+      for (int u = 0; u < kGroup; ++u) {
+        const int v = min(v0 + u, s.V - 1);
+        ProjT pr;
+        const bool ok = project_tab(s.cam64 + kCam64 * v, px, py, pz, s.W, s.H, z_near, pr);
+        seen[u] = visible_at<T>(depth ? depth + plane * v : nullptr, s.W, ok, pr,
+                                (double)s.vis_tau) && v0 + u < s.V;
+      }
+#pragma unroll
+      for (int u = 0; u < kGroup; ++u)
+        if (seen[u])
+          take(frontal_key(s.cam64 + kCam64 * (v0 + u), px, py, pz, bx, by, bz), v0 + u);
+    }
+  };
+  FrontalList<16> list;
+  list.clear();
+  each_view([&](double key, int v) { list.insert(key, v); });
+  list.views(id);
+  if (__ballot(!list.settled())) list_whole_keys(each_view, id);
 }
 
-// Eq. (4) view selection and the proposal features in one pass over the
-// views (one projection per view): writes views / kcount like topk_point
-// and feature row row_base + j.
+// Eq. (4) view selection and the frontal list in one pass over the views (one
+// projection per view): writes views / kcount like topk_point and leaves the
+// list in id.
 template <typename T, int KS>
 __device__ __forceinline__ void topk_features_point(const SceneDev& s, const SearchDev& q,
-                                                    int64_t j, int64_t row_base,
-                                                    uint16_t* __restrict__ feats) {
+                                                    int64_t j, int (&id)[kSlots]) {
   const uint32_t i = s.perm[j];
   const double px = s.pts[3 * (size_t)i], py = s.pts[3 * (size_t)i + 1],
                pz = s.pts[3 * (size_t)i + 2];
@@ -337,7 +415,6 @@ __device__ __forceinline__ void topk_features_point(const SceneDev& s, const Sea
     vk[k] = 0;
   }
   double sc[kSlots];
-  int id[kSlots];
 #pragma unroll
   for (int k = 0; k < kSlots; ++k) {
     sc[k] = -INFINITY;
@@ -387,7 +464,6 @@ __device__ __forceinline__ void topk_features_point(const SceneDev& s, const Sea
     s.views[FD_TOPK_SLOTS * j + k] = (uint16_t)vk[k];
   }
   s.kcount[j] = (uint8_t)keff;
-  write_feature_row<T>(s, s.cam64, px, py, pz, id, row_base + j, feats);
 }
 
 // Bitwise OR of m over the wave, in a scalar register.
@@ -397,15 +473,15 @@ __device__ __forceinline__ uint32_t wave_or32(uint32_t m) {
   return __builtin_amdgcn_readfirstlane(m);
 }
 
-// For scenes of at most 32 MW views the view selection and the features
+// For scenes of at most 32 MW views the view selection and the frontal list
 // run as two kernels, each holding less state.  The first
 // (vis_topk_masked) makes the Eq. (4) selection (four views at a time, as
 // topk_point) and keeps each view's visibility as a bit in MW registers,
 // which it leaves in the first 4 MW bytes of the point's feature row; the
-// second (frontal_row_masked) takes the bits back, ranks the visible views
+// second (frontal_masked) takes the bits back, ranks the visible views
 // by frontality (projections and depth texels are not read again; the
 // views are taken in increasing order, so the list is the same as the
-// one-pass form's) and writes the row over them.  The gather loop of the
+// one-pass form's) and returns the list.  The gather loop of the
 // first then runs at the occupancy its own registers allow.  ctab is the
 // scene's camera table, read at wave-uniform addresses only (the caller may
 // pass the global table, whose records then come through the scalar cache
@@ -477,10 +553,11 @@ __device__ __forceinline__ void vis_topk_masked(const SceneDev& s, const SearchD
   for (int w = 0; w < MW; ++w) bits_out[w] = mask[w];
 }
 
-template <typename T, int MW>
-__device__ __forceinline__ void frontal_row_masked(const SceneDev& s,
-                                                   const double* __restrict__ ctab, int64_t j,
-                                                   int64_t row, uint16_t* __restrict__ feats) {
+template <int MW>
+__device__ __forceinline__ void frontal_masked(const SceneDev& s,
+                                               const double* __restrict__ ctab, int64_t j,
+                                               int64_t row, const uint16_t* feats,
+                                               int (&id)[kSlots]) {
   const uint32_t i = s.perm[j];
   const double px = s.pts[3 * (size_t)i], py = s.pts[3 * (size_t)i + 1],
                pz = s.pts[3 * (size_t)i + 2];
@@ -488,29 +565,26 @@ __device__ __forceinline__ void frontal_row_masked(const SceneDev& s,
   const uint32_t* bits_in = (const uint32_t*)(feats + (size_t)row * (7 * kSlots));
 #pragma unroll
   for (int w = 0; w < MW; ++w) mask[w] = bits_in[w];
-  double sc[kSlots];
-  int id[kSlots];
-#pragma unroll
-  for (int k = 0; k < kSlots; ++k) {
-    sc[k] = -INFINITY;
-    id[k] = -1;
-  }
   const double bx = px - (double)s.hc[0], by = py - (double)s.hc[1], bz = pz - (double)s.hc[2];
+  auto each_view = [&](auto&& take) {
 #pragma unroll
-  for (int w = 0; w < MW; ++w) {
-    uint32_t um = wave_or32(mask[w]);  // views some lane of the wave sees
-    while (um) {
-      const int b = __builtin_ctz(um);
-      um &= um - 1u;
-      const int v = 32 * w + b;
-      if ((mask[w] >> b) & 1u)
-        frontal_insert(sc, id, frontal_key(ctab + kCam64 * v, px, py, pz, bx, by, bz), v);
+    for (int w = 0; w < MW; ++w) {
+      uint32_t um = wave_or32(mask[w]);  // views some lane of the wave sees
+      while (um) {
+        const int b = __builtin_ctz(um);
+        um &= um - 1u;
+        const int v = 32 * w + b;
+        if ((mask[w] >> b) & 1u)
+          take(frontal_key(ctab + kCam64 * v, px, py, pz, bx, by, bz), v);
+      }
     }
-  }
-  // the row reads its slots' camera records from the global table: their
-  // views differ from lane to lane (per-lane reads of the LDS copy have
-  // given results that varied from run to run)
-  write_feature_row<T>(s, s.cam64, px, py, pz, id, row, feats);
+  };
+  static_assert(32 * MW <= 128, "seven bits of view index");
+  FrontalList<7> list;
+  list.clear();
+  each_view([&](double key, int v) { list.insert(key, v); });
+  list.views(id);
+  if (__ballot(!list.settled())) list_whole_keys(each_view, id);
 }
 
 }  // namespace fd

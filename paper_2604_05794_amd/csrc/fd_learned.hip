@@ -20,20 +20,36 @@ int mlp_forward_dev(const fd_mlp* m, const uint16_t* feats, int64_t n, float* ou
 
 namespace {
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_features(SceneDev s, float z_near, int by_j,
-                                                  uint16_t* __restrict__ feats) {
-  const int64_t j = xcd_tile(gridDim.x) * blockDim.x + threadIdx.x;
-  if (j >= s.n) return;
-  features_point<T>(s, z_near, j, by_j, 0, feats);
+// Whole waves stay for the rows: a lane without a point has an empty list.
+__device__ __forceinline__ void empty_list(int (&id)[kSlots]) {
+#pragma unroll
+  for (int k = 0; k < kSlots; ++k) id[k] = -1;
+}
+
+// PW points a wave.
+template <typename T, int PW>
+__global__ __launch_bounds__(kFeatureBlock) void k_features(SceneDev s, float z_near,
+                                                            uint16_t* __restrict__ feats) {
+  __shared__ FrontalLists lists;
+  const int lane = (int)(threadIdx.x & (kWave - 1));
+  const int64_t j0 =
+      PW * (xcd_tile(gridDim.x) * (kFeatureBlock / kWave) + (int64_t)(threadIdx.x / kWave));
+  int id[kSlots];
+  empty_list(id);
+  if (lane < PW && j0 + lane < s.n) features_point<T>(s, z_near, j0 + lane, id);
+  wave_feature_rows<T, PW>(s, lists, id, j0, s.n, j0, feats);
 }
 
 template <typename T, int KS>
-__global__ __launch_bounds__(256) void k_topk_features(SceneDev s, SearchDev q,
-                                                       uint16_t* __restrict__ feats) {
+__global__ __launch_bounds__(kFeatureBlock) void k_topk_features(SceneDev s, SearchDev q,
+                                                                 uint16_t* __restrict__ feats) {
+  __shared__ FrontalLists lists;
   const int64_t j = xcd_tile(gridDim.x) * blockDim.x + threadIdx.x;
-  if (j >= s.n) return;
-  topk_features_point<T, KS>(s, q, j, 0, feats);
+  const int64_t j0 = j - (threadIdx.x & (kWave - 1));
+  int id[kSlots];
+  empty_list(id);
+  if (j < s.n) topk_features_point<T, KS>(s, q, j, id);
+  wave_feature_rows<T>(s, lists, id, j0, s.n, j0, feats);
 }
 
 // The same for scenes of at most kMaskViews views, in two kernels (view
@@ -48,22 +64,42 @@ void k_vis_m(SceneDev s, SearchDev q, uint16_t* __restrict__ feats) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_frontal_row_m(SceneDev s, uint16_t* __restrict__ feats) {
+__global__ __launch_bounds__(kFeatureBlock) void k_frontal_row_m(SceneDev s, uint16_t* feats) {
+  __shared__ FrontalLists lists;
   const int64_t j = xcd_tile(gridDim.x) * blockDim.x + threadIdx.x;
-  if (j >= s.n) return;
-  frontal_row_masked<T, kMaskViews / 32>(s, s.cam64, j, j, feats);
+  const int64_t j0 = j - (threadIdx.x & (kWave - 1));
+  int id[kSlots];
+  empty_list(id);
+  if (j < s.n) frontal_masked<kMaskViews / 32>(s, s.cam64, j, j, feats, id);
+  wave_feature_rows<T>(s, lists, id, j0, s.n, j0, feats);
 }
 
 }  // namespace
 
-static hipError_t launch_features_rows(const SceneDev& s, int dtype, float z_near, int by_j,
+// Points a wave: 64, but 16 up to as many points as give every SIMD of the
+// card (1024) one wave of 64; the waiting of one wave's gathers is then all
+// there is.  16 and 64 a wave, us: 83 and 129 at 5000 points, 98 and 133 at
+// 20,000, 138 and 144 at 60,000, 228 and 208 at 120,000 (binary32 maps).
+constexpr int64_t kFewPoints = 1 << 16;
+constexpr int kFewPW = 16;
+
+static hipError_t launch_features_rows(const SceneDev& s, int dtype, float z_near,
                                        uint16_t* feats, hipStream_t st) {
   if (s.n <= 0) return hipSuccess;
-  dim3 grid((unsigned)((s.n + 255) / 256));
+  const int pw = s.n <= kFewPoints ? kFewPW : kWave;
+  const dim3 grid((unsigned)((s.n + 4 * pw - 1) / (4 * pw))), block(kFeatureBlock);
+#define FD_FEATURES(T)                                                             \
+  do {                                                                             \
+    if (pw == kWave)                                                               \
+      hipLaunchKernelGGL((k_features<T, kWave>), grid, block, 0, st, s, z_near, feats);  \
+    else                                                                           \
+      hipLaunchKernelGGL((k_features<T, kFewPW>), grid, block, 0, st, s, z_near, feats); \
+  } while (0)
   if (dtype == 1)
-    hipLaunchKernelGGL(k_features<__half>, grid, dim3(256), 0, st, s, z_near, by_j, feats);
+    FD_FEATURES(__half);
   else
-    hipLaunchKernelGGL(k_features<float>, grid, dim3(256), 0, st, s, z_near, by_j, feats);
+    FD_FEATURES(float);
+#undef FD_FEATURES
   return hipGetLastError();
 }
 
@@ -199,7 +235,7 @@ extern "C" int fd_features(const float* points, int64_t n_points, const fd_camer
   s.H = params->height;
   for (int k = 0; k < 3; ++k) s.hc[k] = params->head_centre[k];
   s.pairs = scene_pairs(params->map_dtype, s.W, orient_maps, conf_maps, params->depth_maps);
-  hipError_t e = launch_features_rows(s, params->map_dtype, params->z_near, 0, (uint16_t*)feats,
+  hipError_t e = launch_features_rows(s, params->map_dtype, params->z_near, (uint16_t*)feats,
                                       (hipStream_t)params->stream);
   return e == hipSuccess ? FD_OK : hip_error(e, "feature kernel");
 }

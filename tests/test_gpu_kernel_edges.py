@@ -176,3 +176,40 @@ def test_volume_slots_and_lanes(dims, n):
     # weights outside [0, 1] act as the nearest (the oracle takes them as they are)
     for a, b in zip(out, V._gpu(pts, d, *grid, w)):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("views", [1, 15, 16, 17, 40, 128, 131])
+def test_feature_rows_and_lists(views, half):
+    """Fewer and more views than slots, some of them the same camera again
+    (equal keys: the lower view first); point counts around those that a wave
+    takes, on either side of the 65,536 from which it takes more.  Every count
+    gives the rows that one call over all points gives, and those are the
+    oracle's: the same slots, values within a bfloat16 step (of the 7504, four
+    may miss it: the share that the feature test grants is 1e-4)."""
+    nat = _native()
+    rec = dict(scenegen.RECIPES["tiny"])
+    rec.update(n_views=24, arc_deg=360.0)
+    sc = scenegen.make_scene(rec, 5)
+    v = np.arange(views) % 24
+    v[2::3] = v[1::3][:len(v[2::3])]
+    th, cf, dm = sc.theta[v], sc.conf[v], sc.depth[v]
+    if half:
+        th, cf, dm = (a.astype(np.float16) for a in (th, cf, dm))
+    maps = (_t(sc.cams[v]), _t(th), _t(cf))
+    kw = dict(head_centre=sc.head_centre, depth_maps=_t(dm))
+    few = np.asarray(sc.points[:67], np.float32)
+    pts = _t(np.resize(few, ((1 << 16) + 1 if views == 40 else 67, 3)))
+    rows = nat.features(pts, *maps, **kw)
+    head = rows[:67]
+    if views == 40:  # the points repeat
+        assert torch.equal(rows, head.repeat(len(pts) // 67 + 1, 1)[:len(pts)])
+        assert torch.equal(nat.features(pts[:-1].contiguous(), *maps, **kw), rows[:-1])
+    for n in (1, 3, 15, 16, 17, 63, 64, 65):
+        assert torch.equal(nat.features(pts[:n].contiguous(), *maps, **kw), head[:n]), n
+    f = head.float().cpu().numpy().astype(np.float64)
+    fo = oracle.Oracle(sc.cams[v], th.astype(np.float32), cf.astype(np.float32), patch=1,
+                       depth=dm.astype(np.float32)).features(few, sc.head_centre)
+    assert np.array_equal(f[:, 6::7], fo[:, 6::7])
+    err = np.abs(f - oracle.round_bf16(fo.astype(np.float32)).astype(np.float64))
+    assert (err > 2.0 ** -7 * np.abs(fo) + 1e-5).sum() <= 4

@@ -117,8 +117,7 @@ extern "C" int fd_context_create(fd_context** out) {
   if (!c) return set_error(FD_E_NOMEM, "fd_context_create: host allocation failed");
   c->device = dev;
   size_t cap = 0;
-  if ((r = grow(&c->bbox, &cap, 6, "bbox")) ||
-      (r = grow(&c->counts, &(cap = 0), (size_t)tile_cells(), "cell counts")) ||
+  if ((r = grow(&c->counts, &cap, (size_t)tile_cells(), "cell counts")) ||
       (r = grow(&c->cursor, &(cap = 0), (size_t)tile_cells(), "cell cursor")) ||
       (r = grow(&c->scan_sums, &(cap = 0), (size_t)tile_cells() / 1024, "scan sums")) ||
       (r = grow(&c->lattice, &(cap = 0), (size_t)3 * FD_MAX_CANDIDATES, "lattice")) ||
@@ -150,7 +149,7 @@ extern "C" int fd_context_reserve(fd_context* c, int64_t max_points, int32_t max
 extern "C" void fd_context_destroy(fd_context* c) {
   if (!c) return;
   (void)hipDeviceSynchronize();
-  void* bufs[] = {c->bbox, c->counts, c->cursor, c->scan_sums, c->lattice, c->consts64,
+  void* bufs[] = {c->counts, c->cursor, c->scan_sums, c->lattice, c->consts64,
                   c->cams64,
                   c->fb_count, c->key,
                   c->perm, c->views, c->kcount, c->fb_list, c->prop, c->feats,
@@ -430,11 +429,13 @@ int fd::run_scene(fd_context* c, const SceneArgs& a, const fd_params* p, hipStre
   double step0, lstep0;
   resolve_steps(p, &step0, &lstep0);
   const ConstsDev kc = context_consts(c);
-  hipError_t e0 = launch_consts(kc, p->n_candidates, step0, lstep0, st);
-  if (e0 != hipSuccess) return hip_error(e0, "search constants");
-  TileWork tw{c->bbox, c->key, c->counts, c->cursor, c->scan_sums, c->perm};
+  // a point's rank in its cell: 4 of its 16 bytes of view list
+  static_assert(FD_TOPK_SLOTS * sizeof(uint16_t) >= sizeof(uint32_t), "");
+  TileWork tw{c->key, (uint32_t*)c->views, c->counts, c->cursor, c->scan_sums, c->perm};
   StageTimer t_tile(c, FD_STAGE_TILING, st);
-  hipError_t e = launch_tiling(a.points, a.n, tw, st);
+  hipError_t e = launch_setup(a.points, a.n, tw, c->fb_count, kc, p->n_candidates, step0, lstep0,
+                              a.cams, a.V, c->cams64, st);
+  if (e == hipSuccess) e = launch_tiling(a.points, a.n, tw, st);
   if (e != hipSuccess) return hip_error(e, "tiling kernels");
   t_tile.stop();
   SceneDev s;
@@ -457,8 +458,6 @@ int fd::run_scene(fd_context* c, const SceneArgs& a, const fd_params* p, hipStre
   for (int k = 0; k < 3; ++k) s.hc[k] = a.hc[k];
   s.pairs = scene_pairs(p->map_dtype, a.W, a.theta, a.conf, a.depth);
   const SearchDev q = make_search(kc, p->n_candidates, p->refine_iters, p->top_k, p->z_near);
-  if ((e = launch_cams64(a.cams, a.V, c->cams64, st)) != hipSuccess)
-    return hip_error(e, "camera table");
   s.cam64 = c->cams64;
   const bool fused_topk = p->mode == FD_MODE_LEARNED && p->proposal == FD_PROPOSAL_MLP;
   if (!fused_topk) {  // the learned network path selects views with its features

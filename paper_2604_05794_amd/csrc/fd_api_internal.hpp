@@ -17,7 +17,6 @@ struct fd_context {
   // batched graph or uploaded scene table never keeps a freed pointer
   uint64_t generation = 0;
   // fixed buffers
-  int* bbox = nullptr;
   uint32_t* counts = nullptr;
   uint32_t* cursor = nullptr;
   uint32_t* scan_sums = nullptr;

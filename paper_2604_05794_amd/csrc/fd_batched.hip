@@ -91,6 +91,13 @@ __device__ __forceinline__ int64_t block_point(const BatchDev& b, int* scene,
 // this stage 137 us for 2M points.  k_b_bbox_final folds the copies.
 constexpr int kBboxRep = 64;
 
+// The camera table of scene blockIdx.y.
+__global__ void k_b_cams64(BatchDev b) {
+  const SceneDev& sc = b.tab[blockIdx.y];
+  const int v = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (sc.n > 0 && v < sc.V) camera_record(sc.cams, v, (double*)sc.cam64);
+}
+
 __global__ void k_b_init(uint32_t* counts, int64_t n_counts, int* rep, int n_scenes) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -153,6 +160,7 @@ __device__ __forceinline__ uint32_t spread3_b(uint32_t x) {
 
 __global__ __launch_bounds__(kBlock) void k_b_count(BatchDev b, const int* __restrict__ bbox,
                                                     uint32_t* __restrict__ key,
+                                                    uint32_t* __restrict__ rank,
                                                     uint32_t* __restrict__ counts) {
   int s;
   const int64_t j = block_point(b, &s);
@@ -170,19 +178,20 @@ __global__ __launch_bounds__(kBlock) void k_b_count(BatchDev b, const int* __res
   }
   const uint32_t k = spread3_b(q[0]) | (spread3_b(q[1]) << 1) | (spread3_b(q[2]) << 2);
   key[b.pt_off[s] + j] = k;
-  atomicAdd(&counts[(size_t)s * kBCells + k], 1u);
+  rank[b.pt_off[s] + j] = atomicAdd(&counts[(size_t)s * kBCells + k], 1u);
 }
 
 // cursor holds global positions (scenes concatenated, cells scene-major);
 // perm receives the scene-local point index
 __global__ __launch_bounds__(kBlock) void k_b_scatter(BatchDev b, const uint32_t* __restrict__ key,
-                                                      uint32_t* __restrict__ cursor,
+                                                      const uint32_t* __restrict__ rank,
+                                                      const uint32_t* __restrict__ cursor,
                                                       uint32_t* __restrict__ perm) {
   int s;
   const int64_t j = block_point(b, &s);
   if (j < 0) return;
-  const uint32_t pos = atomicAdd(&cursor[(size_t)s * kBCells + key[b.pt_off[s] + j]], 1u);
-  perm[pos] = (uint32_t)j;
+  const int64_t i = b.pt_off[s] + j;
+  perm[cursor[(size_t)s * kBCells + key[i]] + rank[i]] = (uint32_t)j;
 }
 
 template <typename T, int KS>
@@ -498,8 +507,8 @@ int fd::context_reserve_scenes(fd_context* c, int32_t n_scenes, int64_t total_po
 // ---- the batched call --------------------------------------------------------------------
 
 static int record_batch(fd_context* c, const fd_params* p, int n_scenes, int64_t total,
-                        const int64_t* blk_off_host, int64_t n_tiles, const float* const* cams,
-                        const int* views, const int64_t* view_off, hipStream_t st) {
+                        const int64_t* blk_off_host, int64_t n_tiles, const int* views,
+                        hipStream_t st) {
   SceneDev* tab = (SceneDev*)c->scene_tab;
   int64_t* pt_off = (int64_t*)(tab + FD_MAX_BATCH_SCENES);
   int64_t* blk_off = pt_off + (FD_MAX_BATCH_SCENES + 1);
@@ -511,11 +520,11 @@ static int record_batch(fd_context* c, const fd_params* p, int n_scenes, int64_t
   uint32_t* sums = c->batch_perm + FD_MAX_BATCH_SCENES * kBCells;
   int* bbox = (int*)c->tile_tab;
   hipError_t e;
+  int max_views = 0;
+  for (int s = 0; s < n_scenes; ++s) max_views = views[s] > max_views ? views[s] : max_views;
   // binary64 camera tables of every scene
-  for (int s = 0; s < n_scenes; ++s)
-    if ((e = launch_cams64(cams[s], views[s], c->cams64 + (size_t)kCam64 * view_off[s], st)) !=
-        hipSuccess)
-      return hip_error(e, "camera tables");
+  hipLaunchKernelGGL(k_b_cams64, dim3((unsigned)((max_views + 127) / 128), (unsigned)n_scenes),
+                     dim3(128), 0, st, b);
   // tiling
   StageTimer t_tile(c, FD_STAGE_TILING, st);
   int* rep = bbox + 6 * FD_MAX_BATCH_SCENES;
@@ -523,11 +532,13 @@ static int record_batch(fd_context* c, const fd_params* p, int n_scenes, int64_t
                      rep, n_scenes);
   hipLaunchKernelGGL(k_b_bbox, dim3((unsigned)nblocks), dim3(kBlock), 0, st, b, rep);
   hipLaunchKernelGGL(k_b_bbox_final, dim3(1), dim3(256), 0, st, rep, n_scenes, bbox);
+  // ranks within the cells in the view lists' place, as in run_scene
+  uint32_t* rank = (uint32_t*)c->views;
   hipLaunchKernelGGL(k_b_count, dim3((unsigned)nblocks), dim3(kBlock), 0, st, b, bbox, c->key,
-                     counts);
+                     rank, counts);
   if ((e = launch_scan_runs(counts, n_scenes * (kBCells / 1024), sums, cursor, st)) != hipSuccess)
     return hip_error(e, "batched scan");
-  hipLaunchKernelGGL(k_b_scatter, dim3((unsigned)nblocks), dim3(kBlock), 0, st, b, c->key, cursor,
+  hipLaunchKernelGGL(k_b_scatter, dim3((unsigned)nblocks), dim3(kBlock), 0, st, b, c->key, rank, cursor,
                      c->perm);
   t_tile.stop();
   double step0, lstep0;
@@ -584,8 +595,6 @@ static int record_batch(fd_context* c, const fd_params* p, int n_scenes, int64_t
       StageTimer t_feat(c, FD_STAGE_FEATURES, st);
       const dim3 grid((unsigned)nblocks), block(kBlock);
       const bool k5 = q.K <= 5;
-      int max_views = 0;
-      for (int s = 0; s < n_scenes; ++s) max_views = views[s] > max_views ? views[s] : max_views;
       const bool m = max_views <= kMaskViews;
 #define FD_B_TOPK_FEATURES(T, KS)                                                          \
   do {                                                                                     \
@@ -664,7 +673,6 @@ extern "C" int fd_fuse_directions_batched(const fd_scene* scenes, int32_t n_scen
   const int G = 64 / params->top_k;  // points per search tile (one wave)
   std::vector<int64_t> pt_off(n_scenes + 1, 0), blk_off(n_scenes + 1, 0),
       tile_off(n_scenes + 1, 0), view_off(n_scenes + 1, 0);
-  std::vector<const float*> cam_ptrs(n_scenes);
   std::vector<int> n_views(n_scenes);
   for (int s = 0; s < n_scenes; ++s) {
     const fd_scene& sc = scenes[s];
@@ -683,7 +691,6 @@ extern "C" int fd_fuse_directions_batched(const fd_scene* scenes, int32_t n_scen
     blk_off[s + 1] = blk_off[s] + (sc.n_points + kBlock - 1) / kBlock;
     tile_off[s + 1] = tile_off[s] + (sc.n_points + G - 1) / G;
     view_off[s + 1] = view_off[s] + sc.n_views;
-    cam_ptrs[s] = (const float*)sc.cams;
     n_views[s] = sc.n_views;
   }
   if (total > (int64_t)UINT32_MAX) return set_error(FD_E_INVAL, "%s: too many points", fn);
@@ -767,7 +774,7 @@ extern "C" int fd_fuse_directions_batched(const fd_scene* scenes, int32_t n_scen
     // stage timing: the same kernels launched directly, with events between
     // the stages (a graph would hold no event records)
     r = record_batch(ctx, params, n_scenes, total, blk_off.data(), tile_off[n_scenes],
-                     cam_ptrs.data(), n_views.data(), view_off.data(), st);
+                     n_views.data(), st);
     if (r) return r;
     tb.stop();
     return FD_OK;
@@ -786,7 +793,7 @@ extern "C" int fd_fuse_directions_batched(const fd_scene* scenes, int32_t n_scen
     e = hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_error(e, "hipStreamBeginCapture");
     r = record_batch(ctx, params, n_scenes, total, blk_off.data(), tile_off[n_scenes],
-                     cam_ptrs.data(), n_views.data(), view_off.data(), ctx->cap_stream);
+                     n_views.data(), ctx->cap_stream);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(ctx->cap_stream, &g);
     if (r) {

@@ -8,6 +8,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "../../include/fusedir.h"
+#include "fd_kernels.hpp"
+
 namespace fd {
 
 constexpr int kWave = 64;
@@ -267,6 +270,65 @@ __device__ __forceinline__ V group_sum_t(V v, int group_base, int k) {
   } else {
     return group_sum<V>(v, group_base, k);
   }
+}
+
+// ---- per-call constants -------------------------------------------------------
+// Hemisphere Fibonacci lattice (Gonzalez 2010): z_k = 1 - (k + 1/2)/n,
+// psi_k = k pi (3 - sqrt 5), in binary64 and rounded to binary32 for the
+// lattice stage.  Refinement steps alpha_t = step0 / 2^t (exact halvings) with
+// their cosines, sines and cosines minus one, for the plain search and for
+// the learned form's short refinement.  The part of index k (below
+// n_constants(n)).
+__host__ __device__ inline int n_constants(int n) {
+  return n > 2 * FD_MAX_REFINE ? n : 2 * FD_MAX_REFINE;
+}
+__device__ __forceinline__ void search_constants(const ConstsDev& c, int n, double step0,
+                                                 double lstep0, int k) {
+  if (k < n) {
+    const double golden = 3.14159265358979323846 * (3.0 - sqrt(5.0));
+    const double z = 1.0 - ((double)k + 0.5) / (double)n;
+    const double rho = sqrt(fmax(0.0, 1.0 - z * z));
+    const double psi = golden * (double)k;
+    const double x = rho * cos(psi), y = rho * sin(psi);
+    c.lattice64[3 * k] = x;
+    c.lattice64[3 * k + 1] = y;
+    c.lattice64[3 * k + 2] = z;
+    c.lattice[3 * k] = (float)x;
+    c.lattice[3 * k + 1] = (float)y;
+    c.lattice[3 * k + 2] = (float)z;
+  }
+  if (k < 2 * FD_MAX_REFINE) {
+    const int t = k % FD_MAX_REFINE;
+    const double a = (k < FD_MAX_REFINE ? step0 : lstep0) * ldexp(1.0, -t);
+    double* dst = c.steps + (k < FD_MAX_REFINE ? 0 : 3 * FD_MAX_REFINE);
+    const double h = sin(0.5 * a);
+    dst[t] = cos(a);
+    dst[FD_MAX_REFINE + t] = sin(a);
+    dst[2 * FD_MAX_REFINE + t] = -2.0 * h * h;  // cos a - 1 without cancellation
+  }
+}
+
+// ---- per-call camera table: the record of view v ------------------------------
+__device__ __forceinline__ void camera_record(const float* __restrict__ cams, int v,
+                                              double* __restrict__ out) {
+  const float* c = cams + 16 * v;
+  const double fx = c[0], fy = c[1], cx = c[2], cy = c[3];
+  const float* R = c + 4;
+  const float* t = c + 13;
+  double* o = out + (size_t)kCam64 * v;
+  for (int k = 0; k < 3; ++k) {
+    o[k] = fx * (double)R[k] + cx * (double)R[6 + k];
+    o[4 + k] = fy * (double)R[3 + k] + cy * (double)R[6 + k];
+    o[8 + k] = (double)R[6 + k];
+  }
+  o[3] = fx * (double)t[0] + cx * (double)t[2];
+  o[7] = fy * (double)t[1] + cy * (double)t[2];
+  o[11] = (double)t[2];
+  for (int k = 0; k < 3; ++k)
+    o[12 + k] = -((double)R[k] * t[0] + (double)R[3 + k] * t[1] + (double)R[6 + k] * t[2]);
+  o[15] = 0.0;
+  for (int k = 0; k < 8; ++k)
+    o[kCam32Off + k] = __builtin_bit_cast(double, make_float2(c[2 * k], c[2 * k + 1]));
 }
 
 }  // namespace fd

@@ -13,8 +13,8 @@ namespace fd {
 
 // Workspace of the spatial tiling (fd_tile.hip).
 struct TileWork {
-  int* bbox;         // 6 ints
   uint32_t* key;     // n
+  uint32_t* rank;    // n (the view lists' place: they are made later)
   uint32_t* counts;  // tile_cells()
   uint32_t* cursor;  // tile_cells()
   uint32_t* sums;    // tile_cells() / 1024
@@ -143,8 +143,10 @@ constexpr int kConstsDoubles = 3 * FD_MAX_CANDIDATES + 6 * FD_MAX_REFINE;
 
 hipError_t launch_fpmvo(const SceneDev& s, const SearchDev& q, const FpmvoDev& f, int dtype,
                         int patch, hipStream_t st);
+hipError_t launch_setup(const float* pts, int64_t n, TileWork w, uint32_t* fb_count,
+                        const ConstsDev& c, int n_candidates, double step0, double lstep0,
+                        const float* cams, int V, double* cam64, hipStream_t st);
 hipError_t launch_tiling(const float* pts, int64_t n, TileWork w, hipStream_t st);
-hipError_t launch_identity_perm(int64_t n, uint32_t* perm, hipStream_t st);
 hipError_t launch_scan_runs(const uint32_t* counts, int n_runs, uint32_t* sums, uint32_t* cursor,
                             hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);

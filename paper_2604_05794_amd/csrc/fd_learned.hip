@@ -106,8 +106,6 @@ static hipError_t launch_features_rows(const SceneDev& s, int dtype, float z_nea
 int fd::run_learned(fd_context* c, const SceneDev& s, const SearchDev& q, const fd_params* p,
                     hipStream_t st) {
   hipError_t e;
-  if ((e = launch_fill_u32(c->fb_count, 2, 0u, st)) != hipSuccess)
-    return hip_error(e, "fallback counter reset");
   LearnedDev l;
   // the learned steps follow the plain ones in the per-call constants
   l.steps = q.steps + 3 * FD_MAX_REFINE;

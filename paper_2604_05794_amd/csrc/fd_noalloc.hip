@@ -25,8 +25,7 @@ constexpr size_t kCellsMax = (size_t)1 << 18;  // cells of the single-scene tili
 // byte offsets of the workspace inside the array
 constexpr size_t kOffLattice = 0;
 constexpr size_t kOffConsts = align_up(kOffLattice + sizeof(float) * 3 * FD_MAX_CANDIDATES);
-constexpr size_t kOffBbox = align_up(kOffConsts + sizeof(double) * kConstsDoubles);
-constexpr size_t kOffCounts = align_up(kOffBbox + sizeof(int) * 8);
+constexpr size_t kOffCounts = align_up(kOffConsts + sizeof(double) * kConstsDoubles);
 constexpr size_t kOffCursor = align_up(kOffCounts + sizeof(uint32_t) * kCellsMax);
 constexpr size_t kOffSums = align_up(kOffCursor + sizeof(uint32_t) * kCellsMax);
 constexpr size_t kOffFbCount = align_up(kOffSums + sizeof(uint32_t) * (kCellsMax / 1024));
@@ -107,7 +106,6 @@ extern "C" int fd_fuse_directions_noalloc(const float* points, int64_t n_points,
   c.max_points = (int64_t)kMaxPts;
   c.lattice = (float*)(base + kOffLattice);
   c.consts64 = (double*)(base + kOffConsts);
-  c.bbox = (int*)(base + kOffBbox);
   c.counts = (uint32_t*)(base + kOffCounts);
   c.cursor = (uint32_t*)(base + kOffCursor);
   c.scan_sums = (uint32_t*)(base + kOffSums);

@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fd_device.hpp"
 #include "fd_kernels.hpp"
 
 namespace fd {
@@ -30,44 +31,61 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, int64_t n, uint32_t v) {
   for (; i < n; i += stride) p[i] = v;
 }
 
-// bbox[0..2] = ordered min, bbox[3..5] = ordered max (pre-filled by the host
-// path with INT_MAX / INT_MIN through k_fill_u32).  Grid-stride loop, then a
-// wave and a workgroup reduction, so there are 6 atomics per workgroup.
-__global__ __launch_bounds__(256) void k_bbox(const float* __restrict__ pts,
-                                              int64_t n, int* __restrict__ bbox) {
+// The smallest (v[0..2]) and largest (v[3..5]) ordered value over the
+// workgroup's 256 threads, in every thread.
+__device__ __forceinline__ void block_box(int (&v)[6]) {
   __shared__ int red[4][6];
-  int v[6] = {INT32_MAX, INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN, INT32_MIN};
-  int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    for (int a = 0; a < 3; ++a) {
-      float f = pts[3 * i + a];
-      if (f == f) {  // skip NaN
-        int o = float_to_ordered(f);
-        v[a] = min(v[a], o);
-        v[3 + a] = max(v[3 + a], o);
-      }
-    }
-  }
   for (int a = 0; a < 3; ++a) {
     for (int off = 32; off > 0; off >>= 1) {
       v[a] = min(v[a], __shfl_xor(v[a], off, 64));
       v[3 + a] = max(v[3 + a], __shfl_xor(v[3 + a], off, 64));
     }
   }
-  const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0)
-    for (int a = 0; a < 6; ++a) red[w][a] = v[a];
+    for (int a = 0; a < 6; ++a) red[threadIdx.x >> 6][a] = v[a];
   __syncthreads();
-  if (threadIdx.x < 6) {
-    const int a = threadIdx.x;
-    int r = red[0][a];
-    for (int k = 1; k < (int)(blockDim.x >> 6); ++k)
-      r = a < 3 ? min(r, red[k][a]) : max(r, red[k][a]);
-    if (a < 3)
-      atomicMin(&bbox[a], r);
-    else
-      atomicMax(&bbox[a], r);
+  for (int a = 0; a < 3; ++a) {
+    v[a] = min(min(red[0][a], red[1][a]), min(red[2][a], red[3][a]));
+    v[3 + a] = max(max(red[0][3 + a], red[1][3 + a]), max(red[2][3 + a], red[3][3 + a]));
   }
+}
+
+// All that a call starts with, in one launch (five before, 2 to 4 us each):
+// the cell counts and the fallback counters cleared, the search constants,
+// the camera table, and every workgroup's part of the points' bounding box
+// (boxes[6 b ..]; the next kernel folds the parts, so that none of them
+// needs a value to start from).
+constexpr int kSetupBlocks = 256;
+__global__ __launch_bounds__(256) void k_setup(const float* __restrict__ pts, int64_t n,
+                                               int* __restrict__ boxes,
+                                               uint32_t* __restrict__ counts,
+                                               uint32_t* __restrict__ fb_count, ConstsDev c,
+                                               int n_candidates, double step0, double lstep0,
+                                               const float* __restrict__ cams, int V,
+                                               double* __restrict__ cam64) {
+  const int first = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  constexpr int kStride = kSetupBlocks * 256;
+  int v[6] = {INT32_MAX, INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN, INT32_MIN};
+  for (int64_t i = first; i < n; i += kStride) {
+    for (int a = 0; a < 3; ++a) {
+      const float f = pts[3 * i + a];
+      if (f == f) {  // skip NaN
+        const int o = float_to_ordered(f);
+        v[a] = min(v[a], o);
+        v[3 + a] = max(v[3 + a], o);
+      }
+    }
+  }
+  for (int k = first; k < kCells; k += kStride) counts[k] = 0u;
+  if (first < 2) fb_count[first] = 0u;
+  // from the last thread down: the first workgroups may have more points
+  const int last = kStride - 1 - first;
+  for (int k = last; k < n_constants(n_candidates); k += kStride)
+    search_constants(c, n_candidates, step0, lstep0, k);
+  for (int k = last; k < V; k += kStride) camera_record(cams, k, cam64);
+  block_box(v);
+  if (threadIdx.x == 0)
+    for (int a = 0; a < 6; ++a) boxes[6 * blockIdx.x + a] = v[a];
 }
 
 __device__ __forceinline__ uint32_t spread3(uint32_t x) {
@@ -77,15 +95,23 @@ __device__ __forceinline__ uint32_t spread3(uint32_t x) {
   return r;
 }
 
+// The count's old value is the point's rank within its cell, so that the
+// scatter is a plain write (with a second atomic there: count and scatter 30 +
+// 34 us for 500,000 points, now 31 + 8).
 __global__ __launch_bounds__(256) void k_cell_count(const float* __restrict__ pts,
-                                                    int64_t n, const int* __restrict__ bbox,
+                                                    int64_t n, const int* __restrict__ boxes,
                                                     uint32_t* __restrict__ key,
+                                                    uint32_t* __restrict__ rank,
                                                     uint32_t* __restrict__ counts) {
+  static_assert(kSetupBlocks == 256, "one part of the box per thread");
+  int box[6];
+  for (int a = 0; a < 6; ++a) box[a] = boxes[6 * threadIdx.x + a];
+  block_box(box);
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   uint32_t q[3];
   for (int a = 0; a < 3; ++a) {
-    float lo = ordered_to_float(bbox[a]), hi = ordered_to_float(bbox[3 + a]);
+    float lo = ordered_to_float(box[a]), hi = ordered_to_float(box[3 + a]);
     float f = pts[3 * i + a];
     float ext = hi - lo;
     float s = ext > 0.0f ? (f - lo) / ext : 0.0f;
@@ -95,13 +121,12 @@ __global__ __launch_bounds__(256) void k_cell_count(const float* __restrict__ pt
   }
   uint32_t k = spread3(q[0]) | (spread3(q[1]) << 1) | (spread3(q[2]) << 2);
   key[i] = k;
-  atomicAdd(&counts[k], 1u);
+  rank[i] = atomicAdd(&counts[k], 1u);
 }
 
 // Exclusive scan of the kCells counts in two passes: k_cell_block_sums
 // reduces each run of 1024 cells; k_cell_scan scans those sums and then its
-// own run, writing the cell start offsets into `cursor` (the scatter
-// advances them).  Both read coalesced.
+// own run, writing the cell start offsets into `cursor`.  Both read coalesced.
 constexpr int kScanRun = 1024;
 constexpr int kScanRuns = kCells / kScanRun;  // 256
 
@@ -157,41 +182,38 @@ __global__ __launch_bounds__(1024) void k_cell_scan(const uint32_t* __restrict__
 }
 
 __global__ __launch_bounds__(256) void k_cell_scatter(const uint32_t* __restrict__ key,
+                                                      const uint32_t* __restrict__ rank,
                                                       int64_t n,
-                                                      uint32_t* __restrict__ cursor,
+                                                      const uint32_t* __restrict__ cursor,
                                                       uint32_t* __restrict__ perm) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  uint32_t pos = atomicAdd(&cursor[key[i]], 1u);
-  perm[pos] = (uint32_t)i;
+  perm[cursor[key[i]] + rank[i]] = (uint32_t)i;
 }
 
-__global__ void k_iota(uint32_t* __restrict__ perm, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) perm[i] = (uint32_t)i;
+hipError_t launch_setup(const float* pts, int64_t n, TileWork w, uint32_t* fb_count,
+                        const ConstsDev& c, int n_candidates, double step0, double lstep0,
+                        const float* cams, int V, double* cam64, hipStream_t st) {
+  // the parts of the box in the cursors' place: they are read before the scan
+  static_assert(6 * kSetupBlocks <= kCells, "");
+  hipLaunchKernelGGL(k_setup, dim3(kSetupBlocks), dim3(256), 0, st, pts, n, (int*)w.cursor,
+                     w.counts, fb_count, c, n_candidates, step0, lstep0, cams, V, cam64);
+  return hipGetLastError();
 }
 
+// After launch_setup.
 hipError_t launch_tiling(const float* pts, int64_t n, TileWork w, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   const int bs = 256;
   const int64_t nb = (n + bs - 1) / bs;
-  // bbox <- (INT_MAX x3, INT_MIN x3), counts <- 0, through fill kernels so
-  // the sequence stays valid under stream capture
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, (uint32_t*)w.bbox, (int64_t)3,
-                     (uint32_t)INT32_MAX);
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, (uint32_t*)(w.bbox + 3),
-                     (int64_t)3, (uint32_t)INT32_MIN);
-  hipLaunchKernelGGL(k_fill_u32, dim3(256), dim3(256), 0, st, w.counts, (int64_t)kCells, 0u);
-  int gb = (int)(nb < 256 ? nb : 256);
-  hipLaunchKernelGGL(k_bbox, dim3(gb), dim3(bs), 0, st, pts, n, w.bbox);
-  hipLaunchKernelGGL(k_cell_count, dim3((unsigned)nb), dim3(bs), 0, st, pts, n, w.bbox,
-                     w.key, w.counts);
+  hipLaunchKernelGGL(k_cell_count, dim3((unsigned)nb), dim3(bs), 0, st, pts, n,
+                     (const int*)w.cursor, w.key, w.rank, w.counts);
   hipLaunchKernelGGL(k_cell_block_sums, dim3(kScanRuns), dim3(kScanRun), 0, st, w.counts,
                      w.sums);
   hipLaunchKernelGGL(k_cell_scan, dim3(kScanRuns), dim3(kScanRun), 0, st, w.counts, w.sums,
                      w.cursor);
-  hipLaunchKernelGGL(k_cell_scatter, dim3((unsigned)nb), dim3(bs), 0, st, w.key, n, w.cursor,
-                     w.perm);
+  hipLaunchKernelGGL(k_cell_scatter, dim3((unsigned)nb), dim3(bs), 0, st, w.key, w.rank, n,
+                     w.cursor, w.perm);
   return hipGetLastError();
 }
 
@@ -236,12 +258,6 @@ hipError_t launch_scan_runs(const uint32_t* counts, int n_runs, uint32_t* sums, 
   hipLaunchKernelGGL(k_run_scan, dim3(1), dim3(kScanRun), 0, st, sums, n_runs);
   hipLaunchKernelGGL(k_cell_scan_from, dim3(n_runs), dim3(kScanRun), 0, st, counts, sums,
                      cursor);
-  return hipGetLastError();
-}
-
-hipError_t launch_identity_perm(int64_t n, uint32_t* perm, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_iota, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, perm, n);
   return hipGetLastError();
 }
 

@@ -213,3 +213,28 @@ def test_feature_rows_and_lists(views, half):
     assert np.array_equal(f[:, 6::7], fo[:, 6::7])
     err = np.abs(f - oracle.round_bf16(fo.astype(np.float32)).astype(np.float64))
     assert (err > 2.0 ** -7 * np.abs(fo) + 1e-5).sum() <= 4
+
+
+@pytest.mark.parametrize("n", [1, 255, 257, 4095, 66000])
+def test_setup_and_cell_ranks(n):
+    """Point counts around a workgroup and above one round of the setup
+    kernel (65,536 threads), points of one cell, a NaN: a point's result does
+    not depend on the others, so every call gives the bits of its part of one
+    call over all."""
+    nat = _native()
+    sc = scenegen.make_scene("tiny", 7)
+    few = np.asarray(sc.points[:997], np.float32)
+    pts = np.resize(few, (n, 3)).copy()
+    pts[n // 2:] += np.float32(1e-6)  # twice the cells' points, not the same
+    kw = dict(depth_maps=_t(sc.depth), patch=3, n_candidates=32, refine_iters=3, top_k=3)
+    maps = (_t(sc.cams), _t(sc.theta), _t(sc.conf))
+    one = nat.fuse_directions(_t(pts), *maps, **kw)
+    torch.cuda.synchronize()
+    part = max(1, n // 3)
+    for rows in (np.arange(part), np.arange(n)[::-1].copy()):
+        d, c = nat.fuse_directions(_t(pts[rows]), *maps, **kw)
+        assert torch.equal(d, one[0][_t(rows)]) and torch.equal(c, one[1][_t(rows)])
+    bad = np.vstack([pts[:part], np.full((1, 3), np.nan, np.float32)])
+    d, c = nat.fuse_directions(_t(bad), *maps, **kw)
+    assert torch.equal(d[:-1], one[0][:part]) and torch.equal(c[:-1], one[1][:part])
+    assert not d[-1].any() and torch.isinf(c[-1])

@@ -238,3 +238,28 @@ def test_setup_and_cell_ranks(n):
     d, c = nat.fuse_directions(_t(bad), *maps, **kw)
     assert torch.equal(d[:-1], one[0][:part]) and torch.equal(c[:-1], one[1][:part])
     assert not d[-1].any() and torch.isinf(c[-1])
+
+
+@pytest.mark.parametrize("patch", [1, 3, 5, 7])
+@pytest.mark.parametrize("scale", [10, -19, -22, -30, 29, 32])
+def test_patch_normalisation_ranges(patch, scale):
+    """Confidences times a power of two scale every sample's form exactly and
+    leave every decision as it is, so the directions are the same bits whether
+    the short or the general normalisation is taken (within 2^-44 < n2 and
+    a form below 2^60, outside, or both in one map: confidences reach down
+    from 1).  Costs are 1 - S / K of the scaled sums."""
+    nat = _native()
+    sc = scenegen.make_scene("tiny", 11)
+    pts = _t(sc.points[:1500])
+    kw = dict(depth_maps=_t(sc.depth), patch=patch, n_candidates=48, refine_iters=6, top_k=4)
+    th = _t(sc.theta.astype(np.float32))
+    cf = sc.conf.astype(np.float32)
+    d0, c0 = nat.fuse_directions(pts, _t(sc.cams), th, _t(cf), **kw)
+    d1, c1 = nat.fuse_directions(pts, _t(sc.cams), th, _t(cf * np.float32(2.0 ** scale)), **kw)
+    assert torch.equal(d0, d1)
+    s0, s1 = 1.0 - c0.double(), (1.0 - c1.double()) * 2.0 ** -scale
+    ok = torch.isfinite(c0)
+    assert torch.equal(ok, torch.isfinite(c1))
+    # both costs are rounded to binary32
+    tol = 2.0 ** -24 * (1.0 + c0.double().abs() + (1.0 + c1.double().abs()) * 2.0 ** -scale)
+    assert ((s0 - s1).abs() <= tol)[ok].all()

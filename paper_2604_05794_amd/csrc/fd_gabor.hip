@@ -177,13 +177,15 @@ struct GaborLds {
 // every pixel's the same: one of a wave's 128 pixels waits and stands for
 // all (kFixAll).  Where most of a wave's pixels wait (smooth regions without
 // any noise) the wave sums its rows at once (dense).
+// Which sum a pixel's confidence comes from depends on its tile alone, so a
+// frame's maps do not depend on the other frames of a call.
 // Bound by the matrix operations (half of their issue slots; the clock drops
 // to 1.8 GHz under them) and the epilogue's 630 vector instructions a tile
 // and wave.  64 frames of 1024 x 1024, radius 8, 32 orientations, on the maps
-// of rendered hair: 10.4 -> 4.6 ms (binary32 operations only before; 4.2 ms
-// without a second sum); 16 frames of noise 2.82 -> 1.30 ms, of a constant
-// 2.61 -> 1.85 ms, of a linear ramp without noise (every pixel summed twice,
-// the worst case) 2.65 -> 4.5 ms.
+// of rendered hair: 10.4 -> 4.41 ms (binary32 operations only before); 16
+// frames of noise 2.82 -> 1.23 ms, of a constant 2.61 -> 1.84 ms, of a linear
+// ramp without noise (every response is rounding: the worst case) 2.65 -> 4.42
+// ms.
 // FULL: 32 orientations (no validity tests).
 constexpr int kFixRound = 16 * kWaves;
 constexpr int kFixCap = kFixRound + kTile * kTileRows;  // a round less one, plus a tile's
@@ -487,6 +489,38 @@ __global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
       place(tid + gridDim.x);
       load_tile(f, x0, y0, tv);
     }
+    // The range of the pixels that the wave's rows read, from the high
+    // halves (which are within 2^-11 of them).
+    f16x2 lo2 = {(_Float16)INFINITY, (_Float16)INFINITY}, hi2 = -lo2;
+    for (int e = lane; e < (kRowsPerWave + 2 * R) * (RS / 2); e += 64) {
+      const bool on = e % (RS / 2) < tw / 2;
+      const f16x2 v = __builtin_bit_cast(f16x2, lds[L.planes + kRowsPerWave * w * (RS / 2) + e]);
+      lo2 = on ? __builtin_elementwise_min(lo2, v) : lo2;
+      hi2 = on ? __builtin_elementwise_max(hi2, v) : hi2;
+    }
+    float lo = fminf((float)lo2[0], (float)lo2[1]), hi = fmaxf((float)hi2[0], (float)hi2[1]);
+    for (int off = 32; off > 0; off >>= 1) {
+      lo = fminf(lo, __shfl_xor(lo, off, 64));
+      hi = fmaxf(hi, __shfl_xor(hi, off, 64));
+    }
+    lo = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(lo)));
+    hi = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(hi)));
+    // in units of the scaled responses
+    float mg = kBankScale * (margin.mid * fabsf(0.5f * (hi + lo)) +
+                                   margin.half * (0.5f * (hi - lo) +
+                                                  0x1p-10f * fmaxf(fabsf(hi), fabsf(lo))));
+    // A window far below the tile's largest pixel has lost bits to the split's
+    // smallest step (2^-24, as 2^-22 of a pixel of 1/4): summed again.
+    const float top = fmaxf(fabsf(hi), fabsf(lo));
+    if (top < 1.0f) {  // uniform
+      int any = top > 0.0f;
+#pragma unroll
+      for (int k = 0; k < kWaves; ++k) any |= wlost[k];
+      if (any) mg = INFINITY;
+    }
+    float m = 0.0f;
+    const bool inner = cx0 >= R && cx0 + kTile + R <= W && cy0 + kRowsPerWave * w >= R &&
+                       cy0 + kRowsPerWave * (w + 1) + R <= H;
     f32x16 acc[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -557,33 +591,6 @@ __global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
           acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[q], acc[q], 0, 0, 0);
       }
     }
-    // The range of the pixels that the wave's rows read, from the high
-    // halves (which are within 2^-11 of them).
-    f16x2 lo2 = {(_Float16)INFINITY, (_Float16)INFINITY}, hi2 = -lo2;
-    for (int e = lane; e < (kRowsPerWave + 2 * R) * (RS / 2); e += 64) {
-      const bool on = e % (RS / 2) < tw / 2;
-      const f16x2 v = __builtin_bit_cast(f16x2, lds[L.planes + kRowsPerWave * w * (RS / 2) + e]);
-      lo2 = on ? __builtin_elementwise_min(lo2, v) : lo2;
-      hi2 = on ? __builtin_elementwise_max(hi2, v) : hi2;
-    }
-    float lo = fminf((float)lo2[0], (float)lo2[1]), hi = fmaxf((float)hi2[0], (float)hi2[1]);
-    for (int off = 32; off > 0; off >>= 1) {
-      lo = fminf(lo, __shfl_xor(lo, off, 64));
-      hi = fmaxf(hi, __shfl_xor(hi, off, 64));
-    }
-    // in units of the scaled responses
-    float mg = kBankScale * (margin.mid * fabsf(0.5f * (hi + lo)) +
-                                   margin.half * (0.5f * (hi - lo) +
-                                                  0x1p-10f * fmaxf(fabsf(hi), fabsf(lo))));
-    // A window far below the tile's largest pixel has lost bits to the split's
-    // smallest step (2^-24, as 2^-22 of a pixel of 1/4): summed again.
-    const float top = fmaxf(fabsf(hi), fabsf(lo));
-    if (top < 1.0f) {  // uniform
-      int any = top > 0.0f;
-#pragma unroll
-      for (int k = 0; k < kWaves; ++k) any |= wlost[k];
-      if (any) mg = INFINITY;
-    }
     // per pixel: argmax |F_j| (first of equals), then the spread of the
     // responses around it
     int jbs[4];
@@ -603,7 +610,6 @@ __global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
       n_near += __popcll(__ballot(near));
       near_q |= near ? 1u << q : 0u;
     }
-    float m = 0.0f;
     // one value all over the window of the wave's pixels: then no part of it
     // is outside the frame, which reads as 0 (and 0 everywhere is no choice)
     bool flat = n_near > 1 && lo == hi && lo != 0.0f;
@@ -628,8 +634,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
       if (lane == 0)
         fix[atomicAdd(&n_fix, 1)] =
             make_int2(cf, ((cy0 + kRowsPerWave * w) * W + cx0) | kFixAll);
-    } else if (n_near > kDense && cx0 >= R && cx0 + kTile + R <= W &&
-               cy0 + kRowsPerWave * w >= R && cy0 + kRowsPerWave * (w + 1) + R <= H) {  // uniform
+    } else if (n_near > kDense && inner) {  // uniform
       m = dense(cf, cx0, cy0 + kRowsPerWave * w);
     } else {
 #pragma unroll

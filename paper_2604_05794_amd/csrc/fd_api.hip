@@ -432,8 +432,10 @@ int fd::run_scene(fd_context* c, const SceneArgs& a, const fd_params* p, hipStre
   // a point's rank in its cell: 4 of its 16 bytes of view list
   static_assert(FD_TOPK_SLOTS * sizeof(uint16_t) >= sizeof(uint32_t), "");
   TileWork tw{c->key, (uint32_t*)c->views, c->counts, c->cursor, c->scan_sums, c->perm};
+  // the counters stay those of the last learned call on the context
+  uint32_t* const fb_count = p->mode == FD_MODE_LEARNED ? c->fb_count : nullptr;
   StageTimer t_tile(c, FD_STAGE_TILING, st);
-  hipError_t e = launch_setup(a.points, a.n, tw, c->fb_count, kc, p->n_candidates, step0, lstep0,
+  hipError_t e = launch_setup(a.points, a.n, tw, fb_count, kc, p->n_candidates, step0, lstep0,
                               a.cams, a.V, c->cams64, st);
   if (e == hipSuccess) e = launch_tiling(a.points, a.n, tw, st);
   if (e != hipSuccess) return hip_error(e, "tiling kernels");

@@ -143,6 +143,7 @@ constexpr int kConstsDoubles = 3 * FD_MAX_CANDIDATES + 6 * FD_MAX_REFINE;
 
 hipError_t launch_fpmvo(const SceneDev& s, const SearchDev& q, const FpmvoDev& f, int dtype,
                         int patch, hipStream_t st);
+// fb_count NULL: the fallback counters are left alone.
 hipError_t launch_setup(const float* pts, int64_t n, TileWork w, uint32_t* fb_count,
                         const ConstsDev& c, int n_candidates, double step0, double lstep0,
                         const float* cams, int V, double* cam64, hipStream_t st);

@@ -51,8 +51,8 @@ __device__ __forceinline__ void block_box(int (&v)[6]) {
 }
 
 // All that a call starts with, in one launch (five before, 2 to 4 us each):
-// the cell counts and the fallback counters cleared, the search constants,
-// the camera table, and every workgroup's part of the points' bounding box
+// the cell counts and (unless NULL) the fallback counters cleared, the search
+// constants, the camera table, and every workgroup's part of the points' bounding box
 // (boxes[6 b ..]; the next kernel folds the parts, so that none of them
 // needs a value to start from).
 constexpr int kSetupBlocks = 256;
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(256) void k_setup(const float* __restrict__ pts, in
     }
   }
   for (int k = first; k < kCells; k += kStride) counts[k] = 0u;
-  if (first < 2) fb_count[first] = 0u;
+  if (fb_count && first < 2) fb_count[first] = 0u;
   // from the last thread down: the first workgroups may have more points
   const int last = kStride - 1 - first;
   for (int k = last; k < n_constants(n_candidates); k += kStride)

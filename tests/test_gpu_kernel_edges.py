@@ -263,3 +263,26 @@ def test_patch_normalisation_ranges(patch, scale):
     # both costs are rounded to binary32
     tol = 2.0 ** -24 * (1.0 + c0.double().abs() + (1.0 + c1.double().abs()) * 2.0 ** -scale)
     assert ((s0 - s1).abs() <= tol)[ok].all()
+
+
+@pytest.mark.parametrize("mode", ["plain", "fpmvo", "batched"])
+def test_fallback_count_outlives_other_modes(mode):
+    """The fallback counters are those of the last learned call on a context:
+    calls in the other modes leave them as they are."""
+    nat = _native()
+    sc = scenegen.make_scene("tiny", 2)
+    n = sc.n_points
+    maps = (_t(sc.cams), _t(sc.theta), _t(sc.conf))
+    kw = dict(depth_maps=_t(sc.depth), patch=3, n_candidates=32, refine_iters=3, top_k=3)
+    ctx = nat.Context(max_points=2 * n, max_views=2 * len(sc.cams), max_scenes=2)
+    learned = dict(mode=nat.FD_MODE_LEARNED, proposal=nat.FD_PROPOSAL_NAN, fallback_cost=float("inf"), ctx=ctx)
+    nat.fuse_directions(_t(sc.points), *maps, **learned, **kw)
+    split = ctx.fallback_split()
+    assert ctx.fallback_count() == sum(split) == n
+    if mode == "batched":
+        import test_gpu_batched as B
+        nat.fuse_batched([B._dev_scene(sc), B._dev_scene(sc)], ctx, **{k: v for k, v in kw.items() if k != "depth_maps"})
+    else:
+        other = dict(plain=nat.FD_MODE_PLAIN, fpmvo=nat.FD_MODE_FPMVO)[mode]
+        nat.fuse_directions(_t(sc.points), *maps, mode=other, ctx=ctx, **kw)
+    assert ctx.fallback_count() == n and ctx.fallback_split() == split

@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
     }
     for (int off = first_xor; off < 64; off <<= 1) s += __shfl_xor(s, off, 64);
     conf = sqrtf(s);
-    near = !(fb - f2 >= mg);
+    near = !(fb >= 0.0f && fb - f2 >= mg);  // also where every response is a NaN
   };
   // The waiting pixels fix[first .. first + count), 16 per wave, summed over
   // all taps in order from the frame itself.

@@ -286,3 +286,28 @@ def test_fallback_count_outlives_other_modes(mode):
         other = dict(plain=nat.FD_MODE_PLAIN, fpmvo=nat.FD_MODE_FPMVO)[mode]
         nat.fuse_directions(_t(sc.points), *maps, mode=other, ctx=ctx, **kw)
     assert ctx.fallback_count() == n and ctx.fallback_split() == split
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("radius,n_orient", [(1, 32), (3, 16), (7, 8), (8, 32), (11, 16), (12, 32)])
+def test_non_finite_pixels_on_a_black_background(bad, radius, n_orient):
+    """A non-finite pixel reaches the pixels whose window holds it and no
+    other, also where everything around it is 0 (a window of zeros has no
+    response and no confidence)."""
+    import test_gpu_gabor as G
+    h, w = 150, 64
+    img = np.zeros((h, w), np.float32)
+    img[4:7, 5] = 1.0
+    kw = dict(n_orient=n_orient, radius=radius)
+    t0, c0 = G._gpu(img[None], **kw)
+    for y, x in ((70, 30), (63, 16), (64, 47), (140, 60)):
+        f = img.copy()
+        f[y, x] = bad
+        t1, c1 = G._gpu(f[None], **kw)
+        inside = np.zeros((h, w), bool)
+        inside[max(0, y - radius):y + radius + 1, max(0, x - radius):x + radius + 1] = True
+        assert np.isnan(c1[0][inside]).all()
+        assert np.array_equal(t1[0][~inside], t0[0][~inside])
+        # a rescaled tile may take the same response from the other sum
+        assert np.allclose(c1[0][~inside], c0[0][~inside], rtol=0.0, atol=2e-5)
+        assert not c1[0][~inside][c0[0][~inside] == 0.0].any()

@@ -154,7 +154,7 @@ extern "C" void fd_context_destroy(fd_context* c) {
                   c->fb_count, c->key,
                   c->perm, c->views, c->kcount, c->fb_list, c->prop, c->feats,
                   c->scene_tab, c->tile_tab, c->tile_queue, c->batch_key, c->batch_perm,
-                  c->gabor_bank, c->gabor_raw, c->gabor_max, c->vol_key, c->vol_perm,
+                  c->gabor_bank, c->gabor_raw, c->gabor_max, c->gabor_list, c->vol_key, c->vol_perm,
                   c->vol_off, c->vol_list, c->link_counts,
                   c->link_cursor, c->link_sums, c->link_bucket, c->link_perm, c->link_key,
                   c->link_best, c->strand_len};

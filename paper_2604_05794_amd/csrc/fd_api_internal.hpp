@@ -65,8 +65,10 @@ struct fd_context {
   float gabor_margin[2] = {};  // of the bank (choice_margin)
   float* gabor_raw = nullptr;
   size_t cap_gabor_raw = 0;
-  uint32_t* gabor_max = nullptr;
+  uint32_t* gabor_max = nullptr;  // the list's cursor (two words), then the frame maxima
   size_t cap_gabor_max = 0;
+  uint32_t* gabor_list = nullptr;  // tiles by the sum they take
+  size_t cap_gabor_list = 0;
   // orientation volume: counting sort of the points by voxel
   uint32_t* vol_key = nullptr;   // voxel and rank per point
   size_t cap_vol_key = 0;

@@ -2,13 +2,16 @@
 // gfx950 (the Gabor-filter extraction the paper names at the start of Sec. 3.1;
 // its reading is documented with fd_orientation_maps in fusedir.h).
 //
-// k_gabor_mfma: the filter bank is a dense contraction over the taps, run on
-// the binary16 matrix cores with both factors split in two.  Persistent
-// workgroups of eight waves hold the bank in LDS and walk 16 x 64 pixel
-// tiles, each staged in LDS with its radius-R halo; the epilogue takes the
-// argmax orientation and the raw confidence, and the workgroup's largest raw
-// confidence goes to the frame maximum (an integer atomic on the bits of a
-// non-negative float).  k_gabor_norm divides by that maximum.
+// The filter bank is a dense contraction over the taps, run on the matrix
+// cores.  The choice of an orientation is defined by one sum, binary32 over
+// the taps in order.  Tiles of 16 x 64 pixels where that choice is clear take
+// the faster binary16 operations with both factors split in two
+// (k_gabor_split), the others the binary32 ones (k_gabor_f32); k_gabor_sort
+// looks at 16 pixels of each tile and says which.  Either stages a tile in LDS
+// with its radius-R halo and takes the argmax orientation and the raw
+// confidence, and a workgroup's largest raw confidence goes to the frame
+// maximum (an integer atomic on the bits of a non-negative float).
+// k_gabor_norm divides by that maximum.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -82,17 +85,373 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+constexpr int kRowsPerWave = 8;
+constexpr int kTileRows = 64;
+
+// What every kernel reads.  tid counts the 16 x 64 tiles, frame by frame; the
+// tiles of successive tile rows and frames are shifted against each other, so
+// that no workgroup that strides over them gets nothing but tiles of a frame's
+// edge.
+struct GaborDev {
+  const float* frames;
+  int W, H, R, NO;
+  const float* bank;  // [tap][orientation]
+  int n_tiles, tiles_x, tiles_y;
+  size_t plane;
+
+  __device__ __forceinline__ void place(int tid, int* f, int* x0, int* y0) const {
+    const int per_frame = tiles_x * tiles_y;
+    *f = tid / per_frame;
+    const int rem = tid - *f * per_frame, r = rem / tiles_x;
+    *y0 = (r + *f) % tiles_y * kTileRows;
+    *x0 = (rem - r * tiles_x + r + *f) % tiles_x * kTile;
+  }
+};
+struct GaborOut {
+  void* theta;
+  float* raw;
+  uint32_t* frame_max;
+};
+
+// d2tab[NO + k] = squared line distance of two bins k apart (|k| < NO), 64
+// entries by the workgroup's first 64 threads.
+__device__ __forceinline__ void fill_d2(float* d2tab, int NO) {
+  if (threadIdx.x < 64) {
+    const int k = abs((int)threadIdx.x - NO);
+    float v = 0.0f;
+    if (k < NO) {
+      const float dd = (float)min(k, NO - k) * (kPi / NO);
+      v = dd * dd;
+    }
+    d2tab[threadIdx.x] = v;
+  }
+}
+
+// The bank in binary32 for the 16 x 16 x 4 operation, zero-padded to whole
+// 4-tap steps and 16-orientation tiles and laid out
+// [tap / 4][orientation tile][tap % 4][16], so that a wave's A operand is 64
+// consecutive words.
+__host__ __device__ inline int padded_taps(int taps) { return (taps + 3) & ~3; }
+template <int NT>
+__device__ __forceinline__ void fill_bank(float* sbank, const GaborDev& d, int taps) {
+  constexpr int NJ = 16 * NT;
+  for (int e = threadIdx.x; e < padded_taps(taps) * NJ; e += blockDim.x) {
+    const int t = e / NJ, j = e - t * NJ;
+    const int dst = (t >> 2) * 4 * NJ + (j >> 4) * 64 + (t & 3) * 16 + (j & 15);
+    sbank[dst] = (t < taps && j < d.NO) ? d.bank[(size_t)t * d.NO + j] : 0.0f;
+  }
+}
+
+// The largest and the second largest response of one pixel, which 2 or 4 lanes
+// (first_xor 32 or 16) hold: a lane orientations p0 + step * (k / 4) + k % 4.
+// Responses past the last orientation become -1 (FULL: there are none).
+template <bool FULL, int K>
+__device__ __forceinline__ void top_two(float (&fv)[K], int p0, int step, int first_xor, int NO,
+                                        float& fb, float& f2) {
+  fb = f2 = -1.0f;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    if (!FULL && p0 + step * (k / 4) + k % 4 >= NO) fv[k] = -1.0f;
+    f2 = __builtin_amdgcn_fmed3f(fv[k], fb, f2);
+    fb = fmaxf(fb, fv[k]);
+  }
+  for (int off = first_xor; off < 64; off <<= 1) {
+    const float o1 = __shfl_xor(fb, off, 64), o2 = __shfl_xor(f2, off, 64);
+    f2 = fmaxf(fminf(fb, o1), fmaxf(f2, o2));
+    fb = fmaxf(fb, o1);
+  }
+}
+
+// The first orientation with the largest response fb, and the spread of the
+// responses around it.
+template <bool FULL, int K>
+__device__ __forceinline__ void choose(const float (&fv)[K], float fb, int p0, int step,
+                                       int first_xor, int NO, const float* d2tab, int& jb,
+                                       float& conf) {
+  jb = 1 << 30;
+#pragma unroll
+  for (int k = K - 1; k >= 0; --k) jb = fv[k] == fb ? p0 + step * (k / 4) + k % 4 : jb;
+  for (int off = first_xor; off < 64; off <<= 1) jb = min(jb, __shfl_xor(jb, off, 64));
+  jb = jb < NO ? jb : 0;  // (no response equals a NaN)
+  float s = 0.0f;
+  const float* d2 = d2tab + (NO + p0 - jb);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int o = step * (k / 4) + k % 4;
+    const float e = FULL || p0 + o < NO ? fv[k] - fb : 0.0f;
+    s = __builtin_fmaf(d2[o], e * e, s);
+  }
+  for (int off = first_xor; off < 64; off <<= 1) s += __shfl_xor(s, off, 64);
+  conf = sqrtf(s);
+}
+
+// ---- the sum in order --------------------------------------------------------
+// Binary32 fused multiply-adds over all taps, row by row, as the 16 x 16 x 4
+// operation evaluates them (v_mfma_f32_16x16x4_f32, 4 taps a step).  In its
+// result lane (g, c) = (lane / 16, lane % 16) holds orientations 16 nt + 4 g + r
+// (r < 4) of pixel c.
+
+// For 16 pixels a wave, lane (g, c) has pixel c's place (px, py) and frame img:
+// read from the frame itself.  tap(k, nt) gives the lane's bank value of taps k
+// .. k + 3, any finite number past the last tap.  lo, hi: the range of the
+// lane's taps (0 outside the frame).
+template <int NT, typename F>
+__device__ __forceinline__ void sum_in_order(const GaborDev& d, const F& tap, const float* img,
+                                             int px, int py, int g, f32x4 (&acc)[NT], float& lo,
+                                             float& hi) {
+  const int R = d.R, W = d.W, H = d.H, w2 = 2 * R + 1, taps = w2 * w2;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  lo = INFINITY;
+  hi = -INFINITY;
+  const int x0 = px - R + g, y0 = py - R;
+  const uint32_t at0 = (uint32_t)(y0 * W + x0);  // (a negative one is not used)
+  // uniform: no window of the wave leaves the frame
+  const bool inner = __all(px >= R && px + R < W && py >= R && py + R < H);
+  // wave-uniform place of a step's first tap in the window and its distance in
+  // the frame; a lane's tap is at most one row further
+  int dx = 0, dy = 0;
+  uint32_t off = 0;
+  constexpr int kAhead = 8;  // steps whose loads are in flight together
+  for (int k0 = 0; k0 < taps; k0 += 4 * kAhead) {
+    float v[kAhead], a[kAhead][NT];
+    bool in[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const bool wrap = g >= w2 - dx;
+      in[u] = k0 + 4 * u + g < taps;
+      if (!inner)
+        in[u] = in[u] && (unsigned)(x0 + dx - (wrap ? w2 : 0)) < (unsigned)W &&
+                (unsigned)(y0 + dy + (wrap ? 1 : 0)) < (unsigned)H;
+      v[u] = img[in[u] ? at0 + off + (wrap ? (uint32_t)(W - w2) : 0u) : 0u];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) a[u][nt] = tap(k0 + 4 * u, nt);
+      dx += 4;
+      off += 4;
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+        if (dx >= w2) {
+          dx -= w2;
+          ++dy;
+          off += (uint32_t)(W - w2);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const float vu = in[u] ? v[u] : 0.0f;
+      lo = fminf(lo, vu);
+      hi = fmaxf(hi, vu);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][nt], vu, acc[nt], 0, 0, 0);
+    }
+  }
+}
+
+// All pixels of the listed tiles (from the list's end), or of every tile.
+// Persistent workgroups of four waves keep the bank in LDS and walk half tiles
+// of 16 x 32, wave w owning rows 8w .. 8w + 7, so each bank read feeds 8 matrix
+// operations.  The tile rows are kTw
+// words apart for every radius: the 8 row reads of a step take immediate
+// offsets and pair up.  The matrix cores only reach their peak when little
+// else is issued beside them, so the per-step bookkeeping is kept small: the
+// position of the step's first tap is wave-uniform (scalar registers) and a
+// lane's tap is at most one row further.
+// FULL: n_orient fills the NT orientation tiles (no per-lane validity
+// tests).  Three waves per SIMD is what the LDS allows (three workgroups per
+// CU at radius 8); the register bound keeps the compiler to it.
+constexpr int kF32Rows = 4 * kRowsPerWave;   // rows of a half tile: four waves
+constexpr int kTw = kTile + 2 * kMaxRadius;  // LDS tile row stride for every radius
+
+template <typename TO, int NT, bool FULL>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_gabor_f32(
+    GaborDev d, const uint32_t* __restrict__ n_listed, const uint32_t* __restrict__ list,
+    GaborOut o) {
+  extern __shared__ float lds_f32[];
+  __shared__ float wmax[256 / 64];
+  const int n_half = 2 * (n_listed ? (int)*n_listed : d.n_tiles);
+  if ((int)blockIdx.x >= n_half) return;
+  constexpr int NJ = 16 * NT;
+  const int W = d.W, H = d.H, R = d.R, NO = d.NO;
+  const int w2 = 2 * R + 1, taps = w2 * w2, kpad = padded_taps(taps), tw = kTile + 2 * R;
+  const int th = kF32Rows + 2 * R;  // tile rows with the halo
+  float* sbank = lds_f32;           // kpad x NJ
+  float* tile = lds_f32 + kpad * NJ;  // th x kTw
+  fill_bank<NT>(sbank, d, taps);
+  float* d2tab = tile + kTw * th;  // 64
+  fill_d2(d2tab, NO);
+  const int lane = (int)(threadIdx.x & 63u), w = (int)(threadIdx.x >> 6);
+  const int g = lane >> 4, c16 = lane & 15;
+  for (int i = blockIdx.x; i < n_half; i += gridDim.x) {
+    int f, x0, y0;
+    d.place(list ? (int)list[d.n_tiles - 1 - (i >> 1)] : i >> 1, &f, &x0, &y0);
+    y0 += kF32Rows * (i & 1);
+    if (y0 >= H) continue;  // uniform
+    const float* img = d.frames + d.plane * f;
+    __syncthreads();  // the bank is in place; the previous tile is no longer read
+    for (int e = threadIdx.x; e < kTw * th; e += blockDim.x) {
+      const int yy = e / kTw, xx = e - yy * kTw;
+      const int x = x0 + xx - R, y = y0 + yy - R;
+      tile[e] = (xx < tw && x >= 0 && x < W && y >= 0 && y < H) ? img[(size_t)y * W + x] : 0.0f;
+    }
+    __syncthreads();
+    f32x4 acc[kRowsPerWave][NT];
+#pragma unroll
+    for (int p = 0; p < kRowsPerWave; ++p)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[p][nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const float* base = tile + kRowsPerWave * w * kTw + c16 + g;
+    const float* bk = sbank + lane;
+    // wave-uniform (row offset, column) of tap k0; a lane's tap k0 + g is at
+    // most one row further (g < 4 <= w2 + 1 and the column stays < w2)
+    int s_off = 0, s_dx = 0;
+    for (int k0 = 0; k0 < kpad; k0 += 4) {
+      const int wrap = g >= w2 - s_dx ? kTw - w2 : 0;
+      const int off = k0 + g < taps ? s_off + wrap : -g;
+      float a[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) a[nt] = bk[k0 * NJ + 64 * nt];
+      const float* src = base + off;
+#pragma unroll
+      for (int p = 0; p < kRowsPerWave; ++p) {
+        const float v = src[p * kTw];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          acc[p][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[nt], v, acc[p][nt], 0, 0, 0);
+      }
+      // issue order: the step's LDS reads (the bank, then the row pairs),
+      // then its matrix operations
+      __builtin_amdgcn_sched_group_barrier(0x100, 5, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, kRowsPerWave * NT, 0);
+      s_dx += 4;
+      s_off += 4;
+      if (s_dx >= w2) { s_dx -= w2; s_off += kTw - w2; }
+      if (s_dx >= w2) { s_dx -= w2; s_off += kTw - w2; }
+    }
+    float m = 0.0f;
+#pragma unroll
+    for (int p = 0; p < kRowsPerWave; ++p) {
+      float fv[4 * NT], fb, wv;
+      int jb;
+#pragma unroll
+      for (int k = 0; k < 4 * NT; ++k)
+        fv[k] = FULL || 16 * (k / 4) + 4 * g + k % 4 < NO ? fabsf(acc[p][k / 4][k % 4]) : -1.0f;
+      fb = -1.0f;
+#pragma unroll
+      for (int k = 0; k < 4 * NT; ++k) fb = fmaxf(fb, fv[k]);
+      fb = fmaxf(fb, __shfl_xor(fb, 16, 64));
+      fb = fmaxf(fb, __shfl_xor(fb, 32, 64));
+      choose<FULL>(fv, fb, 4 * g, 16, 16, NO, d2tab, jb, wv);
+      const int x = x0 + c16, y = y0 + kRowsPerWave * w + p;
+      if (g == 0 && x < W && y < H) {
+        const size_t at = d.plane * f + (size_t)y * W + x;
+        store_map<TO>(o.theta, at, (float)jb * (kPi / NO));
+        o.raw[at] = wv;
+        m = fmaxf(m, wv);
+      }
+    }
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    if (lane == 0) wmax[w] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      float bm = wmax[0];
+      for (int k = 1; k < (int)(blockDim.x >> 6); ++k) bm = fmaxf(bm, wmax[k]);
+      atomicMax(&o.frame_max[f], __float_as_uint(bm));  // bm >= 0: bits order as values
+    }
+  }
+}
+
+// Per bank, in units of 2^-24: the rounding bounds of both sums for a window
+// whose pixels lie within `half` of `mid`, per unit of mid and half.
+struct GaborMargin {
+  float mid, half;
+};
+
+// ---- which sum a tile takes --------------------------------------------------
+// A pixel of a split tile whose two best responses are within the rounding of
+// the sums is summed again in order, one by one.  That costs about twice what
+// the pixel costs in k_gabor_f32, and the split sum half of it, so a tile many
+// of whose pixels would wait is better off there.  A wave sums 8 pixels of two
+// tiles in order, or 16 of one where the binary32 sum has half the operations
+// (NT = 1: it pays from half the share on); a tile of which two or more would
+// wait takes that sum.  What a tile takes depends on its own pixels only.
+constexpr int kSortWaves = 16, kSortMost = 8;  // tiles a wave, at most
+
+template <int NT, bool FULL>
+__global__ __launch_bounds__(64 * kSortWaves) void k_gabor_sort(GaborDev d, GaborMargin margin,
+                                                                int per,
+                                                                unsigned long long* cursor,
+                                                                uint32_t* __restrict__ list) {
+  extern __shared__ float lds_sort[];
+  __shared__ uint32_t bits[kSortWaves];
+  __shared__ uint64_t base;
+  constexpr int NJ = 16 * NT;
+  const int taps = (2 * d.R + 1) * (2 * d.R + 1), last = padded_taps(taps) - 4;
+  fill_bank<NT>(lds_sort, d, taps);
+  __syncthreads();
+  const int lane = (int)(threadIdx.x & 63u), g = lane >> 4, c16 = lane & 15;
+  const int second = NT == 2 ? c16 >> 3 : 0;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int first = (int)blockIdx.x * (kSortWaves * per), t0 = first + w * per;
+  const auto tap = [&](int k, int nt) { return lds_sort[min(k, last) * NJ + 64 * nt + lane]; };
+  uint32_t f32s = 0;  // bit k: tile t0 + k takes the binary32 sum
+  for (int k = 0; k < per && t0 + k < d.n_tiles; k += NT) {
+    int f, x0, y0, f1, x1, y1;
+    const bool two = NT == 2 && t0 + k + 1 < d.n_tiles;
+    d.place(t0 + k, &f, &x0, &y0);
+    d.place(t0 + k + two, &f1, &x1, &y1);
+    // four or eight pixels of each of two rows
+    const int row = c16 >> (NT == 2 ? 2 : 3) & 1;
+    const int col = NT == 2 ? 4 * (c16 & 3) + 2 * row + 1 : 2 * (c16 & 7) + row;
+    const int px = (second ? x1 : x0) + col, py = (second ? y1 : y0) + 15 + 33 * row;
+    const bool on = px < d.W && py < d.H;
+    f32x4 acc[NT];
+    float lo, hi, fb, f2, fv[4 * NT];
+    sum_in_order<NT>(d, tap, d.frames + d.plane * (size_t)(second ? f1 : f), px, py, g, acc, lo, hi);
+    for (int off = 16; off < 64; off <<= 1) {
+      lo = fminf(lo, __shfl_xor(lo, off, 64));
+      hi = fmaxf(hi, __shfl_xor(hi, off, 64));
+    }
+#pragma unroll
+    for (int j = 0; j < 4 * NT; ++j) fv[j] = fabsf(acc[j / 4][j % 4]);
+    top_two<FULL>(fv, 4 * g, 16, 16, d.NO, fb, f2);
+    const float mg = margin.mid * fabsf(0.5f * (hi + lo)) + margin.half * (0.5f * (hi - lo));
+    const uint64_t near = __ballot(on && !(fb >= 0.0f && fb - f2 >= mg));
+    if (__popcll(near & (NT == 2 ? 0xffull : 0xffffull)) >= 2) f32s |= 1u << k;
+    if (two && __popcll(near & 0xff00ull) >= 2) f32s |= 2u << k;
+  }
+  if (lane == 0) bits[w] = f32s;
+  __syncthreads();
+  // places in the list: split tiles from its start, the others from its end
+  const int n_here = min(max(d.n_tiles - first, 0), kSortWaves * per);
+  int n_f32 = 0, before = 0;
+  for (int k = 0; k < kSortWaves; ++k) {
+    n_f32 += __popc(bits[k]);
+    before += k < w ? __popc(bits[k]) : 0;
+  }
+  if (threadIdx.x == 0)
+    base = atomicAdd(cursor, (unsigned long long)n_f32 << 32 | (unsigned)(n_here - n_f32));
+  __syncthreads();
+  if (lane < per && t0 + lane < d.n_tiles) {
+    before += __popc(f32s & ((1u << lane) - 1u));
+    const int at = f32s >> lane & 1u
+                       ? d.n_tiles - 1 - ((int)(base >> 32) + before)
+                       : (int)(uint32_t)base + w * per + lane - before;
+    list[at] = (uint32_t)(t0 + lane);
+  }
+}
+
+// ---- the split sum -----------------------------------------------------------
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
-constexpr int kRowsPerWave = 8;
-constexpr int kTileRows = kWaves * kRowsPerWave;  // 64
-constexpr float kBankScale = 16384.0f;            // 2^14: |g| <= 2 stays below 2^15
+static_assert(kTileRows == kWaves * kRowsPerWave, "a wave's rows");
+constexpr float kBankScale = 16384.0f;  // 2^14: |g| <= 2 stays below 2^15
 
 // The taps of the (2R + 1)^2 window in groups of 8, two groups per matrix
 // operation: 8 columns of a row (columns 8c .. 8c + 7, rows 0 .. 2R and one
 // of padding, so that an operation takes two rows of one c), then the columns
-// that are left over.  A leftover of 1 or 3 columns takes groups of 8 rows of
-// one column where that is fewer groups than another (padded) c.
+// that are left over: in groups of 8 rows of one column where that is fewer
+// groups than another (padded) c takes.
 struct Taps {
   int w;        // window edge
   int cols;     // column groups c
@@ -149,14 +508,10 @@ struct GaborLds {
 // (v_mfma_f32_32x32x16_f16, accumulated in float).  Both factors are split
 // into a high and a low binary16 half (22 bits: v = h + l + r, |r| <= 2^-22
 // |v|; the tile scaled by a power of two so that its largest pixel is near
-// 2^14, the bank by 2^14), and three products h l + l h + h h stand for one:
-// 16 times the rate of the binary32 matrix operation, a third of it used.
-// The operation rounds its sum twice per 16 taps (each half of its taps, as
-// measured), the binary32 one once per tap, so the responses are nearer to
-// the exact ones than a binary32 sum in order.
+// 2^14, the bank by 2^14), and three products h l + l h + h h stand for one.
 //
 // Persistent workgroups of eight waves keep the split bank in LDS and walk
-// pixel tiles 16 wide and 64 high, wave w owning rows 8w .. 8w + 7 as four
+// the listed tiles, wave w owning rows 8w .. 8w + 7 as four
 // groups of 32 pixels (two rows).  A step takes two tap rows, so what group q
 // reads at one step group q - 1 reads at the next: the image operands stay in
 // registers and move down by one group, and only the last group's is loaded
@@ -166,50 +521,30 @@ struct GaborLds {
 // then across the two halves; the squared bin distances come from a small
 // LDS table.
 //
-// The choice of the orientation.  Where two responses nearly agree the
-// rounding of the sum decides, so the choice is defined by one sum: binary32
-// fused multiply-adds over all taps in order (which the 16x16x4 binary32
-// matrix operation evaluates).  A pixel whose best response leads by less
-// than the two sums can differ (their rounding bounds: choice_margin) is
-// summed again that way; its confidence is then taken from that sum.  Those
-// pixels, a hundredth of a frame or two, wait in LDS until there are 16 for
-// each wave.  In a constant, non-zero region every response is rounding and
-// every pixel's the same: one of a wave's 128 pixels waits and stands for
-// all (kFixAll).  Where most of a wave's pixels wait (smooth regions without
-// any noise) the wave sums its rows at once (dense).
-// Which sum a pixel's confidence comes from depends on its tile alone, so a
-// frame's maps do not depend on the other frames of a call.
-// Bound by the matrix operations (half of their issue slots; the clock drops
-// to 1.8 GHz under them) and the epilogue's 630 vector instructions a tile
-// and wave.  64 frames of 1024 x 1024, radius 8, 32 orientations, on the maps
-// of rendered hair: 10.4 -> 4.41 ms (binary32 operations only before); 16
-// frames of noise 2.82 -> 1.23 ms, of a constant 2.61 -> 1.84 ms, of a linear
-// ramp without noise (every response is rounding: the worst case) 2.65 -> 4.42
-// ms.
+// A pixel whose best response leads by less than the two sums can differ
+// (their rounding bounds: choice_margin) is summed again in order; its
+// confidence is then taken from that sum.  Those pixels wait in LDS until
+// there are 16 for each wave.  Which sum a pixel's confidence comes from
+// depends on its tile alone, so a frame's maps do not depend on the other
+// frames of a call.
 // FULL: 32 orientations (no validity tests).
 constexpr int kFixRound = 16 * kWaves;
 constexpr int kFixCap = kFixRound + kTile * kTileRows;  // a round less one, plus a tile's
-constexpr int kDense = 48;  // more waiting pixels of a wave's 128: all summed at once
-constexpr int kFixAll = 1 << 30;  // a pixel index stays below 2^30
 
-// Per bank, in units of 2^-24: the rounding bounds of both sums for a window
-// whose pixels lie within `half` of `mid`, per unit of mid and half.
-struct GaborMargin {
-  float mid, half;
-};
-
-template <typename TO, int RS, bool FULL>
-__global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
-    const float* __restrict__ frames, int W, int H, int R, int NO, const float* __restrict__ bank,
-    GaborMargin margin, Taps taps8, GaborLds L, int n_tiles, int tiles_x, int tiles_per_frame,
-    void* __restrict__ theta_out, float* __restrict__ raw, uint32_t* __restrict__ frame_max) {
+template <typename TO, int RS, int NT, bool FULL>
+__global__ __launch_bounds__(kThreads, RS == 32 ? 4 : 2) void k_gabor_split(
+    GaborDev d, GaborMargin margin, Taps taps8, GaborLds L, const uint32_t* __restrict__ n_listed,
+    const uint32_t* __restrict__ list, GaborOut o) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
   __shared__ float wred[kWaves];
   __shared__ int wlost[kWaves];  // the wave staged a non-zero pixel as 0
   __shared__ int2 fix[kFixCap];  // (frame, pixel) to be summed again
   __shared__ int n_fix;
+  const int n_tiles = (int)*n_listed;
+  if ((int)blockIdx.x >= n_tiles) return;
+  const int W = d.W, H = d.H, R = d.R, NO = d.NO;
   constexpr int kLoads = (kTileRows + 32) * RS / kThreads + 1;
-  const int w2 = 2 * R + 1, taps = w2 * w2, tw = kTile + 2 * R;
+  const int w2 = 2 * R + 1, tw = kTile + 2 * R;
   float* d2tab = (float*)(lds + L.d2);
   const int lane = (int)(threadIdx.x & 63u);
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -222,192 +557,44 @@ __global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
     for (int i = 0; i < 8; ++i) {
       int dy, dx;
       const bool on = taps8.tap(2 * st + (l >> 5), i, &dy, &dx) && m < NO;
-      const float v = on ? bank[(size_t)(dy * w2 + dx) * NO + m] * kBankScale : 0.0f;
+      const float v = on ? d.bank[(size_t)(dy * w2 + dx) * NO + m] * kBankScale : 0.0f;
       hi[i] = (_Float16)v;
       lo[i] = (_Float16)(v - (float)hi[i]);
     }
     *(f16x8*)(lds + L.bank + (st * 2 * 64 + l) * 4) = hi;
     *(f16x8*)(lds + L.bank + ((st * 2 + 1) * 64 + l) * 4) = lo;
   }
-  // d2tab[NO + k] = squared line distance of two bins k apart (|k| < NO)
-  if (threadIdx.x < 64) {
-    const int k = abs((int)threadIdx.x - NO);
-    float v = 0.0f;
-    if (k < NO) {
-      const float dd = (float)min(k, NO - k) * (kPi / NO);
-      v = dd * dd;
-    }
-    d2tab[threadIdx.x] = v;
-  }
+  fill_d2(d2tab, NO);
   if (threadIdx.x == 0) n_fix = 0;
-  const size_t plane = (size_t)W * H;
 
-  // Orientation and raw confidence of one pixel whose responses 2 or 4 lanes
-  // hold, lane part `p0` the orientations p0 + step * (k / 4) + k % 4.
-  auto choose = [&](auto& fv, int p0, int step, int first_xor, float mg, int& jb, float& conf,
-                    bool& near) {
-    constexpr int K = sizeof(fv) / sizeof(float);
-    float fb = -1.0f, f2 = -1.0f;  // the largest and the second largest
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      if (!FULL && p0 + step * (k / 4) + k % 4 >= NO) fv[k] = -1.0f;
-      f2 = __builtin_amdgcn_fmed3f(fv[k], fb, f2);
-      fb = fmaxf(fb, fv[k]);
-    }
-    for (int off = first_xor; off < 64; off <<= 1) {
-      const float o1 = __shfl_xor(fb, off, 64), o2 = __shfl_xor(f2, off, 64);
-      f2 = fmaxf(fminf(fb, o1), fmaxf(f2, o2));
-      fb = fmaxf(fb, o1);
-    }
-    jb = 1 << 30;  // the first that equals the largest
-#pragma unroll
-    for (int k = K - 1; k >= 0; --k) jb = fv[k] == fb ? p0 + step * (k / 4) + k % 4 : jb;
-    for (int off = first_xor; off < 64; off <<= 1) jb = min(jb, __shfl_xor(jb, off, 64));
-    jb = jb < NO ? jb : 0;  // (no response equals a NaN)
-    float s = 0.0f;
-    const float* d2 = d2tab + (NO + p0 - jb);
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int o = step * (k / 4) + k % 4;
-      const float e = FULL || p0 + o < NO ? fv[k] - fb : 0.0f;
-      s = __builtin_fmaf(d2[o], e * e, s);
-    }
-    for (int off = first_xor; off < 64; off <<= 1) s += __shfl_xor(s, off, 64);
-    conf = sqrtf(s);
-    near = !(fb >= 0.0f && fb - f2 >= mg);  // also where every response is a NaN
-  };
-  // The waiting pixels fix[first .. first + count), 16 per wave, summed over
-  // all taps in order from the frame itself.
+  // The waiting pixels fix[first .. first + count), 16 per wave.
   auto fix_round = [&](int first, int count) {
     if (16 * w >= count) return;  // wave-uniform
     const bool on = 16 * w + c16 < count;
-    int2 q = fix[first + (on ? 16 * w + c16 : 0)];
-    const bool all = q.y & kFixAll;
-    q.y &= kFixAll - 1;
-    const float* img = frames + plane * (size_t)q.x;
-    const int py = q.y / W, px = q.y - py * W;
-    f32x4 acc[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
-    int y = py - R, x = px - R + g;
-    const int right = px + R;
-    if (x > right) {  // w2 = 3
-      x -= w2;
-      ++y;
-    }
+    const int2 q = fix[first + (on ? 16 * w + c16 : 0)];
+    f32x4 acc[NT];
+    float lo, hi, fb, f2, wv, fv[4 * NT];
+    int jb;
     // orientations and taps past the last read it; such responses are not
     // looked at and such taps multiply 0
-    const float* b0 = bank + (FULL ? c16 : min(c16, NO - 1));
-    const int b1 = FULL ? 16 : min(16 + c16, NO - 1) - min(c16, NO - 1);
-    constexpr int kAhead = 8;  // steps whose loads are in flight together
-    for (int k0 = 0; k0 < taps; k0 += 4 * kAhead) {
-      float v[kAhead], a[kAhead][2];
-      bool in[kAhead];
+    const float* b0 = d.bank + (FULL ? c16 : min(c16, NO - 1));
+    const auto tap = [&](int k, int nt) {
+      return b0[(uint32_t)(min(k + g, w2 * w2 - 1) * NO) + 16 * nt];
+    };
+    sum_in_order<NT>(d, tap, d.frames + d.plane * (size_t)q.x, q.y % W, q.y / W, g, acc, lo, hi);
 #pragma unroll
-      for (int u = 0; u < kAhead; ++u) {
-        const int t = k0 + 4 * u + g;
-        in[u] = t < taps && (unsigned)x < (unsigned)W && (unsigned)y < (unsigned)H;
-        v[u] = img[in[u] ? (uint32_t)(y * W + x) : 0u];
-        const float* bt = b0 + (uint32_t)(min(t, taps - 1) * NO);
-        a[u][0] = bt[0];
-        a[u][1] = bt[b1];
-        x += 4;
-        if (x > right) { x -= w2; ++y; }
-        if (x > right) { x -= w2; ++y; }
-      }
-#pragma unroll
-      for (int u = 0; u < kAhead; ++u) {
-        const float vu = in[u] ? v[u] : 0.0f;
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-          acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][nt], vu, acc[nt], 0, 0, 0);
-      }
-    }
-    int jb;
-    float wv;
-    float fv[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) fv[k] = fabsf(acc[k / 4][k % 4]);
-    bool near;
-    choose(fv, 4 * g, 16, 16, 0.0f, jb, wv, near);
-    const float th = (float)jb * (kPi / NO);
+    for (int k = 0; k < 4 * NT; ++k) fv[k] = fabsf(acc[k / 4][k % 4]);
+    top_two<FULL>(fv, 4 * g, 16, 16, NO, fb, f2);
+    choose<FULL>(fv, fb, 4 * g, 16, 16, NO, d2tab, jb, wv);
     if (g == 0 && on) {
-      const size_t i = plane * (size_t)q.x + q.y;
-      store_map<TO>(theta_out, i, th);
-      raw[i] = wv;
+      const size_t i = d.plane * (size_t)q.x + q.y;
+      store_map<TO>(o.theta, i, (float)jb * (kPi / NO));
+      o.raw[i] = wv;
       // few of these pixels raise their frame's maximum (a NaN none)
       const uint32_t top = __float_as_uint(fmaxf(wv, 0.0f));
-      if (top > __atomic_load_n(&frame_max[q.x], __ATOMIC_RELAXED)) atomicMax(&frame_max[q.x], top);
+      if (top > __atomic_load_n(&o.frame_max[q.x], __ATOMIC_RELAXED))
+        atomicMax(&o.frame_max[q.x], top);
     }
-    // a pixel that stands for its wave's: 64 lanes store them
-    for (uint64_t b = __ballot(all && on && g == 0); b; b &= b - 1) {
-      const int l = __ffsll((unsigned long long)b) - 1;
-      const size_t at = plane * (size_t)__shfl(q.x, l, 64);
-      const int x0 = __shfl(px, l, 64), y0 = __shfl(py, l, 64);
-      const float tl = __shfl(th, l, 64), wl = __shfl(wv, l, 64);
-      for (int dy = g; dy < kRowsPerWave; dy += 4)
-        if (x0 + c16 < W && y0 + dy < H) {
-          const size_t i = at + (size_t)(y0 + dy) * W + (x0 + c16);
-          store_map<TO>(theta_out, i, tl);
-          raw[i] = wl;
-        }
-    }
-  };
-  // The same sum for all 128 pixels of a wave (8 rows from (x0, y0)) whose
-  // window lies in the frame, one bank operand for its rows; returns the
-  // lane's largest confidence.
-  auto dense = [&](int f, int x0, int y0) {
-    const float* img = frames + plane * (size_t)f + (size_t)(y0 - R) * W + (x0 - R);
-    f32x4 acc[kRowsPerWave][2];
-#pragma unroll
-    for (int p = 0; p < kRowsPerWave; ++p) acc[p][0] = acc[p][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    const float* b0 = bank + (FULL ? c16 : min(c16, NO - 1));
-    const int b1 = FULL ? 16 : min(16 + c16, NO - 1) - min(c16, NO - 1);
-    const int px = x0 + c16;
-    int dx = g;
-    uint32_t at = (uint32_t)(c16 + g);
-    if (dx >= w2) {  // w2 = 3
-      dx -= w2;
-      at += (uint32_t)(W - w2);
-    }
-    for (int k0 = 0; k0 < taps; k0 += 4) {
-      const bool on = k0 + g < taps;  // past the last tap: pixel 0
-      const float* bt = b0 + (uint32_t)((on ? k0 + g : 0) * NO);
-      const float a0 = bt[0], a1 = bt[b1];
-      const uint32_t ot = on ? at : (uint32_t)c16;
-      float v[kRowsPerWave];
-#pragma unroll
-      for (int p = 0; p < kRowsPerWave; ++p) v[p] = (img + (size_t)p * W)[ot];
-#pragma unroll
-      for (int p = 0; p < kRowsPerWave; ++p) {
-        v[p] = on ? v[p] : 0.0f;
-        acc[p][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, v[p], acc[p][0], 0, 0, 0);
-        acc[p][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, v[p], acc[p][1], 0, 0, 0);
-      }
-      dx += 4;
-      at += 4;
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const bool wrap = dx >= w2;
-        dx -= wrap ? w2 : 0;
-        at += wrap ? (uint32_t)(W - w2) : 0u;
-      }
-    }
-    float m = 0.0f;
-#pragma unroll
-    for (int p = 0; p < kRowsPerWave; ++p) {
-      float fv[8], wv;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) fv[k] = fabsf(acc[p][k / 4][k % 4]);
-      int jb;
-      bool near;
-      choose(fv, 4 * g, 16, 16, 0.0f, jb, wv, near);
-      if (g == 0 && px < W && y0 + p < H) {
-        const size_t i = plane * (size_t)f + (size_t)(y0 + p) * W + px;
-        store_map<TO>(theta_out, i, (float)jb * (kPi / NO));
-        raw[i] = wv;
-        m = fmaxf(m, wv);
-      }
-    }
-    return m;
   };
 
   // A tile's pixels, kLoads a thread; the loads are unconditional (outside
@@ -415,7 +602,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
   uint32_t keep = 0;  // bit u: tv[u] is a pixel of the frame
   const int lx = (int)threadIdx.x % RS, ly = (int)threadIdx.x / RS;
   auto load_tile = [&](int f, int x0, int y0, float (&tv)[kLoads]) {
-    const float* img = frames + plane * (size_t)f;
+    const float* img = d.frames + d.plane * (size_t)f;
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
       const int e = (int)threadIdx.x + u * kThreads;
@@ -432,21 +619,10 @@ __global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
   };
   float tv[kLoads];
   int f = 0, x0 = 0, y0 = 0;  // of the tile in tv
-  auto place = [&](int tid) {
-    f = tid / tiles_per_frame;
-    const int rem = tid - f * tiles_per_frame, r = rem / tiles_x;
-    // a workgroup's tiles are shifted against each other, so that no workgroup
-    // gets nothing but tiles of a frame's edge (whose pixels often wait)
-    y0 = (r + f) % (tiles_per_frame / tiles_x) * kTileRows;
-    x0 = (rem - r * tiles_x + r + f) % tiles_x * kTile;
-  };
-  if ((int)blockIdx.x < n_tiles) {
-    place(blockIdx.x);
-    load_tile(f, x0, y0, tv);
-  }
-  for (int tid = blockIdx.x; tid < n_tiles; tid += gridDim.x) {
+  d.place((int)list[blockIdx.x], &f, &x0, &y0);
+  load_tile(f, x0, y0, tv);
+  for (int i = blockIdx.x; i < n_tiles; i += gridDim.x) {
     const int cf = f, cx0 = x0, cy0 = y0;  // this tile (f, x0, y0 go on to the next)
-    const float* img = frames + plane * (size_t)cf;
     float mx = 0.0f;
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
@@ -485,8 +661,8 @@ __global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
     if (lane == 0) wlost[w] = lost;
     __syncthreads();
     // the next tile's pixels, on their way during the products
-    if (tid + (int)gridDim.x < n_tiles) {
-      place(tid + gridDim.x);
+    if (i + (int)gridDim.x < n_tiles) {
+      d.place((int)list[i + (int)gridDim.x], &f, &x0, &y0);
       load_tile(f, x0, y0, tv);
     }
     // The range of the pixels that the wave's rows read, from the high
@@ -519,8 +695,6 @@ __global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
       if (any) mg = INFINITY;
     }
     float m = 0.0f;
-    const bool inner = cx0 >= R && cx0 + kTile + R <= W && cy0 + kRowsPerWave * w >= R &&
-                       cy0 + kRowsPerWave * (w + 1) + R <= H;
     f32x16 acc[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -591,62 +765,26 @@ __global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
           acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[q], acc[q], 0, 0, 0);
       }
     }
-    // per pixel: argmax |F_j| (first of equals), then the spread of the
-    // responses around it
-    int jbs[4];
-    float wvs[4];
-    uint32_t near_q = 0;  // this lane's pixel of group q waits (bit q)
-    int n_near = 0;       // pixels of the wave that wait
     const int prow = cy0 + kRowsPerWave * w + ((lane >> 4) & 1), pcol = cx0 + c16;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      float fv[16];
+      float fv[8 * NT], fb, f2, wv;
+      int jb;
 #pragma unroll
-      for (int k = 0; k < 16; ++k) fv[k] = fabsf(acc[q][k]);  // in scaled units
-      bool near;
-      choose(fv, 4 * hf, 8, 32, mg, jbs[q], wvs[q], near);
-      wvs[q] *= unscale;
-      near = near && lane < 32 && pcol < W && prow + 2 * q < H;
-      n_near += __popcll(__ballot(near));
-      near_q |= near ? 1u << q : 0u;
-    }
-    // one value all over the window of the wave's pixels: then no part of it
-    // is outside the frame, which reads as 0 (and 0 everywhere is no choice)
-    bool flat = n_near > 1 && lo == hi && lo != 0.0f;
-    if (flat) {  // uniform; the high halves agree: the pixels themselves?
-      const float* win = img + (size_t)(cy0 + kRowsPerWave * w - R) * W + (cx0 - R);
-      const float v0 = win[0];
-      bool same = true;
-      for (int r0 = 0; r0 < kRowsPerWave + 2 * R; r0 += 8) {
-        float v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {  // rows and columns past the window read its last
-          const int r = min(r0 + 2 * u + hf, kRowsPerWave + 2 * R - 1);
-          v[u] = win[(size_t)r * W + min(lane & 31, tw - 1)];
-          if (RS > 32) same &= win[(size_t)r * W + min(32 + (lane & 31), tw - 1)] == v0;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) same &= v[u] == v0;
-      }
-      flat = __ballot(same) == ~0ull;
-    }
-    if (flat) {
-      if (lane == 0)
-        fix[atomicAdd(&n_fix, 1)] =
-            make_int2(cf, ((cy0 + kRowsPerWave * w) * W + cx0) | kFixAll);
-    } else if (n_near > kDense && inner) {  // uniform
-      m = dense(cf, cx0, cy0 + kRowsPerWave * w);
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int y = prow + 2 * q;
-        if (near_q >> q & 1u) {
+      for (int k = 0; k < 8 * NT; ++k) fv[k] = fabsf(acc[q][k]);  // in scaled units
+      top_two<FULL>(fv, 4 * hf, 8, 32, NO, fb, f2);
+      choose<FULL>(fv, fb, 4 * hf, 8, 32, NO, d2tab, jb, wv);
+      wv *= unscale;
+      const bool near = !(fb >= 0.0f && fb - f2 >= mg);  // also where every response is a NaN
+      const int y = prow + 2 * q;
+      if (lane < 32 && pcol < W && y < H) {
+        if (near) {
           fix[atomicAdd(&n_fix, 1)] = make_int2(cf, y * W + pcol);
-        } else if (lane < 32 && pcol < W && y < H) {
-          const size_t i = plane * (size_t)cf + (size_t)y * W + pcol;
-          store_map<TO>(theta_out, i, (float)jbs[q] * (kPi / NO));
-          raw[i] = wvs[q];
-          m = fmaxf(m, wvs[q]);
+        } else {
+          const size_t at = d.plane * (size_t)cf + (size_t)y * W + pcol;
+          store_map<TO>(o.theta, at, (float)jb * (kPi / NO));
+          o.raw[at] = wv;
+          m = fmaxf(m, wv);
         }
       }
     }
@@ -658,7 +796,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_gabor_mfma(
     if (threadIdx.x == 0) {
       float bm = wred[0];
       for (int k = 1; k < kWaves; ++k) bm = fmaxf(bm, wred[k]);
-      atomicMax(&frame_max[cf], __float_as_uint(bm));  // bm >= 0: bits order as values
+      atomicMax(&o.frame_max[cf], __float_as_uint(bm));  // bm >= 0: bits order as values
     }
     if (waiting >= kFixRound) {  // uniform: whole rounds, from the end of the list
       for (; waiting >= kFixRound; waiting -= kFixRound)
@@ -747,27 +885,55 @@ GaborMargin choice_margin(const std::vector<float>& bank, int N, int R) {
   return GaborMargin{(float)(u * most_p), (float)(u * most_g)};
 }
 
-template <typename TO>
-hipError_t launch_gabor(const float* frames, int n, int W, int H, int R, int N, const float* bank,
-                        const float* margin, void* theta, float* raw, uint32_t* fmax,
-                        hipStream_t st) {
-  const int tiles_x = (W + kTile - 1) / kTile, tiles_y = (H + kTileRows - 1) / kTileRows;
-  const int64_t per_frame = (int64_t)tiles_x * tiles_y;
-  const int n_tiles = (int)(per_frame * n);  // n <= FD_MAX_VIEWS, n W H <= 2^34: below 2^30
-  const GaborLds L(R);
-  const size_t lds = 4 * (size_t)L.total;
-  const auto kern = R <= 8 ? (N == 32 ? k_gabor_mfma<TO, 32, true> : k_gabor_mfma<TO, 32, false>)
-                           : (N == 32 ? k_gabor_mfma<TO, 40, true> : k_gabor_mfma<TO, 40, false>);
-  hipError_t e = hipFuncSetAttribute((const void*)kern,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+// Split sums from this radius on.  Below it the taps are few and staging and
+// epilogue are most of a tile: 16 frames of 1024 x 1024 of rendered hair, 32
+// orientations, binary32 and split sums, us: 434 and 590 at radius 1, 584 and
+// 569 at 2, 690 and 583 at 3; 16 orientations 455 and 504, 432 and 518, 557 and
+// 528.  From 5 on: 1254 and 866 at 5, 2622 and 1310 at 8, 6409 and 2630 at 12;
+// 16 orientations 819 and 650, 1566 and 970, 3171 and 1900.
+constexpr int kSplitRadius = 5;
+bool split_sums(int R) { return R >= kSplitRadius; }
+
+template <typename TO, int NT, bool FULL>
+hipError_t launch_gabor(GaborDev d, const float* margin, uint32_t* cursor, uint32_t* list,
+                        const GaborOut& o, hipStream_t st) {
+  hipError_t e;
+  const bool split = split_sums(d.R);
+  const int taps = (2 * d.R + 1) * (2 * d.R + 1);
+  const size_t bank_lds = sizeof(float) * (size_t)padded_taps(taps) * 16 * NT;
+  if (split) {
+    const GaborMargin mg{margin[0], margin[1]};
+    // as many tiles a wave as leave two workgroups for a compute unit
+    int per = std::min(kSortMost, std::max(1, d.n_tiles / (512 * kSortWaves)));
+    per = (per + NT - 1) / NT * NT;
+    const int here = per * kSortWaves;
+    const auto sort = k_gabor_sort<NT, FULL>;
+    e = hipFuncSetAttribute((const void*)sort, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)bank_lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(sort, dim3((unsigned)((d.n_tiles + here - 1) / here)), dim3(64 * kSortWaves),
+                       bank_lds, st, d, mg, per, (unsigned long long*)cursor, list);
+    const GaborLds L(d.R);
+    const size_t lds = 4 * (size_t)L.total;
+    const auto kern = d.R <= 8 ? k_gabor_split<TO, 32, NT, FULL> : k_gabor_split<TO, 40, NT, FULL>;
+    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds);
+    if (e != hipSuccess) return e;
+    // persistent: each workgroup splits the bank once; two resident per CU
+    // where the LDS allows it
+    const int per_cu = 2 * (lds + 8 * kFixCap + 512) <= 160 * 1024 ? 2 : 1;
+    hipLaunchKernelGGL(kern, dim3((unsigned)std::min(d.n_tiles, 256 * per_cu)), dim3(kThreads), lds,
+                       st, d, mg, Taps(d.R), L, cursor, list, o);
+  }
+  const size_t lds = bank_lds + sizeof(float) * ((size_t)kTw * (kF32Rows + 2 * d.R) + 64);
+  e = hipFuncSetAttribute((const void*)k_gabor_f32<TO, NT, FULL>,
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  // persistent: each workgroup splits the bank once; two resident per CU
-  // where the LDS allows it
-  const int per_cu = 2 * (lds + 8 * kFixCap + 512) <= 160 * 1024 ? 2 : 1;
-  const int grid = std::min(n_tiles, 256 * per_cu);
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), lds, st, frames, W, H, R, N, bank,
-                     GaborMargin{margin[0], margin[1]}, Taps(R), L, n_tiles, tiles_x,
-                     (int)per_frame, theta, raw, fmax);
+  // persistent: each workgroup loads the bank once; several resident per CU
+  const int per_cu = (int)std::max<size_t>(1, (160 * 1024) / (lds + 1024));
+  hipLaunchKernelGGL((k_gabor_f32<TO, NT, FULL>),
+                     dim3((unsigned)std::min(2 * d.n_tiles, 256 * std::min(per_cu, 4))), dim3(256),
+                     lds, st, d, split ? cursor + 1 : nullptr, split ? list : nullptr, o);
   return hipGetLastError();
 }
 
@@ -850,19 +1016,30 @@ extern "C" int fd_orientation_maps(const float* frames, int32_t n_frames, int32_
   if ((r = ctx_buffer((void**)&c->gabor_raw, &c->cap_gabor_raw, total * sizeof(float),
                       "raw confidence")))
     return r;
-  if ((r = ctx_buffer((void**)&c->gabor_max, &c->cap_gabor_max, n_frames * sizeof(uint32_t),
-                      "frame maxima")))
+  // the maxima after the cursor of the tile list
+  if ((r = ctx_buffer((void**)&c->gabor_max, &c->cap_gabor_max,
+                      (2 + (size_t)n_frames) * sizeof(uint32_t), "frame maxima")))
     return r;
-  if ((e = launch_fill_u32(c->gabor_max, n_frames, 0u, st)) != hipSuccess)
+  uint32_t* const fmax = c->gabor_max + 2;
+  GaborDev d{frames, width, height, p->radius, p->n_orient, c->gabor_bank, 0, 0, 0, plane};
+  d.tiles_x = (width + kTile - 1) / kTile;
+  d.tiles_y = (height + kTileRows - 1) / kTileRows;
+  // n_frames <= FD_MAX_VIEWS, at most 2^34 pixels: below 2^30
+  d.n_tiles = d.tiles_x * d.tiles_y * n_frames;
+  if (split_sums(p->radius) &&
+      (r = ctx_buffer((void**)&c->gabor_list, &c->cap_gabor_list,
+                      (size_t)d.n_tiles * sizeof(uint32_t), "tile list")))
+    return r;
+  if ((e = launch_fill_u32(c->gabor_max, 2 + (int64_t)n_frames, 0u, st)) != hipSuccess)
     return hip_error(e, "frame maxima reset");
+  const GaborOut o{theta_out, c->gabor_raw, fmax};
   StageTimer tg(c, FD_STAGE_GABOR, st);
-  e = p->out_dtype == FD_F16
-          ? launch_gabor<__half>(frames, n_frames, width, height, p->radius, p->n_orient,
-                                 c->gabor_bank, c->gabor_margin, theta_out, c->gabor_raw, c->gabor_max,
-                                 st)
-          : launch_gabor<float>(frames, n_frames, width, height, p->radius, p->n_orient,
-                                c->gabor_bank, c->gabor_margin, theta_out, c->gabor_raw,
-                                c->gabor_max, st);
+#define FD_GABOR(TO)                                                                               \
+  (p->n_orient == 32   ? launch_gabor<TO, 2, true>(d, c->gabor_margin, c->gabor_max, c->gabor_list, o, st) \
+   : p->n_orient == 16 ? launch_gabor<TO, 1, true>(d, c->gabor_margin, c->gabor_max, c->gabor_list, o, st) \
+                       : launch_gabor<TO, 1, false>(d, c->gabor_margin, c->gabor_max, c->gabor_list, o, st))
+  e = p->out_dtype == FD_F16 ? FD_GABOR(__half) : FD_GABOR(float);
+#undef FD_GABOR
   if (e != hipSuccess) return hip_error(e, "orientation kernel");
   tg.stop();
   StageTimer tn(c, FD_STAGE_GABOR_NORM, st);
@@ -872,10 +1049,10 @@ extern "C" int fd_orientation_maps(const float* frames, int32_t n_frames, int32_
   const int64_t work = vec ? (int64_t)plane / 8 : (int64_t)plane;
   const dim3 ng((unsigned)std::min<int64_t>((work + 255) / 256, 1 << 20), (unsigned)n_frames);
   if (p->out_dtype == FD_F16)
-    hipLaunchKernelGGL(k_gabor_norm<__half>, ng, dim3(256), 0, st, c->gabor_raw, c->gabor_max,
+    hipLaunchKernelGGL(k_gabor_norm<__half>, ng, dim3(256), 0, st, c->gabor_raw, fmax,
                        (int64_t)plane, vec, conf_out);
   else
-    hipLaunchKernelGGL(k_gabor_norm<float>, ng, dim3(256), 0, st, c->gabor_raw, c->gabor_max,
+    hipLaunchKernelGGL(k_gabor_norm<float>, ng, dim3(256), 0, st, c->gabor_raw, fmax,
                        (int64_t)plane, vec, conf_out);
   if ((e = hipGetLastError()) != hipSuccess) return hip_error(e, "confidence kernel");
   tn.stop();

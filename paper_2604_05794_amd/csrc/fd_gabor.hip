@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/fusedir.h"
@@ -95,7 +96,7 @@ constexpr int kTileRows = 64;
 struct GaborDev {
   const float* frames;
   int W, H, R, NO;
-  const float* bank;  // [tap][orientation]
+  const float* bank;  // [tap][orientation], then each orientation's sum
   int n_tiles, tiles_x, tiles_y;
   size_t plane;
 
@@ -490,15 +491,15 @@ struct Taps {
 // either copy, and the same a tap row further) touch no bank twice.
 struct GaborLds {
   int RS, th, plane, bank, planes, d2, total;
-  __host__ __device__ explicit GaborLds(int R) {
+  __host__ __device__ GaborLds(int R, bool pair) {
     const Taps t(R);
     RS = R <= 8 ? 32 : 40;
     th = kTileRows + 8 * t.rows8;
     plane = ((th * RS / 2 + 63) & ~63) + 8;
     bank = 0;
-    planes = t.steps * 2 * 64 * 4;
+    planes = t.steps * (pair ? 1 : 2) * 64 * 4;
     d2 = planes + 4 * plane;
-    total = d2 + 64;
+    total = d2 + 64 + 32;
   }
 };
 
@@ -506,9 +507,21 @@ struct GaborLds {
 // F[orientation][pixel] = sum_tap G[orientation][tap] I[pixel + tap]: 32
 // orientations x 16 taps times 16 taps x 32 pixels per operation
 // (v_mfma_f32_32x32x16_f16, accumulated in float).  Both factors are split
-// into a high and a low binary16 half (22 bits: v = h + l + r, |r| <= 2^-22
-// |v|; the tile scaled by a power of two so that its largest pixel is near
-// 2^14, the bank by 2^14), and three products h l + l h + h h stand for one.
+// into a high and a low binary16 half (v = h + l + r, |r| <= 2^-23 |v| and
+// mostly 0; the tile scaled by a power of two so that its largest pixel is near
+// 2^14, the bank by 2^14), and the four products of the halves stand for one.
+// Those with a low half are summed first, over all taps, while the sum is
+// small; the high halves' come after, with two roundings per 16 taps (each half
+// of its taps, as measured) where the binary32 operation rounds once per tap.
+// A tile of one sign whose largest pixel is at most three times its smallest
+// is taken less its middle (nearer to each pixel than 0 is), and the middle's
+// response, from the exact sum of the rounded taps, is added at the end.
+// Errors of the confidences against binary64, rms, in-order binary32 sum and
+// this: rendered hair, radius 8, 32 orientations 1.8e-6 and 0.7e-6, radius 12
+// 2.1e-6 and 1.0e-6; relative to the confidence on 0.15 with noise of 0.02
+// 9.7e-7 and 4.8e-7 (16 orientations 9.6e-7 and 5.6e-7), on bare scalp between
+// hair at radius 5 5.0e-7 and 5.0e-7.  Below radius 5 such windows would be
+// worse off: 5.5e-7 and 6.5e-7 at 4, 4.9e-7 and 6.9e-7 at 3 (kSplitRadius).
 //
 // Persistent workgroups of eight waves keep the split bank in LDS and walk
 // the listed tiles, wave w owning rows 8w .. 8w + 7 as four
@@ -519,7 +532,9 @@ struct GaborLds {
 // holds orientations 8 q + 4 h + r (q, r < 4) of pixel n: the argmax (first
 // of equals) and the confidence sum run over those 16 values in the lane,
 // then across the two halves; the squared bin distances come from a small
-// LDS table.
+// LDS table.  With at most 16 orientations (PAIR) the operation's 32 rows are
+// the bank's high halves and its low ones, two products in one, and a lane's
+// values 8 apart belong to one orientation.
 //
 // A pixel whose best response leads by less than the two sums can differ
 // (their rounding bounds: choice_margin) is summed again in order; its
@@ -527,31 +542,50 @@ struct GaborLds {
 // there are 16 for each wave.  Which sum a pixel's confidence comes from
 // depends on its tile alone, so a frame's maps do not depend on the other
 // frames of a call.
+//
+// Four waves per SIMD (two workgroups per CU) hold the registers to 128, which
+// it just fits: a tile loaded ahead, and thread indexes kept through the
+// products, spilled 42 registers (1511 against 1364 us below; the start with
+// the second sum of whole tiles in the same kernel 56 to 71).  Radii above 8
+// with 32 orientations have one workgroup per CU and twice the registers.
+// 16 frames of 1024 x 1024 of rendered hair, all tiles in k_gabor_f32 and so
+// (with k_gabor_sort and what it leaves to k_gabor_f32), us: 32 orientations
+// 1253 and 768 at radius 5, 2625 and 1313 at 8, 6418 and 2858 at 12; 16
+// orientations 817 and 519, 1570 and 826, 3172 and 1653.
 // FULL: 32 orientations (no validity tests).
 constexpr int kFixRound = 16 * kWaves;
 constexpr int kFixCap = kFixRound + kTile * kTileRows;  // a round less one, plus a tile's
 
+// The thread index as a value that the compiler knows nothing of: what follows
+// from it is formed again where it is used, and not held in registers through
+// the products.
+__device__ __forceinline__ int fresh_thread() {
+  int t = (int)threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 template <typename TO, int RS, int NT, bool FULL>
-__global__ __launch_bounds__(kThreads, RS == 32 ? 4 : 2) void k_gabor_split(
+__global__ __launch_bounds__(kThreads, RS == 32 || NT == 1 ? 4 : 2) void k_gabor_split(
     GaborDev d, GaborMargin margin, Taps taps8, GaborLds L, const uint32_t* __restrict__ n_listed,
     const uint32_t* __restrict__ list, GaborOut o) {
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  __shared__ float wred[kWaves];
+  __shared__ float2 wred[kWaves];
   __shared__ int wlost[kWaves];  // the wave staged a non-zero pixel as 0
   __shared__ int2 fix[kFixCap];  // (frame, pixel) to be summed again
   __shared__ int n_fix;
   const int n_tiles = (int)*n_listed;
   if ((int)blockIdx.x >= n_tiles) return;
   const int W = d.W, H = d.H, R = d.R, NO = d.NO;
+  constexpr bool PAIR = NT == 1;
   constexpr int kLoads = (kTileRows + 32) * RS / kThreads + 1;
   const int w2 = 2 * R + 1, tw = kTile + 2 * R;
   float* d2tab = (float*)(lds + L.d2);
-  const int lane = (int)(threadIdx.x & 63u);
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int g = lane >> 4, c16 = lane & 15, hf = lane >> 5;
-  // the split bank, [step][high, low][lane] 8 taps of orientation lane % 32
+  // the split bank, [step][high, low][lane] 8 taps of orientation lane % 32;
+  // PAIR: [step][lane], the high halves of 16 orientations, then the low ones
   for (int e = threadIdx.x; e < taps8.steps * 64; e += kThreads) {
-    const int st = e >> 6, l = e & 63, m = l & 31;
+    const int st = e >> 6, l = e & 63, m = l & (PAIR ? 15 : 31);
     f16x8 hi, lo;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -561,15 +595,23 @@ __global__ __launch_bounds__(kThreads, RS == 32 ? 4 : 2) void k_gabor_split(
       hi[i] = (_Float16)v;
       lo[i] = (_Float16)(v - (float)hi[i]);
     }
-    *(f16x8*)(lds + L.bank + (st * 2 * 64 + l) * 4) = hi;
-    *(f16x8*)(lds + L.bank + ((st * 2 + 1) * 64 + l) * 4) = lo;
+    if constexpr (PAIR) {
+      *(f16x8*)(lds + L.bank + e * 4) = l & 16 ? lo : hi;
+    } else {
+      *(f16x8*)(lds + L.bank + (st * 2 * 64 + l) * 4) = hi;
+      *(f16x8*)(lds + L.bank + ((st * 2 + 1) * 64 + l) * 4) = lo;
+    }
   }
   fill_d2(d2tab, NO);
+  float* sums = d2tab + 64;  // of each orientation's taps
+  if (threadIdx.x < 32)
+    sums[threadIdx.x] = (int)threadIdx.x < NO ? d.bank[(size_t)(w2 * w2) * NO + threadIdx.x] : 0.0f;
   if (threadIdx.x == 0) n_fix = 0;
 
   // The waiting pixels fix[first .. first + count), 16 per wave.
   auto fix_round = [&](int first, int count) {
     if (16 * w >= count) return;  // wave-uniform
+    const int lane = fresh_thread() & 63, g = lane >> 4, c16 = lane & 15;
     const bool on = 16 * w + c16 < count;
     const int2 q = fix[first + (on ? 16 * w + c16 : 0)];
     f32x4 acc[NT];
@@ -599,42 +641,56 @@ __global__ __launch_bounds__(kThreads, RS == 32 ? 4 : 2) void k_gabor_split(
 
   // A tile's pixels, kLoads a thread; the loads are unconditional (outside
   // the frame at its first pixel, then dropped), so that they go out together.
-  uint32_t keep = 0;  // bit u: tv[u] is a pixel of the frame
-  const int lx = (int)threadIdx.x % RS, ly = (int)threadIdx.x / RS;
+  uint32_t keep = 0;   // bit u: tv[u] is a pixel of the frame
+  bool edge = false;  // the thread's part of the windows leaves the frame
   auto load_tile = [&](int f, int x0, int y0, float (&tv)[kLoads]) {
     const float* img = d.frames + d.plane * (size_t)f;
+    edge = false;
+    const int t = fresh_thread(), lx = t % RS, ly = t / RS;
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
-      const int e = (int)threadIdx.x + u * kThreads;
+      const int e = t + u * kThreads;
       const int xx = RS == 32 ? lx : e % RS, yy = RS == 32 ? ly + u * (kThreads / 32) : e / RS;
       const int x = x0 + xx - R, y = y0 + yy - R;
-      const bool in = xx < tw && yy < kTileRows + 2 * R && (unsigned)x < (unsigned)W &&
-                      (unsigned)y < (unsigned)H;
+      const bool read = xx < tw && yy < kTileRows + 2 * R;
+      const bool in = read && (unsigned)x < (unsigned)W && (unsigned)y < (unsigned)H;
       uint32_t at = in ? (uint32_t)(y * W + x) : 0u;
       asm volatile("" : "+v"(at));  // keeps the load out of a branch
       const float v = img[at];
       tv[u] = v;
       keep = (keep & ~(1u << u)) | (in ? 1u << u : 0u);
+      edge |= read && !in;
     }
   };
-  float tv[kLoads];
-  int f = 0, x0 = 0, y0 = 0;  // of the tile in tv
-  d.place((int)list[blockIdx.x], &f, &x0, &y0);
-  load_tile(f, x0, y0, tv);
   for (int i = blockIdx.x; i < n_tiles; i += gridDim.x) {
-    const int cf = f, cx0 = x0, cy0 = y0;  // this tile (f, x0, y0 go on to the next)
-    float mx = 0.0f;
+    int cf, cx0, cy0;
+    float tv[kLoads];
+    d.place((int)list[i], &cf, &cx0, &cy0);
+    load_tile(cf, cx0, cy0, tv);
+    const int t0 = fresh_thread(), lane = t0 & 63;
+    float tlo = edge ? 0.0f : INFINITY, thi = edge ? 0.0f : -INFINITY;
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
-      tv[u] = keep >> u & 1u ? tv[u] : 0.0f;
-      mx = fmaxf(mx, fabsf(tv[u]));
+      const bool in = keep >> u & 1u;
+      tlo = in ? fminf(tlo, tv[u]) : tlo;
+      thi = in ? fmaxf(thi, tv[u]) : thi;
     }
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    for (int off = 32; off > 0; off >>= 1) {
+      tlo = fminf(tlo, __shfl_xor(tlo, off, 64));
+      thi = fmaxf(thi, __shfl_xor(thi, off, 64));
+    }
     __syncthreads();  // the bank is in place; the previous tile is no longer read
-    if (lane == 0) wred[w] = mx;
+    if (lane == 0) wred[w] = make_float2(tlo, thi);
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kWaves; ++k) mx = fmaxf(mx, wred[k]);
+    for (int k = 0; k < kWaves; ++k) {
+      tlo = fminf(tlo, wred[k].x);
+      thi = fmaxf(thi, wred[k].y);
+    }
+    // a tile of one sign and low contrast: less its middle, which then is
+    // nearer to every pixel than 0 is
+    const float mid = thi - tlo <= 2.0f * fmaxf(tlo, -thi) ? 0.5f * tlo + 0.5f * thi : 0.0f;
+    const float mx = fmaxf(fabsf(thi - mid), fabsf(tlo - mid));
     // the power of two that takes mx to [2^13, 2^14) (within the normal range)
     const int ex = min(max((int)(__float_as_uint(mx) >> 23) - 127, -99), 127);
     const float scale = __uint_as_float((uint32_t)(13 - ex + 127) << 23);
@@ -642,12 +698,13 @@ __global__ __launch_bounds__(kThreads, RS == 32 ? 4 : 2) void k_gabor_split(
     bool lost = false;
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
-      const int e = (int)threadIdx.x + u * kThreads;
+      const int e = t0 + u * kThreads;
       if (e < L.th * RS) {
-        const float v = tv[u] * scale;
+        const float c = keep >> u & 1u ? tv[u] - mid : 0.0f;
+        const float v = c * scale;
         const _Float16 h = (_Float16)v;
         const _Float16 l = (_Float16)(v - (float)h);
-        lost |= tv[u] != 0.0f && h == (_Float16)0.0f;
+        lost |= c != 0.0f && h == (_Float16)0.0f;
         _Float16* pl = (_Float16*)(lds + L.planes);
         pl[e] = h;
         pl[4 * L.plane + e] = l;
@@ -660,11 +717,6 @@ __global__ __launch_bounds__(kThreads, RS == 32 ? 4 : 2) void k_gabor_split(
     lost = __ballot(lost) != 0;
     if (lane == 0) wlost[w] = lost;
     __syncthreads();
-    // the next tile's pixels, on their way during the products
-    if (i + (int)gridDim.x < n_tiles) {
-      d.place((int)list[i + (int)gridDim.x], &f, &x0, &y0);
-      load_tile(f, x0, y0, tv);
-    }
     // The range of the pixels that the wave's rows read, from the high
     // halves (which are within 2^-11 of them).
     f16x2 lo2 = {(_Float16)INFINITY, (_Float16)INFINITY}, hi2 = -lo2;
@@ -682,7 +734,8 @@ __global__ __launch_bounds__(kThreads, RS == 32 ? 4 : 2) void k_gabor_split(
     lo = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(lo)));
     hi = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(hi)));
     // in units of the scaled responses
-    float mg = kBankScale * (margin.mid * fabsf(0.5f * (hi + lo)) +
+    const float level = mid * scale;
+    float mg = kBankScale * (margin.mid * fabsf(level + 0.5f * (hi + lo)) +
                                    margin.half * (0.5f * (hi - lo) +
                                                   0x1p-10f * fmaxf(fabsf(hi), fabsf(lo))));
     // A window far below the tile's largest pixel has lost bits to the split's
@@ -700,7 +753,11 @@ __global__ __launch_bounds__(kThreads, RS == 32 ? 4 : 2) void k_gabor_split(
     for (int q = 0; q < 4; ++q)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[q][r] = 0.0f;
-    {
+    // LOW: the products with a low half; else the high halves'.  PAIR: those
+    // of the low or the high halves of the pixels, with both of the bank.
+    auto products = [&](auto low) {
+      constexpr bool LOW = decltype(low)::value, BL = LOW, BH = !PAIR || !LOW;
+      const int lane = fresh_thread() & 63, c16 = lane & 15, hf = lane >> 5;
       const uint32_t* ab = lds + L.bank + lane * 4;
       // this lane's pixel of group 0, a tap row further in the upper half, in
       // the copy of its column's parity
@@ -709,10 +766,31 @@ __global__ __launch_bounds__(kThreads, RS == 32 ? 4 : 2) void k_gabor_split(
           lds + L.planes + (c16 & 1) * L.plane + ((row + hf) * RS + c16 - (c16 & 1)) / 2;
       const int n2 = (w2 + 1) / 2;  // steps of a column group
       f16x8 bh[4], bl[4];           // group q's operands at step s: slot (q + s) % 4
+      f16x8 ah, al;
+      auto load_a = [&]() {
+        ah = *(const f16x8*)ab;
+        if (LOW && !PAIR) al = *(const f16x8*)(ab + 256);
+        ab += PAIR ? 256 : 512;
+      };
       auto load_b = [&](int slot, const uint32_t* sh) {
         const uint32_t* sl = sh + 2 * L.plane;
-        bh[slot] = __builtin_bit_cast(f16x8, (u32x4){sh[0], sh[1], sh[2], sh[3]});
-        bl[slot] = __builtin_bit_cast(f16x8, (u32x4){sl[0], sl[1], sl[2], sl[3]});
+        if (BH) bh[slot] = __builtin_bit_cast(f16x8, (u32x4){sh[0], sh[1], sh[2], sh[3]});
+        if (BL) bl[slot] = __builtin_bit_cast(f16x8, (u32x4){sl[0], sl[1], sl[2], sl[3]});
+      };
+      auto step = [&](int u) {
+        auto mul = [&](const f16x8& x, const f16x8 (&y)[4]) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x, y[(q + u) & 3], acc[q], 0, 0, 0);
+        };
+        if constexpr (LOW && !PAIR) {
+          mul(al, bl);
+          mul(al, bh);
+        }
+        if constexpr (LOW)
+          mul(ah, bl);
+        else
+          mul(ah, bh);
       };
       for (int c = 0; c < taps8.cols; ++c) {
         const uint32_t* src = pb + 4 * c;
@@ -723,27 +801,15 @@ __global__ __launch_bounds__(kThreads, RS == 32 ? 4 : 2) void k_gabor_split(
           for (int u = 0; u < 4; ++u) {
             if (s0 + u >= n2) break;  // uniform
             load_b((u + 3) & 3, src + (s0 + u + 3) * RS);
-            const f16x8 ah = *(const f16x8*)ab;
-            const f16x8 al = *(const f16x8*)(ab + 256);
-            ab += 512;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[(q + u) & 3], acc[q], 0, 0, 0);
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[(q + u) & 3], acc[q], 0, 0, 0);
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[(q + u) & 3], acc[q], 0, 0, 0);
+            load_a();
+            step(u);
           }
         }
       }
       // groups of 8 rows of one column
       const _Float16* vb = (const _Float16*)(lds + L.planes) + row * RS + c16 + 8 * taps8.cols;
       for (int v0 = 0; v0 < taps8.left * taps8.rows8; v0 += 2) {
-        const f16x8 ah = *(const f16x8*)ab;
-        const f16x8 al = *(const f16x8*)(ab + 256);
-        ab += 512;
+        load_a();
         // a padding group past the last one reads the last one
         const int v = min(v0 + hf, taps8.left * taps8.rows8 - 1);
         const _Float16* src = vb + v / taps8.rows8 + 8 * (v % taps8.rows8) * RS;
@@ -751,33 +817,37 @@ __global__ __launch_bounds__(kThreads, RS == 32 ? 4 : 2) void k_gabor_split(
         for (int q = 0; q < 4; ++q)
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
-            bh[q][i] = src[(2 * q + i) * RS];
-            bl[q][i] = src[4 * L.plane + (2 * q + i) * RS];
+            if (BH) bh[q][i] = src[(2 * q + i) * RS];
+            if (BL) bl[q][i] = src[4 * L.plane + (2 * q + i) * RS];
           }
+        step(0);
+      }
+    };
+    products(std::true_type{});
+    products(std::false_type{});
+    const int el = fresh_thread() & 63, hf = el >> 5;
+    if (mid != 0.0f) {  // uniform: the middle's responses
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[q], acc[q], 0, 0, 0);
+      for (int k = 0; k < 8 * NT; ++k) {
+        const float part = level * kBankScale * sums[8 * (k / 4) + 4 * hf + k % 4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[q], acc[q], 0, 0, 0);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[q], acc[q], 0, 0, 0);
+        for (int q = 0; q < 4; ++q) acc[q][k] += part;
       }
     }
-    const int prow = cy0 + kRowsPerWave * w + ((lane >> 4) & 1), pcol = cx0 + c16;
+    const int prow = cy0 + kRowsPerWave * w + ((el >> 4) & 1), pcol = cx0 + (el & 15);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       float fv[8 * NT], fb, f2, wv;
       int jb;
 #pragma unroll
-      for (int k = 0; k < 8 * NT; ++k) fv[k] = fabsf(acc[q][k]);  // in scaled units
+      for (int k = 0; k < 8 * NT; ++k)  // in scaled units
+        fv[k] = fabsf(PAIR ? acc[q][k] + acc[q][k + 8] : acc[q][k]);
       top_two<FULL>(fv, 4 * hf, 8, 32, NO, fb, f2);
       choose<FULL>(fv, fb, 4 * hf, 8, 32, NO, d2tab, jb, wv);
       wv *= unscale;
       const bool near = !(fb >= 0.0f && fb - f2 >= mg);  // also where every response is a NaN
       const int y = prow + 2 * q;
-      if (lane < 32 && pcol < W && y < H) {
+      if (el < 32 && pcol < W && y < H) {
         if (near) {
           fix[atomicAdd(&n_fix, 1)] = make_int2(cf, y * W + pcol);
         } else {
@@ -790,12 +860,12 @@ __global__ __launch_bounds__(kThreads, RS == 32 ? 4 : 2) void k_gabor_split(
     }
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
     __syncthreads();  // wred and the waiting pixels
-    if (lane == 0) wred[w] = m;
+    if (el == 0) wred[w].x = m;
     int waiting = n_fix;
     __syncthreads();
     if (threadIdx.x == 0) {
-      float bm = wred[0];
-      for (int k = 1; k < kWaves; ++k) bm = fmaxf(bm, wred[k]);
+      float bm = wred[0].x;
+      for (int k = 1; k < kWaves; ++k) bm = fmaxf(bm, wred[k].x);
       atomicMax(&o.frame_max[cf], __float_as_uint(bm));  // bm >= 0: bits order as values
     }
     if (waiting >= kFixRound) {  // uniform: whole rounds, from the end of the list
@@ -814,7 +884,8 @@ uint64_t fnv1(uint64_t h, const void* p, size_t n) {
   return h;
 }
 
-// The bank in binary64 from its definition, rounded to binary32, tap-major.
+// The bank in binary64 from its definition, rounded to binary32, tap-major;
+// then the sum of each orientation's rounded taps.
 std::vector<float> make_bank(const fd_gabor_params* p) {
   const int N = p->n_orient, R = p->radius, w = 2 * R + 1;
   std::vector<double> g((size_t)N * w * w);
@@ -833,9 +904,13 @@ std::vector<float> make_bank(const fd_gabor_params* p) {
     mean /= (double)(w * w);
     for (int k = 0; k < w * w; ++k) g[(size_t)i * w * w + k] -= mean;
   }
-  std::vector<float> out((size_t)N * w * w);
-  for (int i = 0; i < N; ++i)
-    for (int k = 0; k < w * w; ++k) out[(size_t)k * N + i] = (float)g[(size_t)i * w * w + k];
+  std::vector<float> out((size_t)N * (w * w + 1));
+  for (int i = 0; i < N; ++i) {
+    double sum = 0.0;
+    for (int k = 0; k < w * w; ++k)
+      sum += out[(size_t)k * N + i] = (float)g[(size_t)i * w * w + k];
+    out[(size_t)(w * w) * N + i] = (float)sum;
+  }
   return out;
 }
 
@@ -844,12 +919,15 @@ std::vector<float> make_bank(const fd_gabor_params* p) {
 // A rounding is at most 2^-24 of the running sum, which is bounded by
 // |mid| |sum of the taps so far| + half (sum of their magnitudes so far).
 // Sum in order: one rounding per tap (the bound is taken at the start of a
-// 4-tap step, the step's own magnitudes on top).  Split sum: three matrix
-// operations per 16 taps, each rounding twice and cutting off as much again
-// where it aligns its products; the parts that the splits drop are within 3
-// 2^-22 of the magnitudes (and, for pixels or taps far below the largest,
-// 2^-36 of the largest, which is within 2^14 of the window's: else the pixel is
-// summed again without a look at the margin).  First order, one percent on top for the rest.
+// 4-tap step, the step's own magnitudes on top).
+// Split sum: the products with a low half first, whose sum stays below 2^-10 of
+// the magnitudes and takes three roundings and cuts of that for each of the
+// others', then the high halves', two roundings per 16 taps and as much cut off
+// again where the operation aligns its products.  What the splits do not hold
+// is within 2^-23 of either factor (and, for pixels or taps far below the
+// largest, 2^-36 of the largest, which is within 2^14 of the window's: else the
+// pixel is summed again without a look at the margin).  First order, one percent
+// on top for the rest.
 GaborMargin choice_margin(const std::vector<float>& bank, int N, int R) {
   const Taps tp(R);
   const int w = tp.w, taps = w * w;
@@ -867,8 +945,8 @@ GaborMargin choice_margin(const std::vector<float>& bank, int N, int R) {
     const double all = G;
     P = G = 0.0;
     for (int st = 0; st < tp.steps; ++st) {
-      sp += 3 * 4.0 * std::fabs(P);
-      sg += 3 * 4.0 * G;
+      sp += 4.0 * std::fabs(P);
+      sg += 4.0 * G;
       for (int q = 2 * st; q < 2 * st + 2; ++q)
         for (int i = 0; i < 8; ++i) {
           int dy, dx;
@@ -877,7 +955,9 @@ GaborMargin choice_margin(const std::vector<float>& bank, int N, int R) {
           G += std::fabs((double)bank[(size_t)(dy * w + dx) * N + j]);
         }
     }
-    const double rest = all * (4 + 3 * 4 + 3 * 4 + 4) + taps;
+    // each sum's own steps, the splits, the middle's subtraction, the low
+    // halves' roundings
+    const double rest = all * (4 + 4 + 4 + 1 + 12.0 * tp.steps / 1024.0 + 4) + taps;
     most_p = std::max(most_p, sp + rest);
     most_g = std::max(most_g, sg + rest);
   }
@@ -885,12 +965,10 @@ GaborMargin choice_margin(const std::vector<float>& bank, int N, int R) {
   return GaborMargin{(float)(u * most_p), (float)(u * most_g)};
 }
 
-// Split sums from this radius on.  Below it the taps are few and staging and
-// epilogue are most of a tile: 16 frames of 1024 x 1024 of rendered hair, 32
-// orientations, binary32 and split sums, us: 434 and 590 at radius 1, 584 and
-// 569 at 2, 690 and 583 at 3; 16 orientations 455 and 504, 432 and 518, 557 and
-// 528.  From 5 on: 1254 and 866 at 5, 2622 and 1310 at 8, 6409 and 2630 at 12;
-// 16 orientations 819 and 650, 1566 and 970, 3171 and 1900.
+// Split sums from this radius on: below it a sum in order over so few taps is
+// nearer to the exact one on low-contrast windows (figures with k_gabor_split),
+// and there is less to gain: 16 frames of rendered hair, 32 orientations, 716
+// and 524 us at radius 3, 456 and 472 at 1.
 constexpr int kSplitRadius = 5;
 bool split_sums(int R) { return R >= kSplitRadius; }
 
@@ -913,7 +991,7 @@ hipError_t launch_gabor(GaborDev d, const float* margin, uint32_t* cursor, uint3
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(sort, dim3((unsigned)((d.n_tiles + here - 1) / here)), dim3(64 * kSortWaves),
                        bank_lds, st, d, mg, per, (unsigned long long*)cursor, list);
-    const GaborLds L(d.R);
+    const GaborLds L(d.R, NT == 1);
     const size_t lds = 4 * (size_t)L.total;
     const auto kern = d.R <= 8 ? k_gabor_split<TO, 32, NT, FULL> : k_gabor_split<TO, 40, NT, FULL>;
     e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -303,8 +303,9 @@ void fd_gabor_params_init(fd_gabor_params* params);
  * fd_fuse_directions reads.  0 <= n_frames <= FD_MAX_VIEWS,
  * 1 <= W, H <= 32768, at most 2^34 pixels; otherwise FD_E_INVAL and nothing
  * is launched.  The bank (rebuilt when its parameters change, after
- * synchronising the stream), the raw confidences (4 B per pixel) and the
- * frame maxima live in the context's workspace, grown on demand.
+ * synchronising the stream), the raw confidences (4 B per pixel), the frame
+ * maxima and for large frames a list of tiles (4 B per 16 x 64 pixels) live in
+ * the context's workspace, grown on demand.
  * Asynchronous on params->stream. */
 int fd_orientation_maps(const float* frames, int32_t n_frames, int32_t width, int32_t height,
                         const fd_gabor_params* params, void* theta_out, void* conf_out);

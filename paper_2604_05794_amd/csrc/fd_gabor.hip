@@ -89,6 +89,10 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kRowsPerWave = 8;
 constexpr int kTileRows = 64;
 
+constexpr int kRound = 32;        // taps of a round of sum_in_order
+constexpr int kBankPad = kRound;  // a last round's taps past the window are 0
+__host__ __device__ inline int round_taps(int taps) { return (taps + kRound - 1) / kRound * kRound; }
+
 // What every kernel reads.  tid counts the 16 x 64 tiles, frame by frame; the
 // tiles of successive tile rows and frames are shifted against each other, so
 // that no workgroup that strides over them gets nothing but tiles of a frame's
@@ -96,7 +100,8 @@ constexpr int kTileRows = 64;
 struct GaborDev {
   const float* frames;
   int W, H, R, NO;
-  const float* bank;  // [tap][orientation], then each orientation's sum
+  const float* bank;  // [tap][orientation], kBankPad taps of 0, each orientation's sum
+  const uint32_t* split;  // its halves as k_gabor_split reads them (k_gabor_halves)
   int n_tiles, tiles_x, tiles_y;
   size_t plane;
 
@@ -128,19 +133,36 @@ __device__ __forceinline__ void fill_d2(float* d2tab, int NO) {
   }
 }
 
-// The bank in binary32 for the 16 x 16 x 4 operation, zero-padded to whole
-// 4-tap steps and 16-orientation tiles and laid out
+// The bank in binary32 for the 16 x 16 x 4 operation, n taps (a multiple of 4,
+// past the window's 0), zero-padded to 16-orientation tiles and laid out
 // [tap / 4][orientation tile][tap % 4][16], so that a wave's A operand is 64
 // consecutive words.
 __host__ __device__ inline int padded_taps(int taps) { return (taps + 3) & ~3; }
 template <int NT>
-__device__ __forceinline__ void fill_bank(float* sbank, const GaborDev& d, int taps) {
+__device__ __forceinline__ void fill_bank(float* sbank, const GaborDev& d, int n) {
   constexpr int NJ = 16 * NT;
-  for (int e = threadIdx.x; e < padded_taps(taps) * NJ; e += blockDim.x) {
-    const int t = e / NJ, j = e - t * NJ;
-    const int dst = (t >> 2) * 4 * NJ + (j >> 4) * 64 + (t & 3) * 16 + (j & 15);
-    sbank[dst] = (t < taps && j < d.NO) ? d.bank[(size_t)t * d.NO + j] : 0.0f;
+  constexpr int kAhead = 4;  // loads in flight together
+  for (int e0 = threadIdx.x; e0 < n * NJ; e0 += kAhead * (int)blockDim.x) {
+    float v[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int e = min(e0 + u * (int)blockDim.x, n * NJ - 1), t = e / NJ, j = e - t * NJ;
+      v[u] = d.bank[t * d.NO + min(j, d.NO - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int e = e0 + u * (int)blockDim.x, t = e / NJ, j = e - t * NJ;
+      const int dst = (t >> 2) * 4 * NJ + (j >> 4) * 64 + (t & 3) * 16 + (j & 15);
+      if (e < n * NJ) sbank[dst] = j < d.NO ? v[u] : 0.0f;
+    }
   }
+}
+
+// The distance in the frame of each tap from the window's first, whole rounds
+// (past the window: the first).
+__device__ __forceinline__ void fill_offsets(uint32_t* offs, int W, int w2) {
+  for (int t = threadIdx.x; t < round_taps(w2 * w2); t += blockDim.x)
+    offs[t] = t < w2 * w2 ? (uint32_t)(t / w2 * W + t % w2) : 0u;
 }
 
 // The largest and the second largest response of one pixel, which 2 or 4 lanes
@@ -194,57 +216,51 @@ __device__ __forceinline__ void choose(const float (&fv)[K], float fb, int p0, i
 
 // For 16 pixels a wave, lane (g, c) has pixel c's place (px, py) and frame img:
 // read from the frame itself.  tap(k, nt) gives the lane's bank value of taps k
-// .. k + 3, any finite number past the last tap.  lo, hi: the range of the
-// lane's taps (0 outside the frame).
+// .. k + 3, 0 past the last one.  lo, hi: the range of the lane's taps (0 outside
+// the frame).  Bound by the vector instructions around a step's one load: with
+// the window's place kept and checked step by step a wave took 9 us alone.
 template <int NT, typename F>
-__device__ __forceinline__ void sum_in_order(const GaborDev& d, const F& tap, const float* img,
-                                             int px, int py, int g, f32x4 (&acc)[NT], float& lo,
-                                             float& hi) {
+__device__ __forceinline__ void sum_in_order(const GaborDev& d, const F& tap, const uint32_t* offs,
+                                             const float* img, int px, int py, int g,
+                                             f32x4 (&acc)[NT], float& lo, float& hi) {
   const int R = d.R, W = d.W, H = d.H, w2 = 2 * R + 1, taps = w2 * w2;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   lo = INFINITY;
   hi = -INFINITY;
-  const int x0 = px - R + g, y0 = py - R;
-  const uint32_t at0 = (uint32_t)(y0 * W + x0);  // (a negative one is not used)
+  const int x0 = px - R, y0 = py - R;
+  const float* win = img + ((int64_t)y0 * W + x0);  // (not read outside the frame)
   // uniform: no window of the wave leaves the frame
-  const bool inner = __all(px >= R && px + R < W && py >= R && py + R < H);
-  // wave-uniform place of a step's first tap in the window and its distance in
-  // the frame; a lane's tap is at most one row further
-  int dx = 0, dy = 0;
-  uint32_t off = 0;
-  constexpr int kAhead = 8;  // steps whose loads are in flight together
-  for (int k0 = 0; k0 < taps; k0 += 4 * kAhead) {
+  const bool inner = __all(x0 >= 0 && px + R < W && y0 >= 0 && py + R < H);
+  offs += g;
+  constexpr int kAhead = kRound / 4;  // steps whose loads are in flight together
+  for (int k0 = 0; k0 < taps; k0 += kRound) {
     float v[kAhead], a[kAhead][NT];
-    bool in[kAhead];
+    if (inner) {
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const bool wrap = g >= w2 - dx;
-      in[u] = k0 + 4 * u + g < taps;
-      if (!inner)
-        in[u] = in[u] && (unsigned)(x0 + dx - (wrap ? w2 : 0)) < (unsigned)W &&
-                (unsigned)(y0 + dy + (wrap ? 1 : 0)) < (unsigned)H;
-      v[u] = img[in[u] ? at0 + off + (wrap ? (uint32_t)(W - w2) : 0u) : 0u];
+      for (int u = 0; u < kAhead; ++u) v[u] = win[offs[k0 + 4 * u]];
+    } else {
+      bool in[kAhead];
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) a[u][nt] = tap(k0 + 4 * u, nt);
-      dx += 4;
-      off += 4;
+      for (int u = 0; u < kAhead; ++u) {
+        const int t = k0 + 4 * u + g, dy = t / w2, dx = t - dy * w2;
+        in[u] = t < taps && (unsigned)(x0 + dx) < (unsigned)W && (unsigned)(y0 + dy) < (unsigned)H;
+        v[u] = *(in[u] ? win + offs[k0 + 4 * u] : img);
+      }
 #pragma unroll
-      for (int r = 0; r < 2; ++r)
-        if (dx >= w2) {
-          dx -= w2;
-          ++dy;
-          off += (uint32_t)(W - w2);
-        }
+      for (int u = 0; u < kAhead; ++u) v[u] = in[u] ? v[u] : 0.0f;
     }
 #pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) a[u][nt] = tap(k0 + 4 * u, nt);
+#pragma unroll
     for (int u = 0; u < kAhead; ++u) {
-      const float vu = in[u] ? v[u] : 0.0f;
-      lo = fminf(lo, vu);
-      hi = fmaxf(hi, vu);
+      lo = fminf(lo, v[u]);
+      hi = fmaxf(hi, v[u]);
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
-        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][nt], vu, acc[nt], 0, 0, 0);
+        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][nt], v[u], acc[nt], 0, 0, 0);
     }
   }
 }
@@ -278,7 +294,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   const int th = kF32Rows + 2 * R;  // tile rows with the halo
   float* sbank = lds_f32;           // kpad x NJ
   float* tile = lds_f32 + kpad * NJ;  // th x kTw
-  fill_bank<NT>(sbank, d, taps);
+  fill_bank<NT>(sbank, d, kpad);
   float* d2tab = tile + kTw * th;  // 64
   fill_d2(d2tab, NO);
   const int lane = (int)(threadIdx.x & 63u), w = (int)(threadIdx.x >> 6);
@@ -387,14 +403,17 @@ __global__ __launch_bounds__(64 * kSortWaves) void k_gabor_sort(GaborDev d, Gabo
   __shared__ uint32_t bits[kSortWaves];
   __shared__ uint64_t base;
   constexpr int NJ = 16 * NT;
-  const int taps = (2 * d.R + 1) * (2 * d.R + 1), last = padded_taps(taps) - 4;
-  fill_bank<NT>(lds_sort, d, taps);
+  const int w2 = 2 * d.R + 1, n = round_taps(w2 * w2);
+  fill_bank<NT>(lds_sort, d, n);
+  uint32_t* const offs = (uint32_t*)(lds_sort + n * NJ);
+  fill_offsets(offs, d.W, w2);
   __syncthreads();
   const int lane = (int)(threadIdx.x & 63u), g = lane >> 4, c16 = lane & 15;
   const int second = NT == 2 ? c16 >> 3 : 0;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int first = (int)blockIdx.x * (kSortWaves * per), t0 = first + w * per;
-  const auto tap = [&](int k, int nt) { return lds_sort[min(k, last) * NJ + 64 * nt + lane]; };
+  const int waves = (int)(blockDim.x >> 6), first = (int)blockIdx.x * (waves * per);
+  const int t0 = first + w * per;
+  const auto tap = [&](int k, int nt) { return lds_sort[k * NJ + 64 * nt + lane]; };
   uint32_t f32s = 0;  // bit k: tile t0 + k takes the binary32 sum
   for (int k = 0; k < per && t0 + k < d.n_tiles; k += NT) {
     int f, x0, y0, f1, x1, y1;
@@ -408,7 +427,8 @@ __global__ __launch_bounds__(64 * kSortWaves) void k_gabor_sort(GaborDev d, Gabo
     const bool on = px < d.W && py < d.H;
     f32x4 acc[NT];
     float lo, hi, fb, f2, fv[4 * NT];
-    sum_in_order<NT>(d, tap, d.frames + d.plane * (size_t)(second ? f1 : f), px, py, g, acc, lo, hi);
+    sum_in_order<NT>(d, tap, offs, d.frames + d.plane * (size_t)(second ? f1 : f), px, py, g, acc, lo,
+                     hi);
     for (int off = 16; off < 64; off <<= 1) {
       lo = fminf(lo, __shfl_xor(lo, off, 64));
       hi = fmaxf(hi, __shfl_xor(hi, off, 64));
@@ -424,9 +444,9 @@ __global__ __launch_bounds__(64 * kSortWaves) void k_gabor_sort(GaborDev d, Gabo
   if (lane == 0) bits[w] = f32s;
   __syncthreads();
   // places in the list: split tiles from its start, the others from its end
-  const int n_here = min(max(d.n_tiles - first, 0), kSortWaves * per);
+  const int n_here = min(max(d.n_tiles - first, 0), waves * per);
   int n_f32 = 0, before = 0;
-  for (int k = 0; k < kSortWaves; ++k) {
+  for (int k = 0; k < waves; ++k) {
     n_f32 += __popc(bits[k]);
     before += k < w ? __popc(bits[k]) : 0;
   }
@@ -499,9 +519,34 @@ struct GaborLds {
     bank = 0;
     planes = t.steps * (pair ? 1 : 2) * 64 * 4;
     d2 = planes + 4 * plane;
-    total = d2 + 64 + 32;
+    total = d2 + 64 + 32 + round_taps(t.w * t.w);
   }
 };
+
+// The split bank, [step][high, low][lane] 8 taps of orientation lane % 32; pair:
+// [step][lane], the high halves of 16 orientations, then the low ones.  Once per
+// bank.
+__global__ __launch_bounds__(64) void k_gabor_halves(const float* __restrict__ bank, int NO,
+                                                     bool pair, Taps taps8,
+                                                     uint32_t* __restrict__ split) {
+  const int st = (int)blockIdx.x, l = (int)threadIdx.x, m = l & (pair ? 15 : 31);
+  f16x8 hi, lo;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    int dy, dx;
+    const bool on = taps8.tap(2 * st + (l >> 5), i, &dy, &dx) && m < NO;
+    const float v = on ? bank[(size_t)(dy * taps8.w + dx) * NO + m] * kBankScale : 0.0f;
+    hi[i] = (_Float16)v;
+    lo[i] = (_Float16)(v - (float)hi[i]);
+  }
+  f16x8* out = (f16x8*)split;
+  if (pair) {
+    out[st * 64 + l] = l & 16 ? lo : hi;
+  } else {
+    out[st * 2 * 64 + l] = hi;
+    out[(st * 2 + 1) * 64 + l] = lo;
+  }
+}
 
 // The filter bank as a matrix product on the matrix cores,
 // F[orientation][pixel] = sum_tap G[orientation][tap] I[pixel + tap]: 32
@@ -582,30 +627,15 @@ __global__ __launch_bounds__(kThreads, RS == 32 || NT == 1 ? 4 : 2) void k_gabor
   const int w2 = 2 * R + 1, tw = kTile + 2 * R;
   float* d2tab = (float*)(lds + L.d2);
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  // the split bank, [step][high, low][lane] 8 taps of orientation lane % 32;
-  // PAIR: [step][lane], the high halves of 16 orientations, then the low ones
-  for (int e = threadIdx.x; e < taps8.steps * 64; e += kThreads) {
-    const int st = e >> 6, l = e & 63, m = l & (PAIR ? 15 : 31);
-    f16x8 hi, lo;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      int dy, dx;
-      const bool on = taps8.tap(2 * st + (l >> 5), i, &dy, &dx) && m < NO;
-      const float v = on ? d.bank[(size_t)(dy * w2 + dx) * NO + m] * kBankScale : 0.0f;
-      hi[i] = (_Float16)v;
-      lo[i] = (_Float16)(v - (float)hi[i]);
-    }
-    if constexpr (PAIR) {
-      *(f16x8*)(lds + L.bank + e * 4) = l & 16 ? lo : hi;
-    } else {
-      *(f16x8*)(lds + L.bank + (st * 2 * 64 + l) * 4) = hi;
-      *(f16x8*)(lds + L.bank + ((st * 2 + 1) * 64 + l) * 4) = lo;
-    }
-  }
+  for (int e = threadIdx.x; e < (L.planes - L.bank) / 4; e += kThreads)
+    ((uint4*)(lds + L.bank))[e] = ((const uint4*)d.split)[e];
   fill_d2(d2tab, NO);
   float* sums = d2tab + 64;  // of each orientation's taps
   if (threadIdx.x < 32)
-    sums[threadIdx.x] = (int)threadIdx.x < NO ? d.bank[(size_t)(w2 * w2) * NO + threadIdx.x] : 0.0f;
+    sums[threadIdx.x] =
+        (int)threadIdx.x < NO ? d.bank[(size_t)(w2 * w2 + kBankPad) * NO + threadIdx.x] : 0.0f;
+  uint32_t* const offs = (uint32_t*)sums + 32;
+  fill_offsets(offs, W, w2);
   if (threadIdx.x == 0) n_fix = 0;
 
   // The waiting pixels fix[first .. first + count), 16 per wave.
@@ -617,13 +647,10 @@ __global__ __launch_bounds__(kThreads, RS == 32 || NT == 1 ? 4 : 2) void k_gabor
     f32x4 acc[NT];
     float lo, hi, fb, f2, wv, fv[4 * NT];
     int jb;
-    // orientations and taps past the last read it; such responses are not
-    // looked at and such taps multiply 0
-    const float* b0 = d.bank + (FULL ? c16 : min(c16, NO - 1));
-    const auto tap = [&](int k, int nt) {
-      return b0[(uint32_t)(min(k + g, w2 * w2 - 1) * NO) + 16 * nt];
-    };
-    sum_in_order<NT>(d, tap, d.frames + d.plane * (size_t)q.x, q.y % W, q.y / W, g, acc, lo, hi);
+    // orientations past the last read it; such responses are not looked at
+    const uint32_t b0 = (uint32_t)(g * NO + (FULL ? c16 : min(c16, NO - 1)));
+    const auto tap = [&](int k, int nt) { return (d.bank + (size_t)k * NO + 16 * nt)[b0]; };
+    sum_in_order<NT>(d, tap, offs, d.frames + d.plane * (size_t)q.x, q.y % W, q.y / W, g, acc, lo, hi);
 #pragma unroll
     for (int k = 0; k < 4 * NT; ++k) fv[k] = fabsf(acc[k / 4][k % 4]);
     top_two<FULL>(fv, 4 * g, 16, 16, NO, fb, f2);
@@ -884,8 +911,12 @@ uint64_t fnv1(uint64_t h, const void* p, size_t n) {
   return h;
 }
 
+// floats of the bank, and where its halves start (whole 16 bytes)
+size_t bank_size(int N, int w) { return (size_t)N * (w * w + kBankPad + 1); }
+size_t split_offset(size_t bank) { return (bank + 3) / 4 * 4; }
+
 // The bank in binary64 from its definition, rounded to binary32, tap-major;
-// then the sum of each orientation's rounded taps.
+// then taps of 0 and the sum of each orientation's rounded taps.
 std::vector<float> make_bank(const fd_gabor_params* p) {
   const int N = p->n_orient, R = p->radius, w = 2 * R + 1;
   std::vector<double> g((size_t)N * w * w);
@@ -904,12 +935,12 @@ std::vector<float> make_bank(const fd_gabor_params* p) {
     mean /= (double)(w * w);
     for (int k = 0; k < w * w; ++k) g[(size_t)i * w * w + k] -= mean;
   }
-  std::vector<float> out((size_t)N * (w * w + 1));
+  std::vector<float> out(bank_size(N, w));
   for (int i = 0; i < N; ++i) {
     double sum = 0.0;
     for (int k = 0; k < w * w; ++k)
       sum += out[(size_t)k * N + i] = (float)g[(size_t)i * w * w + k];
-    out[(size_t)(w * w) * N + i] = (float)sum;
+    out[(size_t)(w * w + kBankPad) * N + i] = (float)sum;
   }
   return out;
 }
@@ -965,32 +996,47 @@ GaborMargin choice_margin(const std::vector<float>& bank, int N, int R) {
   return GaborMargin{(float)(u * most_p), (float)(u * most_g)};
 }
 
-// Split sums from this radius on: below it a sum in order over so few taps is
+// Split sums from radius 5 on: below it a sum in order over so few taps is
 // nearer to the exact one on low-contrast windows (figures with k_gabor_split),
 // and there is less to gain: 16 frames of rendered hair, 32 orientations, 716
-// and 524 us at radius 3, 456 and 472 at 1.
+// and 524 us at radius 3, 456 and 472 at 1.  And for frames that are large
+// enough for one of them alone to take no longer, sorted first, than in the
+// binary32 kernel (a frame's maps do not depend on how many there are); noise,
+// binary32 and split, us, waited for after each call:
+//   32 orientations   radius 8                    radius 12
+//     64 tiles        57 and 78                   88 and 119
+//     256             79 and 83                   138 and 182
+//     1024            198 and 166                 442 and 297
+//   16 orientations   radius 8                    radius 11
+//     256             59 and 69                   78 and 125
+//     1024            127 and 98                  196 and 146
 constexpr int kSplitRadius = 5;
-bool split_sums(int R) { return R >= kSplitRadius; }
+bool split_sums(const GaborDev& d) {
+  return d.R >= kSplitRadius && d.tiles_x * d.tiles_y >= (d.NO > 16 ? 320 : 640);
+}
 
 template <typename TO, int NT, bool FULL>
 hipError_t launch_gabor(GaborDev d, const float* margin, uint32_t* cursor, uint32_t* list,
                         const GaborOut& o, hipStream_t st) {
   hipError_t e;
-  const bool split = split_sums(d.R);
+  const bool split = split_sums(d);
   const int taps = (2 * d.R + 1) * (2 * d.R + 1);
-  const size_t bank_lds = sizeof(float) * (size_t)padded_taps(taps) * 16 * NT;
   if (split) {
     const GaborMargin mg{margin[0], margin[1]};
-    // as many tiles a wave as leave two workgroups for a compute unit
+    // one wave per SIMD and a tile or a pair for each wave while that is all
+    // the work there is (256 tiles: 21 us, 38 with 16 waves), else 16 waves and
+    // as many tiles for each as leave two workgroups for a compute unit
+    const int waves = d.n_tiles <= 4 * 256 * NT ? 4 : kSortWaves;
     int per = std::min(kSortMost, std::max(1, d.n_tiles / (512 * kSortWaves)));
     per = (per + NT - 1) / NT * NT;
-    const int here = per * kSortWaves;
+    const int here = per * waves;
+    const size_t sort_lds = sizeof(float) * (size_t)round_taps(taps) * (16 * NT + 1);
     const auto sort = k_gabor_sort<NT, FULL>;
     e = hipFuncSetAttribute((const void*)sort, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)bank_lds);
+                            (int)sort_lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(sort, dim3((unsigned)((d.n_tiles + here - 1) / here)), dim3(64 * kSortWaves),
-                       bank_lds, st, d, mg, per, (unsigned long long*)cursor, list);
+    hipLaunchKernelGGL(sort, dim3((unsigned)((d.n_tiles + here - 1) / here)), dim3(64 * waves),
+                       sort_lds, st, d, mg, per, (unsigned long long*)cursor, list);
     const GaborLds L(d.R, NT == 1);
     const size_t lds = 4 * (size_t)L.total;
     const auto kern = d.R <= 8 ? k_gabor_split<TO, 32, NT, FULL> : k_gabor_split<TO, 40, NT, FULL>;
@@ -1003,7 +1049,8 @@ hipError_t launch_gabor(GaborDev d, const float* margin, uint32_t* cursor, uint3
     hipLaunchKernelGGL(kern, dim3((unsigned)std::min(d.n_tiles, 256 * per_cu)), dim3(kThreads), lds,
                        st, d, mg, Taps(d.R), L, cursor, list, o);
   }
-  const size_t lds = bank_lds + sizeof(float) * ((size_t)kTw * (kF32Rows + 2 * d.R) + 64);
+  const size_t lds = sizeof(float) * ((size_t)padded_taps(taps) * 16 * NT +
+                                      (size_t)kTw * (kF32Rows + 2 * d.R) + 64);
   e = hipFuncSetAttribute((const void*)k_gabor_f32<TO, NT, FULL>,
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -1077,12 +1124,20 @@ extern "C" int fd_orientation_maps(const float* frames, int32_t n_frames, int32_
     const std::vector<float> bank = make_bank(p);
     // a previous call on this stream may still read the old bank
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return hip_error(e, "filter bank");
-    if ((r = ctx_buffer((void**)&c->gabor_bank, &c->cap_gabor_bank, bank.size() * sizeof(float),
+    const GaborLds L(p->radius, p->n_orient <= 16);
+    if ((r = ctx_buffer((void**)&c->gabor_bank, &c->cap_gabor_bank,
+                        split_offset(bank.size()) * sizeof(float) + 4 * (size_t)(L.planes - L.bank),
                         "filter bank")))
       return r;
     e = hipMemcpy(c->gabor_bank, bank.data(), bank.size() * sizeof(float),
                   hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_error(e, "filter bank upload");
+    const Taps t(p->radius);
+    hipLaunchKernelGGL(k_gabor_halves, dim3((unsigned)t.steps), dim3(64), 0, st, c->gabor_bank,
+                       p->n_orient, p->n_orient <= 16, t,
+                       (uint32_t*)(c->gabor_bank + split_offset(bank.size())));
+    if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess)
+      return hip_error(e, "filter bank halves");
     const GaborMargin mg = choice_margin(bank, p->n_orient, p->radius);
     c->gabor_margin[0] = mg.mid;
     c->gabor_margin[1] = mg.half;
@@ -1099,12 +1154,15 @@ extern "C" int fd_orientation_maps(const float* frames, int32_t n_frames, int32_
                       (2 + (size_t)n_frames) * sizeof(uint32_t), "frame maxima")))
     return r;
   uint32_t* const fmax = c->gabor_max + 2;
-  GaborDev d{frames, width, height, p->radius, p->n_orient, c->gabor_bank, 0, 0, 0, plane};
+  const int w2 = 2 * p->radius + 1;
+  const uint32_t* const split =
+      (const uint32_t*)(c->gabor_bank + split_offset(bank_size(p->n_orient, w2)));
+  GaborDev d{frames, width, height, p->radius, p->n_orient, c->gabor_bank, split, 0, 0, 0, plane};
   d.tiles_x = (width + kTile - 1) / kTile;
   d.tiles_y = (height + kTileRows - 1) / kTileRows;
   // n_frames <= FD_MAX_VIEWS, at most 2^34 pixels: below 2^30
   d.n_tiles = d.tiles_x * d.tiles_y * n_frames;
-  if (split_sums(p->radius) &&
+  if (split_sums(d) &&
       (r = ctx_buffer((void**)&c->gabor_list, &c->cap_gabor_list,
                       (size_t)d.n_tiles * sizeof(uint32_t), "tile list")))
     return r;

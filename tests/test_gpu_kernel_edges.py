@@ -311,3 +311,127 @@ def test_non_finite_pixels_on_a_black_background(bad, radius, n_orient):
         # a rescaled tile may take the same response from the other sum
         assert np.allclose(c1[0][~inside], c0[0][~inside], rtol=0.0, atol=2e-5)
         assert not c1[0][~inside][c0[0][~inside] == 0.0].any()
+
+
+def _gabor_kinds(rng, h, w):
+    """Frames that take every way through the orientation kernels: noise, low
+    contrast (centred tiles; some of them in the binary32 kernel), a ramp and a
+    constant (binary32), black with noise, halves of two kinds side by side, one
+    pixel 2^40 times the others, 8 bits, negative values."""
+    noise = rng.uniform(0.0, 1.0, (h, w))
+    yy, xx = np.mgrid[0:h, 0:w]
+    ramp = (xx + 0.3 * yy) / (w + h)
+    lowc = 0.15 + 0.02 * rng.normal(size=(h, w))
+    f = dict(noise=255.0 * noise, lowc=lowc, flat=0.8 + 0.002 * rng.normal(size=(h, w)), ramp=ramp,
+             constant=np.full((h, w), 0.7), black=0.02 * rng.normal(size=(h, w)),
+             sides=np.where(xx < w // 2 + 5, ramp, np.where(yy < h // 3, noise, lowc)), tiny=2.0**-20 * noise,
+             bits8=np.round(255 * np.clip(0.5 + 0.3 * np.sin(0.9 * xx + 0.2 * yy) + 0.02 * rng.normal(size=(h, w)), 0, 1)) / 255,
+             negative=-0.4 - 0.1 * noise)
+    f["tiny"][h // 2, w // 2] = 2.0**20
+    return {k: v.astype(np.float32) for k, v in f.items()}
+
+
+@pytest.mark.parametrize("radius,n_orient", [(5, 32), (5, 16), (6, 8), (7, 16), (8, 32), (8, 16), (9, 32), (10, 8), (11, 32), (12, 32), (12, 16)])
+def test_large_frames_choose_as_small_ones(radius, n_orient):
+    """Frames of more than 640 tiles take the split sums (from radius 5 on), cut
+    up they do not: the orientations are those of the binary32 sum in order,
+    which the small frames' test pins, bit for bit wherever the window lies in
+    the piece or the frame ends with it, and the confidences those of the
+    oracle within its tests' bounds.  1.9 million pixels a kind, many times what
+    the persistent workgroups hold at once."""
+    import test_gpu_gabor as G
+    nat = _native()
+    rng = np.random.default_rng(100 * radius + n_orient)
+    h, w = 1237, 1541  # 20 x 97 tiles, neither edge on a tile's
+    kw = dict(n_orient=n_orient, radius=radius, out_dtype=torch.float32)
+    kinds = _gabor_kinds(rng, h, w)
+    frames = _t(np.stack(list(kinds.values())))
+    theta, conf = nat.orientation_maps(frames, **kw)
+    ph, pw = 252, 236  # 4 x 15 tiles
+    wrong = {}
+    for y0 in range(0, h, ph - 2 * radius):
+        for x0 in range(0, w, pw - 2 * radius):
+            y1, x1 = min(h, y0 + ph), min(w, x0 + pw)
+            ya, yb = y0 + (radius if y0 else 0), y1 - (radius if y1 < h else 0)
+            xa, xb = x0 + (radius if x0 else 0), x1 - (radius if x1 < w else 0)
+            if ya >= yb or xa >= xb:
+                continue
+            t, _ = nat.orientation_maps(frames[:, y0:y1, x0:x1].contiguous(), **kw)
+            off = (t[:, ya - y0:yb - y0, xa - x0:xb - x0] != theta[:, ya:yb, xa:xb]).flatten(1).sum(1)
+            for name, c in zip(kinds, off.tolist()):
+                wrong[name] = wrong.get(name, 0) + c
+    assert not any(wrong.values()), wrong
+    # one by one, the same bits
+    for k in (0, 1, 6):
+        t, c = nat.orientation_maps(frames[k:k + 1], **kw)
+        assert torch.equal(t[0], theta[k]) and torch.equal(c[0], conf[k])
+    # confidences against the oracle over a corner, where the frame's largest is put (bright noise)
+    bank = oracle.gabor_bank(**{k: v if k in kw else float(np.float32(v)) for k, v in G._bank_kw(dict(n_orient=n_orient, radius=radius)).items()})
+    n = 150
+    for name in ("lowc", "flat", "sides", "black"):
+        img = kinds[name].copy()
+        img[:40, :60] = rng.uniform(0.0, 2.0, (40, 60)).astype(np.float32)
+        t, c = nat.orientation_maps(_t(img[None]), **kw)
+        part = img[:n + radius, :n + radius]
+        t, c = t[0, :n, :n].cpu().numpy(), c[0, :n, :n].cpu().numpy()
+        to, co, wmax, F = oracle.gabor(part, bank, responses=True)
+        _, _, _, L1 = oracle.gabor(np.abs(part), np.abs(bank), responses=True)
+        scale = L1.max(axis=-1)[:n, :n]
+        co = co[:n, :n]
+        jo, jt = (np.rint(v * n_orient / np.pi).astype(int)[..., None] for v in (to[:n, :n], t))
+        same = (jo == jt)[..., 0]
+        near = np.take_along_axis(F[:n, :n], jo, -1) - np.take_along_axis(F[:n, :n], jt, -1)
+        assert (near[..., 0] <= 2 * G.REL * scale).all(), name
+        k = np.arange(n_orient)
+        dk = np.minimum(k, n_orient - k) * (np.pi / n_orient)
+        dw = 2 * G.REL * scale * np.sqrt(np.sum(dk * dk))
+        bound = dw / wmax + co * (dw.max() / wmax) + 1e-7
+        assert (np.abs(c - co) <= bound)[same].all(), name
+
+
+@pytest.mark.parametrize("n_orient,tiles", [(32, (16, 20)), (32, (16, 19)), (16, (16, 40)), (16, (16, 39)), (8, (1, 640)), (32, (320, 1))])
+def test_orientation_frames_at_the_split_size(n_orient, tiles):
+    """Frames of just the tiles from which the split sums are taken, and one
+    row of tiles less; a single row and a single column of tiles: orientations
+    of the pieces, and the same maps for a frame alone and among others."""
+    nat = _native()
+    rng = np.random.default_rng(n_orient + tiles[0])
+    h, w = 64 * tiles[0] - 3, 16 * tiles[1] - 1
+    f = _t(rng.uniform(0.0, 1.0, (3, h, w)).astype(np.float32))
+    kw = dict(n_orient=n_orient, radius=8, out_dtype=torch.float32)
+    theta, conf = nat.orientation_maps(f, **kw)
+    t1, c1 = nat.orientation_maps(f[1:2].contiguous(), **kw)
+    assert torch.equal(t1[0], theta[1]) and torch.equal(c1[0], conf[1])
+    for y0 in range(0, h, 100):
+        for x0 in range(0, w, 1000):
+            y1, x1 = min(h, y0 + 116), min(w, x0 + 1016)
+            t, _ = nat.orientation_maps(f[:, y0:y1, x0:x1].contiguous(), **kw)
+            ya, yb = y0 + (8 if y0 else 0), y1 - (8 if y1 < h else 0)
+            xa, xb = x0 + (8 if x0 else 0), x1 - (8 if x1 < w else 0)
+            assert torch.equal(t[:, ya - y0:yb - y0, xa - x0:xb - x0], theta[:, ya:yb, xa:xb])
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("radius,n_orient", [(5, 16), (8, 32), (11, 8), (12, 32)])
+def test_non_finite_pixels_in_large_frames(bad, radius, n_orient):
+    """As on a black background above, in frames that take the split sums: over
+    black, over noise and over low contrast."""
+    nat = _native()
+    rng = np.random.default_rng(radius)
+    h, w = 1030, 1100
+    kw = dict(n_orient=n_orient, radius=radius, out_dtype=torch.float32)
+    base = np.zeros((3, h, w), np.float32)
+    base[0, 4:60, 5:40] = 1.0
+    base[1] = rng.uniform(0.0, 1.0, (h, w))
+    base[2] = 0.15 + 0.02 * rng.normal(size=(h, w))
+    t0, c0 = nat.orientation_maps(_t(base), **kw)
+    f = base.copy()
+    inside = torch.zeros((h, w), dtype=torch.bool, device=DEV)
+    for y, x in ((70, 30), (511, 512), (640, 655), (1020, 1099), (300, 0)):
+        f[:, y, x] = bad
+        inside[max(0, y - radius):y + radius + 1, max(0, x - radius):x + radius + 1] = True
+    t1, c1 = nat.orientation_maps(_t(f), **kw)
+    assert torch.isnan(c1[:, inside]).all() and torch.isfinite(c1[:, ~inside]).all()
+    assert torch.equal(t1[:, ~inside], t0[:, ~inside])
+    black = ~inside & (c0[0] == 0.0)
+    assert not c1[0][black].any()

@@ -181,10 +181,10 @@ hipError_t launch_learned_refine(const SceneDev& s, const SearchDev& q, const Le
 }
 
 // ---- paper-literal candidates ---------------------------------------------------
-// Layers held in registers: 5 (the default of the method) or 16 (the most).
-// The five-layer form is held to two waves per SIMD.
+// Layers held in registers: 5 (the default of the method) or 8, both held to
+// two waves per SIMD, or 16.
 template <typename T, int P, int KT, int NS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NS <= 5 ? 2 : 1)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NS <= 8 ? 2 : 1)))
 void k_fpmvo(SceneDev s, SearchDev q, FpmvoDev f) {
   const Group gr = make_group<KT>(q.K);
   const int64_t wave = wave_tile(gridDim.x);
@@ -203,8 +203,10 @@ hipError_t launch_fpmvo(const SceneDev& s, const SearchDev& q, const FpmvoDev& f
 #define FD_FPMVO_NS(T, P, KT)                                                        \
   if (f.samples <= 5)                                                                \
     hipLaunchKernelGGL((k_fpmvo<T, P, KT, 5>), grid, block, 0, st, s, q, f);         \
+  else if (f.samples <= 8 || P <= 3)                                                 \
+    hipLaunchKernelGGL((k_fpmvo<T, P, KT, 8>), grid, block, 0, st, s, q, f);         \
   else                                                                               \
-    hipLaunchKernelGGL((k_fpmvo<T, P, KT, FD_MAX_FPMVO_SAMPLES>), grid, block, 0, st, s, q, f);
+    hipLaunchKernelGGL((k_fpmvo<T, P, KT, (P <= 3 ? 8 : FD_MAX_FPMVO_SAMPLES)>), grid, block, 0, st, s, q, f);
 #define FD_FPMVO_CASE(T, P)                                                          \
   if (q.K == 5) {                                                                    \
     FD_FPMVO_NS(T, P, 5)                                                             \

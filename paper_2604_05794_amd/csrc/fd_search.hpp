@@ -785,14 +785,20 @@ __device__ __forceinline__ void learned_group(const SceneDev& s, const SearchDev
 // weights, the patch and its score are binary64.
 // The patch is never held: the candidates depend on its centre sample only,
 // so they are fused first and the samples are then formed row by row and
-// folded into each layer's running maximum (NS >= S layers held in
-// registers).  Bound by binary64 arithmetic, most of it the texels' sines
+// folded into each layer's running maximum (NS layers held in registers, the
+// samples formed again for the next NS).
+// Bound by binary64 arithmetic, most of it the texels' sines
 // and cosines (over a hundred instructions each): every texel of the
 // (P + 1)^2 footprint takes them once, where evaluating them per sample took
 // 4 P^2 (100 against 36 + 4 for P = 5).  150,001 points, 64 views of 1024^2
 // binary16, P = 5, S = 5, the whole call: 713 us with the patch held and a
 // sine and cosine per sample, 544 us with the texels shared (330 registers,
 // one wave per SIMD), 435 us with the patch streamed (229, two waves).
+// Whole calls for 40,000 points, 24 views of 512^2, with a sine and cosine per
+// sample, NS = 16 (one wave per SIMD) and NS = 8 (two), us: 6 layers at P = 3
+// 123, 131, 102, at P = 5 223, 175, 143, at P = 7 344, 240, 210; 16 layers at P
+// = 3 159, 184, 155, at P = 5 274, 228, 222 (300 points 101, 88, 103), at P = 7
+// 415, 288, 347.
 template <typename T, int P, int KT, int NS>
 __device__ __forceinline__ void fpmvo_group(const SceneDev& s, const SearchDev& q,
                                             const FpmvoDev& f, const Group& gr, bool pt_ok,
@@ -848,7 +854,6 @@ __device__ __forceinline__ void fpmvo_group(const SceneDev& s, const SearchDev& 
   vok = vok && isfinite(D);
   // Eq. (3): p_s = R^T (X_c - t) with X_c = z_s ((ux - cx)/fx, (uy - cy)/fy, 1)
   const float* R = cam + 4;
-  const float* tc = cam + 13;
   const double S1 = f.samples > 1 ? (double)(f.samples - 1) : 1.0;
 
   // r = J_pi d up to a positive factor, as in build_patch
@@ -856,129 +861,173 @@ __device__ __forceinline__ void fpmvo_group(const SceneDev& s, const SearchDev& 
   const double M[6] = {f0 * (pr.Z * R[0] - pr.X * R[6]), f0 * (pr.Z * R[1] - pr.X * R[7]),
                        f0 * (pr.Z * R[2] - pr.X * R[8]), f1 * (pr.Z * R[3] - pr.Y * R[6]),
                        f1 * (pr.Z * R[4] - pr.Y * R[7]), f1 * (pr.Z * R[5] - pr.Y * R[8])};
-  // per layer: the lane whose candidate was fused (-1: none), the candidate,
-  // this view's doubled image angle of it (on: it has one) and the maximum
-  // over the samples so far
-  int lead[NS];
-  bool on[NS];
-  double lx[NS], ly[NS], lz[NS], c2[NS], s2[NS], m[NS];
-#pragma unroll
-  for (int sl = 0; sl < NS; ++sl) {
-    lead[sl] = -1;
-    on[sl] = false;
-    lx[sl] = ly[sl] = lz[sl] = c2[sl] = s2[sl] = m[sl] = 0.0;
-    if (sl >= f.samples) continue;  // uniform
+  // this lane's candidate of layer sl; a lane without one shares exact zeros
+  // (its depth may be +inf)
+  auto candidate = [&](const float* cm, int sl, double& dx, double& dy, double& dz) {
+    const float *Rm = cm + 4, *tm = cm + 13;
     const double zs =
         D + (f.samples > 1 ? -(double)f.delta + 2.0 * (double)f.delta * (double)sl / S1 : 0.0);
-    const double xc0 = (ux - (double)cam[2]) * zs / (double)cam[0] - (double)tc[0];
-    const double xc1 = (uy - (double)cam[3]) * zs / (double)cam[1] - (double)tc[1];
-    const double xc2 = zs - (double)tc[2];
-    double dx = (double)R[0] * xc0 + (double)R[3] * xc1 + (double)R[6] * xc2 - px;
-    double dy = (double)R[1] * xc0 + (double)R[4] * xc1 + (double)R[7] * xc2 - py;
-    double dz = (double)R[2] * xc0 + (double)R[5] * xc1 + (double)R[8] * xc2 - pz;
+    const double xc0 = (ux - (double)cm[2]) * zs / (double)cm[0] - (double)tm[0];
+    const double xc1 = (uy - (double)cm[3]) * zs / (double)cm[1] - (double)tm[1];
+    const double xc2 = zs - (double)tm[2];
+    dx = (double)Rm[0] * xc0 + (double)Rm[3] * xc1 + (double)Rm[6] * xc2 - px;
+    dy = (double)Rm[1] * xc0 + (double)Rm[4] * xc1 + (double)Rm[7] * xc2 - py;
+    dz = (double)Rm[2] * xc0 + (double)Rm[5] * xc1 + (double)Rm[8] * xc2 - pz;
     const double n = sqrt(dx * dx + dy * dy + dz * dz);
     const bool ok = vok && zs > 0.0 && n > 0.0;
-    // a lane without a candidate shares exact zeros (its depth may be +inf)
     dx = ok ? dx / n : 0.0;
     dy = ok ? dy / n : 0.0;
     dz = ok ? dz / n : 0.0;
-    // Eqs. (5)-(6): weighted consistency of this lane's candidate with the
-    // group's candidates of the same layer (views in the order of Eq. (4))
-    const double wk = ok ? w : 0.0;
-    double num = 0.0, den = 0.0;
-    const int K = KT > 0 ? KT : gr.K;
-    for (int jj = 0; jj < K; ++jj) {
-      const int src = gr.base + jj;
-      const double xj = __shfl(dx, src, kWave), yj = __shfl(dy, src, kWave),
-                   zj = __shfl(dz, src, kWave), wj = __shfl(wk, src, kWave);
-      // G_ii = 1 exactly for a unit direction
-      num += jj == gr.slot ? wj : wj * fabs(dx * xj + dy * yj + dz * zj);
-      den += wj;
+    return ok;
+  };
+  // The best layer's view sum, and its fused candidate: held with the layers,
+  // or (more than 5 layers) formed again in the lane whose it was.
+  constexpr bool KEEP = NS <= 5;
+  double Sb = -INFINITY, bxd = 0.0, byd = 0.0, bzd = 0.0;
+  int best = 0, from = gr.base;
+  // layers l0 .. l0 + NS - 1
+  auto layers = [&](int l0) {
+    // per layer: the lane whose candidate was fused (-1: none), the candidate,
+    // this view's doubled image angle of it (on: it has one) and the maximum
+    // over the samples so far
+    int lead[NS];
+    bool on[NS];
+    double lx[KEEP ? NS : 1], ly[KEEP ? NS : 1], lz[KEEP ? NS : 1], c2[NS], s2[NS], m[NS];
+#pragma unroll
+    for (int sl = 0; sl < NS; ++sl) {
+      lead[sl] = -1;
+      on[sl] = false;
+      c2[sl] = s2[sl] = m[sl] = 0.0;
+      if (KEEP) lx[sl] = ly[sl] = lz[sl] = 0.0;
+      if (l0 + sl >= f.samples) continue;  // uniform
+      double dx, dy, dz;
+      const bool ok = candidate(cam, l0 + sl, dx, dy, dz);
+      // Eqs. (5)-(6): weighted consistency of this lane's candidate with the
+      // group's candidates of the same layer (views in the order of Eq. (4))
+      const double wk = ok ? w : 0.0;
+      double num = 0.0, den = 0.0;
+      const int K = KT > 0 ? KT : gr.K;
+      for (int jj = 0; jj < K; ++jj) {
+        const int src = gr.base + jj;
+        const double xj = __shfl(dx, src, kWave), yj = __shfl(dy, src, kWave),
+                     zj = __shfl(dz, src, kWave), wj = __shfl(wk, src, kWave);
+        // G_ii = 1 exactly for a unit direction
+        num += jj == gr.slot ? wj : wj * fabs(dx * xj + dy * yj + dz * zj);
+        den += wj;
+      }
+      const double sigma = ok ? num / den : -INFINITY;
+      // Eq. (7): the medoid, first of equals
+      int bj = -1;
+      double bs = -INFINITY;
+      for (int jj = 0; jj < K; ++jj) {
+        const double sj = __shfl(sigma, gr.base + jj, kWave);
+        if (sj > bs) {
+          bs = sj;
+          bj = jj;
+        }
+      }
+      // the same in every lane of the group; the shuffles below run in every lane
+      const int src = gr.base + (bj < 0 ? 0 : bj);
+      lead[sl] = bj;
+      const double cx = __shfl(dx, src, kWave), cy = __shfl(dy, src, kWave),
+                   cz = __shfl(dz, src, kWave);
+      if (KEEP) {
+        lx[sl] = cx;
+        ly[sl] = cy;
+        lz[sl] = cz;
+      }
+      const double rx = __builtin_fma(M[0], cx, __builtin_fma(M[1], cy, M[2] * cz));
+      const double ry = __builtin_fma(M[3], cx, __builtin_fma(M[4], cy, M[5] * cz));
+      const double xx = rx * rx;
+      const double n2 = __builtin_fma(ry, ry, xx);
+      on[sl] = slot_ok && n2 > 0.0;
+      const double inv = 1.0 / (on[sl] ? n2 : 1.0);
+      c2[sl] = __builtin_fma(-ry, ry, xx) * inv;
+      s2[sl] = (rx * ry) * inv;
     }
-    const double sigma = ok ? num / den : -INFINITY;
-    // Eq. (7): the medoid, first of equals
-    int bj = -1;
-    double bs = -INFINITY;
-    for (int jj = 0; jj < K; ++jj) {
-      const double sj = __shfl(sigma, gr.base + jj, kWave);
-      if (sj > bs) {
-        bs = sj;
-        bj = jj;
+
+    // Eqs. (9)-(11): the samples of the patch, a texel row at a time
+    int jx0 = ix - HP, jy0 = iy - HP;
+    double gx = fx, gy = fy;
+    if (!KEEP) {  // what follows from them is formed again, not held between the rounds
+      asm volatile("" : "+v"(jx0), "+v"(jy0));
+      asm volatile("" : "+v"(gx), "+v"(gy));
+    }
+    double rc[P + 1], rx[P + 1], ry[P + 1];  // C, cos 2theta, sin 2theta
+    auto load_row = [&](int y) {
+#pragma unroll
+      for (int a = 0; a <= P; ++a) {
+        const double t = tex_load_nb<T>(thm, s.W, s.H, jx0 + a, y);
+        rc[a] = tex_load_nb<T>(cfm, s.W, s.H, jx0 + a, y);
+        sincos(2.0 * t, &ry[a], &rx[a]);
+      }
+    };
+    load_row(jy0);
+#pragma unroll 1
+    for (int b = 0; b < P; ++b) {
+      double pc[P + 1], qx[P + 1], qy[P + 1];  // the row above
+#pragma unroll
+      for (int a = 0; a <= P; ++a) {
+        pc[a] = rc[a];
+        qx[a] = rx[a];
+        qy[a] = ry[a];
+      }
+      load_row(jy0 + b + 1);
+#pragma unroll
+      for (int a = 0; a < P; ++a) {
+        double cb = 0.0, mx = 0.0, my = 0.0;
+#pragma unroll
+        for (int jy = 0; jy < 2; ++jy)
+#pragma unroll
+          for (int jx = 0; jx < 2; ++jx) {
+            const double wt = (jx ? gx : 1.0 - gx) * (jy ? gy : 1.0 - gy);
+            const double c = jy ? rc[a + jx] : pc[a + jx];
+            cb += wt * c;
+            mx += wt * c * (jy ? rx[a + jx] : qx[a + jx]);
+            my += wt * c * (jy ? ry[a + jx] : qy[a + jx]);
+          }
+        const double n = sqrt(mx * mx + my * my);
+        const double al = 0.5 * cb * cb;
+        const double va = n > 0.0 ? al : 0.0;
+        const double vb = n > 0.0 ? al * mx / n : 0.0;
+        const double vc = n > 0.0 ? 2.0 * al * my / n : 0.0;
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl)
+          m[sl] = fmax(m[sl], __builtin_fma(vb, c2[sl], __builtin_fma(vc, s2[sl], va)));
       }
     }
-    // the same in every lane of the group; the shuffles below run in every lane
-    const int src = gr.base + (bj < 0 ? 0 : bj);
-    lead[sl] = bj;
-    lx[sl] = __shfl(dx, src, kWave);
-    ly[sl] = __shfl(dy, src, kWave);
-    lz[sl] = __shfl(dz, src, kWave);
-    const double rx = __builtin_fma(M[0], lx[sl], __builtin_fma(M[1], ly[sl], M[2] * lz[sl]));
-    const double ry = __builtin_fma(M[3], lx[sl], __builtin_fma(M[4], ly[sl], M[5] * lz[sl]));
-    const double xx = rx * rx;
-    const double n2 = __builtin_fma(ry, ry, xx);
-    on[sl] = slot_ok && n2 > 0.0;
-    const double inv = 1.0 / (on[sl] ? n2 : 1.0);
-    c2[sl] = __builtin_fma(-ry, ry, xx) * inv;
-    s2[sl] = (rx * ry) * inv;
-  }
 
-  // Eqs. (9)-(11): the samples of the patch, a texel row at a time
-  double rc[P + 1], rx[P + 1], ry[P + 1];  // C, cos 2theta, sin 2theta
-  auto load_row = [&](int y) {
+    // Eq. (12): patch consistency of each layer's fused candidate
 #pragma unroll
-    for (int a = 0; a <= P; ++a) {
-      const double t = tex_load_nb<T>(thm, s.W, s.H, ix - HP + a, y);
-      rc[a] = tex_load_nb<T>(cfm, s.W, s.H, ix - HP + a, y);
-      sincos(2.0 * t, &ry[a], &rx[a]);
+    for (int sl = 0; sl < NS; ++sl) {
+      if (l0 + sl >= f.samples) continue;  // uniform
+      const double Sv =
+          group_sum_t<KT>((on[sl] && m[sl] > 0.0) ? sqrt(m[sl]) : 0.0, gr.base, gr.K);
+      if (lead[sl] >= 0 && Sv > Sb) {
+        Sb = Sv;
+        if (KEEP) {
+          bxd = lx[sl];
+          byd = ly[sl];
+          bzd = lz[sl];
+        } else {
+          best = l0 + sl;
+          from = gr.base + lead[sl];
+        }
+      }
     }
   };
-  load_row(iy - HP);
+  if constexpr (KEEP) {
+    layers(0);
+  } else {
 #pragma unroll 1
-  for (int b = 0; b < P; ++b) {
-    double pc[P + 1], qx[P + 1], qy[P + 1];  // the row above
-#pragma unroll
-    for (int a = 0; a <= P; ++a) {
-      pc[a] = rc[a];
-      qx[a] = rx[a];
-      qy[a] = ry[a];
-    }
-    load_row(iy - HP + b + 1);
-#pragma unroll
-    for (int a = 0; a < P; ++a) {
-      double cb = 0.0, mx = 0.0, my = 0.0;
-#pragma unroll
-      for (int jy = 0; jy < 2; ++jy)
-#pragma unroll
-        for (int jx = 0; jx < 2; ++jx) {
-          const double wt = (jx ? fx : 1.0 - fx) * (jy ? fy : 1.0 - fy);
-          const double c = jy ? rc[a + jx] : pc[a + jx];
-          cb += wt * c;
-          mx += wt * c * (jy ? rx[a + jx] : qx[a + jx]);
-          my += wt * c * (jy ? ry[a + jx] : qy[a + jx]);
-        }
-      const double n = sqrt(mx * mx + my * my);
-      const double al = 0.5 * cb * cb;
-      const double va = n > 0.0 ? al : 0.0;
-      const double vb = n > 0.0 ? al * mx / n : 0.0;
-      const double vc = n > 0.0 ? 2.0 * al * my / n : 0.0;
-#pragma unroll
-      for (int sl = 0; sl < NS; ++sl)
-        m[sl] = fmax(m[sl], __builtin_fma(vb, c2[sl], __builtin_fma(vc, s2[sl], va)));
-    }
-  }
-
-  // Eq. (12): patch consistency of each layer's fused candidate
-  double Sb = -INFINITY, bxd = 0.0, byd = 0.0, bzd = 0.0;
-#pragma unroll
-  for (int sl = 0; sl < NS; ++sl) {
-    if (sl >= f.samples) continue;  // uniform
-    const double Sv = group_sum_t<KT>((on[sl] && m[sl] > 0.0) ? sqrt(m[sl]) : 0.0, gr.base, gr.K);
-    if (lead[sl] >= 0 && Sv > Sb) {
-      Sb = Sv;
-      bxd = lx[sl];
-      byd = ly[sl];
-      bzd = lz[sl];
-    }
+    for (int l0 = 0; l0 < f.samples; l0 += NS) layers(l0);
+    const float* cm = cam;
+    asm volatile("" : "+v"(cm));  // read again, not held through the samples
+    double dx, dy, dz;
+    candidate(cm, best, dx, dy, dz);
+    bxd = __shfl(dx, from, kWave);
+    byd = __shfl(dy, from, kWave);
+    bzd = __shfl(dz, from, kWave);
   }
   if (pt_ok && gr.slot == 0) {
     if (keff == 0 || !(Sb > -INFINITY))

@@ -435,3 +435,26 @@ def test_non_finite_pixels_in_large_frames(bad, radius, n_orient):
     assert torch.equal(t1[:, ~inside], t0[:, ~inside])
     black = ~inside & (c0[0] == 0.0)
     assert not c1[0][black].any()
+
+
+@pytest.mark.parametrize("samples", [6, 8, 9, 13, 16])
+@pytest.mark.parametrize("patch,top_k", [(1, 5), (3, 5), (3, 2), (5, 5), (7, 8)])
+def test_paper_candidate_rounds(samples, patch, top_k):
+    """Layers held eight at a time, in one round and two, and all at once.  Points
+    of at least two views: the candidates of a single one lie in its own plane,
+    so that all layers tie; of those only the cost is compared."""
+    nat = _native()
+    sc = scenegen.make_scene("tiny", 4)
+    kw = dict(patch=patch, top_k=top_k)
+    fp = dict(lam=2.0, n_samples=samples, delta=8e-3)
+    pts = sc.points[:2003]
+    d, c = nat.fuse_directions(_t(pts), _t(sc.cams), _t(sc.theta), _t(sc.conf), depth_maps=_t(sc.depth),
+                               mode=nat.FD_MODE_FPMVO, fpmvo_lambda=fp["lam"], fpmvo_samples=samples,
+                               fpmvo_delta=fp["delta"], **kw)
+    torch.cuda.synchronize()
+    orc = oracle.Oracle(sc.cams, sc.theta, sc.conf, depth=sc.depth, **kw)
+    do, co = orc.fpmvo(pts, **fp)
+    d, c = d.cpu().numpy(), c.cpu().numpy()
+    two = np.array([len(orc.select_views(p)[0]) > 1 for p in pts])
+    assert_parity(compare(orc, pts[two], d[two], c[two], do[two], co[two]))
+    assert np.allclose(c[~two], co[~two], rtol=0.0, atol=1e-5)

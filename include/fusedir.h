@@ -522,6 +522,15 @@ int fd_profile_read(fd_context* ctx, int stage, double* total_ms, int64_t* count
 int fd_probe_read(const void* buf, int64_t bytes, int32_t reps, int32_t blocks, uint32_t* sink,
                   void* stream);
 
+/* ---- normalisation probe (tests) ---------------------------------------------
+ * pr = p / sqrt(n2) and qr = q / sqrt(n2) as the search forms them for a patch
+ * sample of form al (al m_x / |m| and 2 al m_y / |m|): each operation rounded
+ * to nearest (components below 2^-103 within an ulp).  Device arrays of n float, n in
+ * [0, 2^31]; enqueued on stream.  FD_E_INVAL for n out of range or a null
+ * pointer. */
+int fd_probe_norm(const float* n2, const float* al, const float* p, const float* q, int64_t n,
+                  float* pr, float* qr, void* stream);
+
 const char* fd_last_error(void);
 
 #ifdef __cplusplus

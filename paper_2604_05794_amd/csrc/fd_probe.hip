@@ -1,10 +1,12 @@
-// fd_probe.hip -- read-bandwidth probe for the roofline of the search
-// (measures the L2 ceiling, which has no published figure).
+// fd_probe.hip -- probes: read bandwidth for the roofline of the search (the L2
+// ceiling, which has no published figure), and the search's own normalisation
+// on operands of the caller's.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "../../include/fusedir.h"
 #include "fd_api_internal.hpp"
+#include "fd_device.hpp"
 
 using namespace fd;
 
@@ -31,7 +33,36 @@ __global__ __launch_bounds__(256) void k_probe_read(const uint4* __restrict__ bu
   sink[(size_t)blockIdx.x * 256 + threadIdx.x] = acc;
 }
 
+__global__ __launch_bounds__(256) void k_probe_norm(const float* __restrict__ n2,
+                                                    const float* __restrict__ al,
+                                                    const float* __restrict__ p,
+                                                    const float* __restrict__ q, int64_t n,
+                                                    float* __restrict__ pr,
+                                                    float* __restrict__ qr) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  float a, b;
+  over_norm(n2[i], al[i], p[i], q[i], n2[i] > 0.0f, a, b);
+  pr[i] = a;
+  qr[i] = b;
+}
+
 }  // namespace
+
+extern "C" int fd_probe_norm(const float* n2, const float* al, const float* p, const float* q,
+                             int64_t n, float* pr, float* qr, void* stream) {
+  if (n < 0 || n > ((int64_t)1 << 31))
+    return set_error(FD_E_INVAL, "fd_probe_norm: n must be in [0, 2^31]");
+  if (n > 0 && (!n2 || !al || !p || !q || !pr || !qr))
+    return set_error(FD_E_INVAL, "fd_probe_norm: null pointer");
+  int r;
+  if ((r = check_device(nullptr))) return r;
+  if (n == 0) return FD_OK;
+  hipLaunchKernelGGL(k_probe_norm, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
+                     (hipStream_t)stream, n2, al, p, q, n, pr, qr);
+  hipError_t e = hipGetLastError();
+  return e == hipSuccess ? FD_OK : hip_error(e, "fd_probe_norm");
+}
 
 extern "C" int fd_probe_read(const void* buf, int64_t bytes, int32_t reps, int32_t blocks,
                              uint32_t* sink, void* stream) {

@@ -115,26 +115,6 @@ struct ViewPatch {
   float M[6];                  // image direction r = M d (rows of the projection Jacobian)
 };
 
-// p / sqrt(n2) and q / sqrt(n2), each operation rounded as IEEE rounds it,
-// from one estimate of the square root and one of its reciprocal: the
-// residual of the root, of the reciprocal and of each quotient taken with a
-// fused multiply-add and added back (Markstein 1990).  13 instructions, where
-// a square root and two divisions that hold for every operand are some 36.
-// The residuals are exact, and the results the correctly rounded ones, for
-// 2^-44 < n2 and |p|, |q| < 2^100 down to 2^-103 (no difference in 1.7e10
-// operands, every mantissa of n2 with both parities of its exponent among
-// them); the caller takes the general operations elsewhere.
-// Plain search of 500,000 points, 64 views of 1024^2 binary16, P = 5: 1313 ->
-// 1261 us.
-__device__ __forceinline__ void over_root(float n2, float p, float q, float& pr, float& qr) {
-  const float y = __builtin_amdgcn_rsqf(n2), s0 = __builtin_amdgcn_sqrtf(n2);
-  const float s = __builtin_fmaf(__builtin_fmaf(-s0, s0, n2), 0.5f * y, s0);
-  const float r = __builtin_fmaf(__builtin_fmaf(-s, y, 1.0f), y, y);
-  const float p0 = p * r, q0 = q * r;
-  pr = __builtin_fmaf(__builtin_fmaf(-p0, s, p), r, p0);
-  qr = __builtin_fmaf(__builtin_fmaf(-q0, s, q), r, q0);
-}
-
 // Build the lane's view state: Jacobian rows and the P x P patch of Sec. 3.1.3
 // centred on the projection (offsets (a, b) in {-h..h}^2 pixels from the
 // sub-pixel centre, each a bilinear sample of the doubled-angle vector
@@ -232,12 +212,7 @@ __device__ __forceinline__ void build_patch(const SceneDev& s, const SearchDev& 
       const bool on = n2 > 0.0f;
       const float bx = al * mx, cy = 2.0f * al * my;  // the factor 2 of 2 rx ry folded in
       float qb, qc;
-      over_root(n2, bx, cy, qb, qc);
-      if (on && !(n2 > 0x1p-44f && al < 0x1p60f)) {
-        const float n = sqrtf(n2);
-        qb = bx / n;
-        qc = cy / n;
-      }
+      over_norm(n2, al, bx, cy, on, qb, qc);
       const int k = b * P + a;
       vp.a[k] = on ? al : 0.0f;
       vp.b[k] = on ? qb : 0.0f;

@@ -35,6 +35,7 @@ EXPORTS = (
     "fd_tuned_shape", "fd_set_tuned_shape", "fd_profile_enable", "fd_profile_read", "fd_gabor_params_init",
     "fd_orientation_maps", "fd_fuse_volume", "fd_grow_params_init", "fd_grow_strands",
     "fd_link_segments", "fd_strand_offsets", "fd_assemble_strands", "fd_probe_read",
+    "fd_probe_norm",
     "fd_last_error",
 )
 
@@ -169,6 +170,7 @@ def lib():
         "fd_assemble_strands": (ctypes.c_int, [P, P, i32, i32, P, P, i32, P, P, i32, i32, P, P,
                                                i64, P, P, P]),
         "fd_probe_read": (ctypes.c_int, [P, i64, i32, i32, P, P]),
+        "fd_probe_norm": (ctypes.c_int, [P, P, P, P, i64, P, P, P]),
         "fd_last_error": (ctypes.c_char_p, []),
     }
     for name, (res, args) in sig.items():
@@ -709,6 +711,18 @@ def autotune(scenes, ctx: Context, cache_path=None, **kw):
     p = make_params(1, 1, dt, ctx=ctx, **kw)
     _check(lib().fd_autotune(ctx.handle, arr, len(scenes), ctypes.byref(p),
                              os.fsencode(cache_path) if cache_path else None))
+
+
+def probe_norm(n2, al, p, q, stream=None):
+    """fd_probe_norm: (p / sqrt(n2), q / sqrt(n2)) as the search forms them."""
+    for name, t in (("n2", n2), ("al", al), ("p", p), ("q", q)):
+        _dev_tensor(t, name, torch.float32)
+        if t.shape != n2.shape:
+            raise ValueError(f"{name} must have n2's shape")
+    pr, qr = torch.empty_like(n2), torch.empty_like(n2)
+    _check(lib().fd_probe_norm(_ptr(n2), _ptr(al), _ptr(p), _ptr(q), n2.numel(), _ptr(pr), _ptr(qr),
+                               _stream_handle(stream)))
+    return pr, qr
 
 
 def probe_read(buf, reps, blocks, sink=None, stream=None):

@@ -458,3 +458,48 @@ def test_paper_candidate_rounds(samples, patch, top_k):
     two = np.array([len(orc.select_views(p)[0]) > 1 for p in pts])
     assert_parity(compare(orc, pts[two], d[two], c[two], do[two], co[two]))
     assert np.allclose(c[~two], co[~two], rtol=0.0, atol=1e-5)
+
+
+@pytest.mark.parametrize("part", ["every mantissa", "products", "outside"])
+def test_sample_normalisation_is_rounded_as_ieee(part):
+    """p / sqrt(n2) and q / sqrt(n2) against binary32 square root and division:
+    every mantissa of n2 in two binades; the operands as a sample forms them, of
+    confidences from 2^-22 to 2^30; and outside the short form's range, special
+    values among them.  The same bits, apart from p and q below 2^-103 (an
+    ulp)."""
+    nat = _native()
+    rng = np.random.default_rng(len(part))
+    f = np.float32
+    n = 1 << 24
+    if part == "every mantissa":
+        n2 = np.arange(n, dtype=np.uint32) + f(1.0).view(np.uint32)
+        n2 = n2.view(f) * (f(2.0) ** (2 * rng.integers(-21, 30, n))).astype(f)
+        al = np.full(n, 1.0, f)
+        p = (rng.uniform(1.0, 2.0, n) * 2.0 ** rng.integers(-103, 92, n)).astype(f)
+        q = -(rng.uniform(1.0, 2.0, n) * 2.0 ** rng.integers(-103, 92, n)).astype(f)
+    elif part == "products":
+        n = 1 << 22
+        cb = (rng.uniform(1.0, 2.0, n) * 2.0 ** rng.integers(-23, 30, n)).astype(f)
+        m = cb * rng.uniform(0.0, 1.0, n).astype(f) ** f(2.0)
+        t = np.where(rng.uniform(size=n) < 0.2, rng.choice([0.0, 0.5, 1.0, 1.5], n) * np.pi + 10.0 ** rng.uniform(-40, -6, n),
+                     rng.uniform(0, 2 * np.pi, n))
+        mx, my = (m * np.cos(t)).astype(f), (m * np.sin(t)).astype(f)
+        with np.errstate(all="ignore"):
+            n2, al = mx * mx + my * my, f(0.5) * cb * cb
+            p, q = al * mx, f(2.0) * al * my
+    else:
+        n = 1 << 20
+        special = np.array([0.0, 1e-45, 2.0**-149, 2.0**-126, 2.0**-60, 2.0**-44, 1.0, 2.0**60, 2.0**61, 3e38, np.inf, np.nan], f)
+        n2, al, p, q = (np.where(rng.uniform(size=n) < 0.5, rng.choice(special, n),
+                                 (rng.uniform(1.0, 2.0, n) * 2.0 ** rng.integers(-120, 120, n)).astype(f)).astype(f) for _ in range(4))
+        n2 = np.where((n2 > 2.0**-44) & (al < 2.0**60), f(2.0**-50) * np.minimum(n2, f(16.0)), n2).astype(f)
+        q = -q
+    got = [v.cpu().numpy() for v in nat.probe_norm(*map(_t, (n2, al, p, q)))]
+    on = n2 > 0.0
+    with np.errstate(all="ignore"):
+        for g, x in zip(got, (p, q)):
+            want = x / np.sqrt(n2)
+            same = (g == want) | (np.isnan(g) & np.isnan(want))
+            small = (np.abs(x) < 2.0**-103) & (n2 > 2.0**-44) & (al < 2.0**60)
+            assert same[on & ~small].all(), int((~same & on & ~small).sum())
+            assert (np.abs(g - want) <= np.spacing(np.abs(want)))[on & small].all()

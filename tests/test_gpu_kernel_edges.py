@@ -503,3 +503,28 @@ def test_sample_normalisation_is_rounded_as_ieee(part):
             small = (np.abs(x) < 2.0**-103) & (n2 > 2.0**-44) & (al < 2.0**60)
             assert same[on & ~small].all(), int((~same & on & ~small).sum())
             assert (np.abs(g - want) <= np.spacing(np.abs(want)))[on & small].all()
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("views", [9, 64, 131])
+def test_feature_rows_of_many_points(views, half):
+    """Rows of 3001 distinct points against the oracle: the same slots, and the
+    share of values off by more than a bfloat16 step that the feature test
+    grants (1e-4), of 336,112."""
+    nat = _native()
+    rec = dict(scenegen.RECIPES["tiny"], n_points=3001, n_views=min(views, 48), arc_deg=360.0)
+    sc = scenegen.make_scene(rec, 8)
+    v = np.arange(views) % len(sc.cams)
+    cams = sc.cams[v].copy()
+    cams[len(sc.cams):, 13] += np.float32(1e-3)  # further views: a millimetre aside
+    th, cf, dm = sc.theta[v], sc.conf[v], sc.depth[v]
+    if half:
+        th, cf, dm = (a.astype(np.float16) for a in (th, cf, dm))
+    pts = np.asarray(sc.points, np.float32)
+    rows = nat.features(_t(pts), _t(cams), _t(th), _t(cf), head_centre=sc.head_centre, depth_maps=_t(dm))
+    f = rows.float().cpu().numpy().astype(np.float64)
+    fo = oracle.Oracle(cams, th.astype(np.float32), cf.astype(np.float32), patch=1,
+                       depth=dm.astype(np.float32)).features(pts, sc.head_centre)
+    assert np.array_equal(f[:, 6::7], fo[:, 6::7])
+    err = np.abs(f - oracle.round_bf16(fo.astype(np.float32)).astype(np.float64))
+    assert (err > 2.0 ** -7 * np.abs(fo) + 1e-5).sum() <= 1e-4 * err.size

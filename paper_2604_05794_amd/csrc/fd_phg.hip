@@ -4,8 +4,8 @@
 // The rules are documented with fd_grow_strands and fd_link_segments in
 // fusedir.h.
 //
-// Growing: one wave per strand.  A batch of strands is one launch of
-// k_grow, which reads the crossing counts as the earlier batches left them;
+// Growing: one wave per strand (k_grow) or, in large batches, one lane
+// (k_grow_lane).  A batch of strands is one launch, which reads the crossing counts as the earlier batches left them;
 // the launch boundary is the batch barrier, after which k_cross adds every
 // step of the batch to the count of the voxel it read (integer atomics, so
 // the counts do not depend on the order of the additions).  Each step is a
@@ -53,6 +53,72 @@ struct GrowDev {
 
 __device__ __forceinline__ float dot3(const float* a, const float* b) {
   return __builtin_fmaf(a[2], b[2], __builtin_fmaf(a[1], b[1], a[0] * b[0]));
+}
+
+// ---- growing, one lane per strand ------------------------------------------------
+// Each step is four loads issued together, whose latency the other strands of
+// the SIMD hide.  For batches that have enough of them (kLaneBatch).
+__global__ __launch_bounds__(256) void k_grow_lane(GrowDev d,
+                                                   const float* __restrict__ seeds,
+                                                   const float* __restrict__ seed_dirs, int32_t b0,
+                                                   int32_t b1,
+                                                   const uint32_t* __restrict__ crossings,
+                                                   float* __restrict__ verts,
+                                                   int32_t* __restrict__ n_verts,
+                                                   float* __restrict__ last_dir) {
+  const int32_t i = b0 + (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i >= b1) return;
+  float x[3] = {seeds[3 * (size_t)i], seeds[3 * (size_t)i + 1], seeds[3 * (size_t)i + 2]};
+  float r[3] = {0.0f, 0.0f, 0.0f};
+  if (d.mode == FD_SEED_GIVEN) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) r[a] = seed_dirs[3 * (size_t)i + a];
+  } else {
+    const int64_t v = voxel_index(d.g, x[0], x[1], x[2]);
+    if (v >= 0) {
+      const float t[3] = {d.dir[3 * v], d.dir[3 * v + 1], d.dir[3 * v + 2]};
+      const float off[3] = {x[0] - d.centre[0], x[1] - d.centre[1], x[2] - d.centre[2]};
+      const bool away = !(dot3(t, off) < 0.0f);
+      const float sg = (away == (d.mode == FD_SEED_AWAY)) ? 1.0f : -1.0f;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) r[a] = sg * t[a];
+    }
+  }
+  float* out = verts + (size_t)i * (size_t)(d.max_steps + 1) * 3;
+  out[0] = x[0];
+  out[1] = x[1];
+  out[2] = x[2];
+  int n = 1;
+  for (int k = 1; k <= d.max_steps; ++k) {
+    const int64_t v = voxel_index(d.g, x[0], x[1], x[2]);
+    if (v < 0) break;
+    const uint32_t o = d.occ[v];
+    const float c0 = d.coh[v];
+    const uint32_t cr = crossings[v];
+    float t[3] = {d.dir[3 * v], d.dir[3 * v + 1], d.dir[3 * v + 2]};
+    if (o == 0u || !(c0 >= d.min_coh)) break;
+    if (d.cap > 0u && cr >= d.cap) break;
+    if (t[0] == 0.0f && t[1] == 0.0f && t[2] == 0.0f) break;
+    float c = dot3(t, r);
+    if (c < 0.0f) {
+      t[0] = -t[0];
+      t[1] = -t[1];
+      t[2] = -t[2];
+      c = -c;
+    }
+    if (k > 1 && c < d.bend_cos) break;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      x[a] = __builtin_fmaf(d.step, t[a], x[a]);
+      r[a] = t[a];
+      out[3 * n + a] = x[a];
+    }
+    ++n;
+  }
+  n_verts[i] = n;
+  const float sg = d.mode == FD_SEED_TOWARDS ? -1.0f : 1.0f;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) last_dir[3 * (size_t)i + a] = n > 1 ? sg * r[a] : 0.0f;
 }
 
 // ---- growing, one wave per strand ------------------------------------------------
@@ -230,13 +296,14 @@ __global__ __launch_bounds__(256) void k_grow(GrowDev d, float inv_h,
     // same for all of them.  "Well inside" leaves out the rounding of the
     // voxel rule (three roundings of numbers up to (ix + 1) h, under 2e-7 of
     // them).
+    const float rr = dot3(r, r);  // 0: underflow, where the agreement has no sign
     float mid[3], half[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       mid[a] = ((float)ix[a] + 0.5f) * d.g.h;
-      half[a] = inv_h > 0.0f ? (0.5f - 1e-6f * (float)(ix[a] + 1)) * d.g.h : -1.0f;
+      half[a] = inv_h > 0.0f && rr > 0.0f ? (0.5f - 1e-6f * (float)(ix[a] + 1)) * d.g.h : -1.0f;
     }
-    const bool bent = wave_cond(dot3(r, r) < d.bend_cos);
+    const bool bent = wave_cond(rr < d.bend_cos);
     bool stop = false;
     while (n <= d.max_steps && wave_cond(fabsf((x[0] - d.g.o[0]) - mid[0]) < half[0] &&
                                          fabsf((x[1] - d.g.o[1]) - mid[1]) < half[1] &&
@@ -591,6 +658,18 @@ extern "C" void fd_grow_params_init(fd_grow_params* p) {
   p->ctx = nullptr;
 }
 
+// Batches above this many seeds take a lane per strand: as many waves as the
+// card holds at once (256 compute units of 32).  Below, a wave per strand takes
+// the shorter time for its chain; above, 64 lanes' work for one strand is what
+// counts.  A batch's traces, us, lane and wave, 4096 / 8192 / 16,384 / 65,536
+// seeds:
+//   smooth field, 103 steps   319 / 319 / 319 / 448   106 / 153 / 231 / 672
+//   smooth, 21 steps          33 / 39 / 39 / 100      21 / 31 / 53 / 169
+//   noisy field, bend 45 deg  32 / 33 / 37 / 58       21 / 28 / 41 / 126
+//   a sixth occupied          14 / 17 / 15 / 22       10 / 11 / 14 / 33
+// (a noisy field without a bend limit, cut at 20 steps: 30 / 38 and 35 / 53.)
+constexpr int32_t kLaneBatch = 8192;
+
 extern "C" int fd_grow_strands(const fd_volume_grid* grid, const uint32_t* occ, const float* dir,
                                const float* coherence, const float* seeds,
                                const float* seed_dirs, int32_t n_seeds,
@@ -644,9 +723,13 @@ extern "C" int fd_grow_strands(const fd_volume_grid* grid, const uint32_t* occ, 
     const int32_t b1 = n_seeds - b0 > p->batch ? b0 + p->batch : n_seeds;
     {
       StageTimer t(c, FD_STAGE_GROW, st);
-      const dim3 nb((unsigned)(((int64_t)(b1 - b0) + 3) / 4));
-      hipLaunchKernelGGL(k_grow, nb, dim3(256), 0, st, d, inv_h, seeds, seed_dirs, b0, b1,
-                         crossings, verts, n_verts, last_dir);
+      if (b1 - b0 > kLaneBatch)
+        hipLaunchKernelGGL(k_grow_lane, dim3((unsigned)(((int64_t)(b1 - b0) + 255) / 256)),
+                           dim3(256), 0, st, d, seeds, seed_dirs, b0, b1, crossings, verts, n_verts,
+                           last_dir);
+      else
+        hipLaunchKernelGGL(k_grow, dim3((unsigned)((b1 - b0 + 3) / 4)), dim3(256), 0, st, d, inv_h,
+                           seeds, seed_dirs, b0, b1, crossings, verts, n_verts, last_dir);
       if ((e = hipGetLastError()) != hipSuccess) return hip_error(e, "grow");
       t.stop();
     }

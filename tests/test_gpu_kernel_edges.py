@@ -528,3 +528,41 @@ def test_feature_rows_of_many_points(views, half):
     assert np.array_equal(f[:, 6::7], fo[:, 6::7])
     err = np.abs(f - oracle.round_bf16(fo.astype(np.float32)).astype(np.float64))
     assert (err > 2.0 ** -7 * np.abs(fo) + 1e-5).sum() <= 1e-4 * err.size
+
+
+@pytest.mark.parametrize("mode,cap,bend", [(0, 0, -2.0), (1, 6, 0.5), (2, 3, 0.9)])
+def test_growing_on_both_sides_of_the_lane_batch(mode, cap, bend):
+    """8192 seeds take a wave each, 8193 a lane each: the same traces as the
+    oracle's, and as each other's over the seeds that both have."""
+    nat = _native()
+    rng = np.random.default_rng(mode)
+    dims = (44, 37, 41)
+    nx, ny, nz = dims
+    d = rng.normal(size=(nz, ny, nx, 3)) * 0.3 + np.array([0.5, 0.2, -0.7])
+    d /= np.linalg.norm(d, axis=-1, keepdims=True)
+    d = (d * rng.choice([-1.0, 1.0], size=(nz, ny, nx, 1))).astype(np.float32)
+    d[rng.uniform(size=(nz, ny, nx)) < 0.01] = 0.0
+    d[5:8, :, :] *= np.float32(1e-25)  # an agreement that underflows
+    occ = (rng.uniform(size=(nz, ny, nx)) > 0.02).astype(np.uint32)
+    coh = rng.uniform(0.1, 1.0, size=(nz, ny, nx)).astype(np.float32)
+    grid = (np.array([0.1, -0.07, 0.02], np.float32), np.float32(0.0027), np.array(dims, np.int32))
+    n = 8193
+    seeds = (rng.uniform(-0.02, 1.02, size=(n, 3)) * np.array(dims) * 0.0027 + grid[0]).astype(np.float32)
+    sdirs = rng.normal(size=(n, 3)).astype(np.float32) if mode == 0 else None
+    kw = dict(step=6e-4, max_steps=80, min_coherence=0.12, max_bend_cos=bend, voxel_cap=cap)
+    got = []
+    for batch in (8192, 8193):
+        cr = torch.zeros(occ.size, dtype=torch.int32, device=DEV)
+        v, nv, last = nat.grow_strands(_t(occ.view(np.int32)), _t(d), _t(coh), *grid, _t(seeds), None if sdirs is None else _t(sdirs),
+                                       crossings=cr, seed_mode=mode, centre=(0.15, 0.0, 0.05), batch=batch, **kw)
+        o = oracle.grow(dict(occ=occ, dir=d, coherence=coh), grid, seeds, sdirs, crossings=np.zeros(occ.size, np.uint32),
+                        seed_mode=mode, centre=(0.15, 0.0, 0.05), batch=batch, **kw)
+        v, nv, last = v.cpu().numpy(), nv.cpu().numpy(), last.cpu().numpy()
+        on = np.arange(v.shape[1])[None] < nv[:, None]
+        assert np.array_equal(nv, o["n_verts"]) and np.array_equal(last, o["last_dir"])
+        assert np.array_equal(v[on], o["verts"][:, :v.shape[1]][on])
+        assert np.array_equal(cr.cpu().numpy().view(np.uint32), o["crossings"])
+        got.append((nv, v, on, last))
+    (na, va, ona, la), (nb, vb, onb, lb) = got
+    assert np.array_equal(na[:8192], nb[:8192]) and np.array_equal(la[:8192], lb[:8192])
+    assert np.array_equal(va[:8192][ona[:8192]], vb[:8192][onb[:8192]])

@@ -566,3 +566,24 @@ def test_growing_on_both_sides_of_the_lane_batch(mode, cap, bend):
     (na, va, ona, la), (nb, vb, onb, lb) = got
     assert np.array_equal(na[:8192], nb[:8192]) and np.array_equal(la[:8192], lb[:8192])
     assert np.array_equal(va[:8192][ona[:8192]], vb[:8192][onb[:8192]])
+
+
+@pytest.mark.parametrize("counts,singles", [([127, 128, 129, 300, 4001], 3000), ([5000], 1000), ([129] * 70, 600),
+                                            ([1023, 1024, 1025, 6001, 31], 0), ([1025] * 20 + [1] * 5, 0)])
+def test_volume_heavy_voxels(counts, singles):
+    """Voxels around the points from which the whole wave takes one, few and
+    many to a wave, with one lane a voxel (many single points) and eight.  The
+    bounds of the volume tests."""
+    import test_gpu_volume as V
+    rng = np.random.default_rng(len(counts) + singles)
+    dims = np.array([40, 30, 20])
+    h = np.float32(0.01)
+    at = rng.choice(int(np.prod(dims)), len(counts) + singles, replace=False)
+    at = np.repeat(at, np.array(counts + [1] * singles))
+    cell = np.stack([at % 40, at // 40 % 30, at // 1200], 1)
+    pts = ((cell + rng.uniform(0.01, 0.99, cell.shape)) * 0.01).astype(np.float32)
+    keep = rng.permutation(len(pts))
+    d = rng.normal(size=(len(pts), 3)) + np.array([1.0, -0.4, 0.8])
+    d = (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32)
+    w = rng.uniform(0.0, 1.0, len(pts)).astype(np.float32)
+    V._compare(pts[keep], d[keep], np.zeros(3, np.float32), h, dims.astype(np.int32), w[keep])

@@ -587,3 +587,26 @@ def test_volume_heavy_voxels(counts, singles):
     d = (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32)
     w = rng.uniform(0.0, 1.0, len(pts)).astype(np.float32)
     V._compare(pts[keep], d[keep], np.zeros(3, np.float32), h, dims.astype(np.int32), w[keep])
+
+
+@pytest.mark.parametrize("repeat", [2, 3, 64])
+@pytest.mark.parametrize("views", [40, 64, 150])
+def test_feature_lists_of_coinciding_cameras(views, repeat):
+    """Cameras at the same place (with other orientations or the same, more of
+    them than slots, mixed with cameras a rounding apart) leave the list in the
+    order of the oracle's: by frontality, then by view."""
+    nat = _native()
+    rec = dict(scenegen.RECIPES["tiny"], n_points=500, n_views=24, arc_deg=360.0)
+    sc = scenegen.make_scene(rec, 12)
+    rng = np.random.default_rng(views + repeat)
+    v = rng.permutation(np.arange(views) // repeat % 24)
+    cams = sc.cams[v].copy()
+    near = rng.uniform(size=views) < 0.3  # the last bit of the translation
+    cams[near, 13] = np.nextafter(cams[near, 13], np.float32(np.inf))
+    pts = np.asarray(sc.points, np.float32)
+    rows = nat.features(_t(pts), _t(cams), _t(sc.theta[v]), _t(sc.conf[v]), head_centre=sc.head_centre)
+    f = rows.float().cpu().numpy().astype(np.float64)
+    fo = oracle.Oracle(cams, sc.theta[v].astype(np.float32), sc.conf[v].astype(np.float32), patch=1).features(pts, sc.head_centre)
+    assert np.array_equal(f[:, 6::7], fo[:, 6::7])
+    err = np.abs(f - oracle.round_bf16(fo.astype(np.float32)).astype(np.float64))
+    assert (err > 2.0 ** -7 * np.abs(fo) + 1e-5).sum() <= 1e-4 * err.size

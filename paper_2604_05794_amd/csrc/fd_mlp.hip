@@ -635,7 +635,7 @@ __global__ __launch_bounds__(256) void k_train_finish(TrainDev a, int S,
   const int t = threadIdx.x;
   int blk = blockIdx.x;
   if (blk < kFinTiles) {
-    __shared__ uint16_t tr[64][16];
+    __shared__ __attribute__((aligned(16))) uint16_t tr[64][16];  // read 8 bytes at a time
     const int l = blk < kFinTiles1 ? 0 : (blk < kFinTiles1 + kFinTilesH ? 1 : 2);
     blk -= l == 0 ? 0 : (l == 1 ? kFinTiles1 : kFinTiles1 + kFinTilesH);
     const int k0 = blk / kTilesN * 16, n = blk % kTilesN * 64 + (t & 63);

@@ -4,11 +4,12 @@
 // The rules are documented with fd_grow_strands and fd_link_segments in
 // fusedir.h.
 //
-// Growing: one wave per strand (k_grow) or, in large batches, one lane
-// (k_grow_lane).  A batch of strands is one launch, which reads the crossing counts as the earlier batches left them;
-// the launch boundary is the batch barrier, after which k_cross adds every
-// step of the batch to the count of the voxel it read (integer atomics, so
-// the counts do not depend on the order of the additions).  Each step is a
+// Growing: a batch of strands reads the crossing counts as the earlier batches
+// left them, one wave per strand (k_grow) or, in large batches, one lane for the
+// first steps and either for the rest (k_grow_first, k_grow_rest); the end of
+// its launches is the batch barrier, after which k_cross adds every step of the
+// batch to the count of the voxel it read (integer atomics, so the counts do
+// not depend on the order of the additions).  Each step is a
 // voxel lookup (count, coherence, crossings, orientation) and binary32
 // arithmetic written as fused multiply-adds in a fixed order: a trace is a
 // deterministic function of its inputs.
@@ -22,6 +23,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "../../include/fusedir.h"
@@ -57,39 +59,59 @@ __device__ __forceinline__ float dot3(const float* a, const float* b) {
 
 // ---- growing, one lane per strand ------------------------------------------------
 // Each step is four loads issued together, whose latency the other strands of
-// the SIMD hide.  For batches that have enough of them (kLaneBatch).
-__global__ __launch_bounds__(256) void k_grow_lane(GrowDev d,
-                                                   const float* __restrict__ seeds,
-                                                   const float* __restrict__ seed_dirs, int32_t b0,
-                                                   int32_t b1,
-                                                   const uint32_t* __restrict__ crossings,
-                                                   float* __restrict__ verts,
-                                                   int32_t* __restrict__ n_verts,
-                                                   float* __restrict__ last_dir) {
-  const int32_t i = b0 + (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= b1) return;
-  float x[3] = {seeds[3 * (size_t)i], seeds[3 * (size_t)i + 1], seeds[3 * (size_t)i + 2]};
-  float r[3] = {0.0f, 0.0f, 0.0f};
-  if (d.mode == FD_SEED_GIVEN) {
+// the SIMD hide, where there are enough of them.
+//
+// A batch of many seeds is traced in two launches, the first kFirstSteps steps
+// and the rest (k_grow_rest).  Between them, and until k_cross has counted it, a
+// trace that goes on after the first has -n in n_verts; its state is its last
+// vertex and last_dir.
+constexpr int kFirstSteps = 32;
+
+__device__ __forceinline__ void grow_resume(const GrowDev& d, int32_t i, const float* out,
+                                            const float* last_dir, float* x, float* r) {
+  const float sg = d.mode == FD_SEED_TOWARDS ? -1.0f : 1.0f;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) r[a] = seed_dirs[3 * (size_t)i + a];
+  for (int a = 0; a < 3; ++a) {
+    x[a] = out[3 * kFirstSteps + a];
+    r[a] = sg * last_dir[3 * (size_t)i + a];
+  }
+}
+
+// Strand i by a lane: steps up to `last`, from the seed or from the first
+// launch's end.
+__device__ __forceinline__ void grow_lane(
+    const GrowDev& d, int32_t i, bool rest, int last, const float* __restrict__ seeds,
+    const float* __restrict__ seed_dirs, const uint32_t* __restrict__ crossings,
+    float* __restrict__ verts, int32_t* __restrict__ n_verts, float* __restrict__ last_dir) {
+  float* out = verts + (size_t)i * (size_t)(d.max_steps + 1) * 3;
+  float x[3], r[3];
+  int n = 1;
+  if (rest) {
+    n = 1 + kFirstSteps;
+    grow_resume(d, i, out, last_dir, x, r);
   } else {
-    const int64_t v = voxel_index(d.g, x[0], x[1], x[2]);
-    if (v >= 0) {
-      const float t[3] = {d.dir[3 * v], d.dir[3 * v + 1], d.dir[3 * v + 2]};
-      const float off[3] = {x[0] - d.centre[0], x[1] - d.centre[1], x[2] - d.centre[2]};
-      const bool away = !(dot3(t, off) < 0.0f);
-      const float sg = (away == (d.mode == FD_SEED_AWAY)) ? 1.0f : -1.0f;
 #pragma unroll
-      for (int a = 0; a < 3; ++a) r[a] = sg * t[a];
+    for (int a = 0; a < 3; ++a) {
+      x[a] = out[a] = seeds[3 * (size_t)i + a];
+      r[a] = 0.0f;
+    }
+    if (d.mode == FD_SEED_GIVEN) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) r[a] = seed_dirs[3 * (size_t)i + a];
+    } else {
+      const int64_t v = voxel_index(d.g, x[0], x[1], x[2]);
+      if (v >= 0) {
+        const float t[3] = {d.dir[3 * v], d.dir[3 * v + 1], d.dir[3 * v + 2]};
+        const float off[3] = {x[0] - d.centre[0], x[1] - d.centre[1], x[2] - d.centre[2]};
+        const bool away = !(dot3(t, off) < 0.0f);
+        const float sg = (away == (d.mode == FD_SEED_AWAY)) ? 1.0f : -1.0f;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) r[a] = sg * t[a];
+      }
     }
   }
-  float* out = verts + (size_t)i * (size_t)(d.max_steps + 1) * 3;
-  out[0] = x[0];
-  out[1] = x[1];
-  out[2] = x[2];
-  int n = 1;
-  for (int k = 1; k <= d.max_steps; ++k) {
+  int k = n;
+  for (; k <= last; ++k) {
     const int64_t v = voxel_index(d.g, x[0], x[1], x[2]);
     if (v < 0) break;
     const uint32_t o = d.occ[v];
@@ -115,7 +137,7 @@ __global__ __launch_bounds__(256) void k_grow_lane(GrowDev d,
     }
     ++n;
   }
-  n_verts[i] = n;
+  n_verts[i] = rest || (k > last && last < d.max_steps) ? -n : n;
   const float sg = d.mode == FD_SEED_TOWARDS ? -1.0f : 1.0f;
 #pragma unroll
   for (int a = 0; a < 3; ++a) last_dir[3 * (size_t)i + a] = n > 1 ? sg * r[a] : 0.0f;
@@ -137,10 +159,9 @@ __global__ __launch_bounds__(256) void k_grow_lane(GrowDev d,
 // the two could differ.  The seed's own voxel is read by itself first: most
 // interior seeds stop there.  Vertices are kept one per lane and stored 64
 // at a time.  4096 guide strands through a 3 mm volume (mean 22 steps, longest
-// 200) take 80 us, 234 us with one lane per strand (1.15 us a step); 68,000
-// interior seeds, a sixth of which grow, 135 us against 252.  Measured between
-// the two: 16 lanes a strand with 4 x 2 x 2 blocks 92 and 112-162 us, 64
-// lanes under divergent branches 88 us.  What is left is the wait where a
+// 200) take 76 us, 243 us with one lane per strand (1.15 us a step).  Measured
+// between the two: 16 lanes a strand with 4 x 2 x 2 blocks 92 us, 64 lanes under
+// divergent branches 88 us.  What is left is the wait where a
 // strand leaves its block sideways and, early in a batch, the cache lines
 // that its blocks touch.
 
@@ -225,24 +246,25 @@ struct GrowBlock {
 // A condition that is the same in every lane of the wave, as a scalar.
 __device__ __forceinline__ bool wave_cond(bool c) { return __ballot(c) != 0ull; }
 
-__global__ __launch_bounds__(256) void k_grow(GrowDev d, float inv_h,
-                                              const float* __restrict__ seeds,
-                                              const float* __restrict__ seed_dirs, int32_t b0,
-                                              int32_t b1, const uint32_t* __restrict__ crossings,
-                                              float* __restrict__ verts,
-                                              int32_t* __restrict__ n_verts,
-                                              float* __restrict__ last_dir) {
-  __shared__ float4 blocks[4][64];
-  const int lane = (int)(threadIdx.x & 63u);
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  float4* blk = blocks[w];
-  const int32_t i = b0 + (int32_t)(blockIdx.x * 4u) + w;
-  if (i >= b1) return;  // wave-uniform
-  float x[3] = {seeds[3 * (size_t)i], seeds[3 * (size_t)i + 1], seeds[3 * (size_t)i + 2]};
-  float r[3] = {0.0f, 0.0f, 0.0f};
+// Strand i by the wave, from the seed or from the first launch's end; blk: its
+// 64 places in LDS.
+__device__ __forceinline__ void grow_wave(
+    const GrowDev& d, float inv_h, int32_t i, bool rest, int lane, float4* blk,
+    const float* __restrict__ seeds, const float* __restrict__ seed_dirs, const uint32_t* __restrict__ crossings,
+    float* __restrict__ verts, int32_t* __restrict__ n_verts, float* __restrict__ last_dir) {
   float* out = verts + (size_t)i * (size_t)(d.max_steps + 1) * 3;
-  float keep[3] = {x[0], x[1], x[2]};  // the lane's vertex n with n % 64 == lane
+  float x[3], r[3] = {0.0f, 0.0f, 0.0f};
+  float keep[3];  // the lane's vertex n with n % 64 == lane
   int n = 1;
+  if (rest) {
+    n = 1 + kFirstSteps;
+    grow_resume(d, i, out, last_dir, x, r);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) keep[a] = out[3 * min(lane, kFirstSteps) + a];
+  } else {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) keep[a] = x[a] = seeds[3 * (size_t)i + a];
+  }
   GrowBlock here, next;                // the block in LDS, the one being loaded into pre
   GrowVoxel pre{};
   bool pending = false;
@@ -254,7 +276,7 @@ __global__ __launch_bounds__(256) void k_grow(GrowDev d, float inv_h,
     tv[0] = t4.x;
     tv[1] = t4.y;
     tv[2] = t4.z;
-    if (d.mode != FD_SEED_GIVEN) {
+    if (!rest && d.mode != FD_SEED_GIVEN) {
       const float t[3] = {g.dx, g.dy, g.dz};
       const float off[3] = {x[0] - d.centre[0], x[1] - d.centre[1], x[2] - d.centre[2]};
       const bool away = !(dot3(t, off) < 0.0f);
@@ -263,7 +285,7 @@ __global__ __launch_bounds__(256) void k_grow(GrowDev d, float inv_h,
       for (int a = 0; a < 3; ++a) r[a] = sg * t[a];
     }
   }
-  if (d.mode == FD_SEED_GIVEN) {
+  if (!rest && d.mode == FD_SEED_GIVEN) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) r[a] = seed_dirs[3 * (size_t)i + a];
   }
@@ -358,10 +380,98 @@ __global__ __launch_bounds__(256) void k_grow(GrowDev d, float inv_h,
     for (int a = 0; a < 3; ++a) out[3 * (n - (n & 63) + lane) + a] = keep[a];
   }
   if (lane == 0) {
-    n_verts[i] = n;
+    n_verts[i] = rest ? -n : n;
     const float sg = d.mode == FD_SEED_TOWARDS ? -1.0f : 1.0f;
 #pragma unroll
     for (int a = 0; a < 3; ++a) last_dir[3 * (size_t)i + a] = n > 1 ? sg * r[a] : 0.0f;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_grow(
+    GrowDev d, float inv_h, const float* __restrict__ seeds, const float* __restrict__ seed_dirs,
+    int32_t b0, int32_t b1, const uint32_t* __restrict__ crossings, float* __restrict__ verts,
+    int32_t* __restrict__ n_verts, float* __restrict__ last_dir) {
+  __shared__ float4 blocks[4][64];
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int32_t i = b0 + (int32_t)(blockIdx.x * 4u) + w;
+  if (i >= b1) return;  // wave-uniform
+  grow_wave(d, inv_h, i, false, (int)(threadIdx.x & 63u), blocks[w], seeds, seed_dirs, crossings,
+            verts, n_verts, last_dir);
+}
+
+// Batches above kFewSeeds, as many waves as the card holds at once (256 compute
+// units of 32).  A wave per strand shortens the chain of steps but does 64
+// lanes' work for it; in a large batch it pays only for the strands that go far,
+// if they are few, and how many do only the volume says: most interior seeds
+// stop in their own voxel.  So a lane each takes the first steps of all, and
+// k_grow_rest the rest in the form that their number asks for.  A batch, us, a
+// lane for all / a wave for all / this:
+//   68,000 interior seeds of a hairstyle, 12,000 of which grow  254 / 137 / 132
+//   65,536 in a smooth field, 103 steps   448 / 672 / 472; 21 steps  100 / 169 / 100
+//   65,536 in a noisy field, bend 45 deg   58 / 126 / 59
+//   65,536 in a field a sixth occupied     22 /  33 / 27 (two launches)
+//   131,072 in a noisy field, no bend limit, 176 steps  1802 / 4600 / 1804
+// First steps of 16: 134 for the interior seeds, and short traces longer (52
+// for 30 at 20 steps); 8: 244; 48: 131.
+constexpr int32_t kFewSeeds = 8192;
+constexpr int kRestBlocks = kFewSeeds / 4;
+
+__global__ __launch_bounds__(256) void k_grow_first(
+    GrowDev d, int last, const float* __restrict__ seeds, const float* __restrict__ seed_dirs,
+    int32_t b0, int32_t b1, const uint32_t* __restrict__ crossings, float* __restrict__ verts,
+    int32_t* __restrict__ n_verts, float* __restrict__ last_dir) {
+  const int64_t i = b0 + (int64_t)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i < b1)
+    grow_lane(d, (int32_t)i, false, last, seeds, seed_dirs, crossings, verts, n_verts, last_dir);
+}
+
+// The traces that go on: a wave each where they are few, a lane each where there
+// are enough to hide their latency.  Every workgroup looks at the same places of
+// n_verts, spread over the batch, and so takes the same form (the signs do not
+// change in here).  The seeds of a workgroup lie far apart, since those that grow
+// lie together; its waves take their traces in turn.
+__global__ __launch_bounds__(256, 8) void k_grow_rest(
+    GrowDev d, float inv_h, const float* __restrict__ seeds, const float* __restrict__ seed_dirs,
+    int32_t b0, int32_t b1, const uint32_t* __restrict__ crossings, float* __restrict__ verts,
+    int32_t* __restrict__ n_verts, float* __restrict__ last_dir) {
+  __shared__ float4 blocks[4][64];
+  __shared__ uint32_t part[4], list[256], listed;
+  const int lane = (int)(threadIdx.x & 63u);
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t n = (uint32_t)(b1 - b0);
+  uint32_t c = 0;
+#pragma unroll
+  for (uint32_t s = 0; s < 2; ++s) {  // multiples of the golden ratio, modulo 1, spread evenly
+    const uint32_t u = (threadIdx.x + 256u * s) * 0x9e3779b9u;
+    const uint32_t k = (uint32_t)(((uint64_t)u * n) >> 32);
+    c += (uint32_t)__builtin_popcountll(__ballot(n_verts[b0 + (int32_t)k] < 0));
+  }
+  if (lane == 0) part[w] = c;
+  __syncthreads();
+  const uint32_t on = part[0] + part[1] + part[2] + part[3];  // of 512
+  if ((uint64_t)on * n > (uint64_t)kFewSeeds * 512u) {
+    for (uint32_t k = blockIdx.x * 256u + threadIdx.x; k < n; k += gridDim.x * 256u)
+      if (n_verts[b0 + (int32_t)k] < 0)
+        grow_lane(d, b0 + (int32_t)k, true, d.max_steps, seeds, seed_dirs, crossings, verts,
+                  n_verts, last_dir);
+    return;
+  }
+  for (uint32_t r = 0; r * gridDim.x < n; r += 256u) {  // the same for the whole workgroup
+    __syncthreads();
+    if (threadIdx.x == 0) listed = 0u;
+    __syncthreads();
+    const uint32_t k = blockIdx.x + (r + threadIdx.x) * gridDim.x;
+    if (k < n && n_verts[b0 + (int32_t)k] < 0) list[atomicAdd(&listed, 1u)] = k;
+    __syncthreads();
+    const int m = __builtin_amdgcn_readfirstlane((int)listed);
+    // In turn, by a scalar counter.  Not from a queue that lane 0 takes from: the
+    // compiler joins that condition with the one at the end of grow_wave, and
+    // the other lanes then go round without lane 0, for ever.
+    for (int j = w; j < m; j += 4) {
+      const int32_t i = b0 + __builtin_amdgcn_readfirstlane((int)list[j]);
+      grow_wave(d, inv_h, i, true, lane, blocks[w], seeds, seed_dirs, crossings, verts, n_verts,
+                last_dir);
+    }
   }
 }
 
@@ -370,14 +480,18 @@ __global__ __launch_bounds__(256) void k_grow(GrowDev d, float inv_h,
 // strand, its lanes over the steps: the vertex reads coalesce and the
 // atomics of a strand issue together.
 __global__ __launch_bounds__(256) void k_cross(GridDev g, const float* __restrict__ verts,
-                                               const int32_t* __restrict__ n_verts, int32_t b0,
+                                               int32_t* __restrict__ n_verts, int32_t b0,
                                                int32_t b1, int32_t stride,
                                                uint32_t* __restrict__ crossings) {
   const int lane = (int)(threadIdx.x & 63u);
   const int32_t i = b0 + (int32_t)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
   if (i >= b1) return;  // wave-uniform
   const float* p = verts + (size_t)i * (size_t)stride * 3;
-  const int32_t n = n_verts[i];
+  int32_t n = n_verts[i];
+  if (n < 0) {  // traced in two launches
+    n = -n;
+    if (lane == 0) n_verts[i] = n;
+  }
   for (int k = lane; k + 1 < n; k += 64) {
     const int64_t v = voxel_index(g, p[3 * k], p[3 * k + 1], p[3 * k + 2]);
     if (v >= 0) atomicAdd(&crossings[v], 1u);
@@ -658,18 +772,6 @@ extern "C" void fd_grow_params_init(fd_grow_params* p) {
   p->ctx = nullptr;
 }
 
-// Batches above this many seeds take a lane per strand: as many waves as the
-// card holds at once (256 compute units of 32).  Below, a wave per strand takes
-// the shorter time for its chain; above, 64 lanes' work for one strand is what
-// counts.  A batch's traces, us, lane and wave, 4096 / 8192 / 16,384 / 65,536
-// seeds:
-//   smooth field, 103 steps   319 / 319 / 319 / 448   106 / 153 / 231 / 672
-//   smooth, 21 steps          33 / 39 / 39 / 100      21 / 31 / 53 / 169
-//   noisy field, bend 45 deg  32 / 33 / 37 / 58       21 / 28 / 41 / 126
-//   a sixth occupied          14 / 17 / 15 / 22       10 / 11 / 14 / 33
-// (a noisy field without a bend limit, cut at 20 steps: 30 / 38 and 35 / 53.)
-constexpr int32_t kLaneBatch = 8192;
-
 extern "C" int fd_grow_strands(const fd_volume_grid* grid, const uint32_t* occ, const float* dir,
                                const float* coherence, const float* seeds,
                                const float* seed_dirs, int32_t n_seeds,
@@ -723,13 +825,20 @@ extern "C" int fd_grow_strands(const fd_volume_grid* grid, const uint32_t* occ, 
     const int32_t b1 = n_seeds - b0 > p->batch ? b0 + p->batch : n_seeds;
     {
       StageTimer t(c, FD_STAGE_GROW, st);
-      if (b1 - b0 > kLaneBatch)
-        hipLaunchKernelGGL(k_grow_lane, dim3((unsigned)(((int64_t)(b1 - b0) + 255) / 256)),
-                           dim3(256), 0, st, d, seeds, seed_dirs, b0, b1, crossings, verts, n_verts,
-                           last_dir);
-      else
+      const int64_t m = b1 - b0;
+      if (m > kFewSeeds) {
+        hipLaunchKernelGGL(k_grow_first, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, d,
+                           std::min(kFirstSteps, d.max_steps), seeds, seed_dirs, b0, b1, crossings,
+                           verts, n_verts, last_dir);
+        if ((e = hipGetLastError()) == hipSuccess && d.max_steps > kFirstSteps)
+          hipLaunchKernelGGL(k_grow_rest, dim3((unsigned)std::min<int64_t>(kRestBlocks, (m + 15) / 16)),
+                             dim3(256), 0, st, d, inv_h, seeds, seed_dirs, b0, b1, crossings, verts,
+                             n_verts, last_dir);
+        if (e != hipSuccess) return hip_error(e, "grow");
+      } else {
         hipLaunchKernelGGL(k_grow, dim3((unsigned)((b1 - b0 + 3) / 4)), dim3(256), 0, st, d, inv_h,
                            seeds, seed_dirs, b0, b1, crossings, verts, n_verts, last_dir);
+      }
       if ((e = hipGetLastError()) != hipSuccess) return hip_error(e, "grow");
       t.stop();
     }

@@ -532,7 +532,7 @@ def test_feature_rows_of_many_points(views, half):
 
 @pytest.mark.parametrize("mode,cap,bend", [(0, 0, -2.0), (1, 6, 0.5), (2, 3, 0.9)])
 def test_growing_on_both_sides_of_the_lane_batch(mode, cap, bend):
-    """8192 seeds take a wave each, 8193 a lane each: the same traces as the
+    """8192 seeds take a wave each, 8193 two launches: the same traces as the
     oracle's, and as each other's over the seeds that both have."""
     nat = _native()
     rng = np.random.default_rng(mode)
@@ -610,3 +610,40 @@ def test_feature_lists_of_coinciding_cameras(views, repeat):
     assert np.array_equal(f[:, 6::7], fo[:, 6::7])
     err = np.abs(f - oracle.round_bf16(fo.astype(np.float32)).astype(np.float64))
     assert (err > 2.0 ** -7 * np.abs(fo) + 1e-5).sum() <= 1e-4 * err.size
+
+
+@pytest.mark.parametrize("n,far,max_steps", [(8193, 0.1, 33), (20011, 0.05, 70), (20011, 1.0, 32), (20011, 1.0, 33),
+                                             (20011, 1.0, 100), (70001, 0.1, 65), (600_000, 0.005, 40)])
+@pytest.mark.parametrize("mode", [0, 2])
+def test_growing_large_batches(n, far, max_steps, mode):
+    """One batch of more than 8192 seeds, few or most of which go further than
+    the first steps, steps that end with them, one after them and past a
+    block of 64 vertices: bit for bit the oracle's traces and crossings."""
+    nat = _native()
+    rng = np.random.default_rng(n + max_steps + mode)
+    dims = (40, 36, 52)
+    nx, ny, nz = dims
+    z = np.arange(nz, dtype=np.float64)[:, None, None, None]
+    d = np.concatenate([np.sin(z / 9), np.cos(z / 7), 1.5 + 0 * z], -1) + 0.15 * rng.normal(size=(nz, ny, nx, 3))
+    d /= np.linalg.norm(d, axis=-1, keepdims=True)
+    d = (d * rng.choice([-1.0, 1.0], size=(nz, ny, nx, 1))).astype(np.float32)
+    occ = np.ones((nz, ny, nx), np.uint32)
+    coh = np.ones((nz, ny, nx), np.float32)
+    h = np.float32(0.003)
+    grid = (np.array([-0.06, -0.05, -0.08], np.float32), h, np.array(dims, np.int32))
+    seeds = (rng.uniform(0.05, 0.95, size=(n, 3)) * np.array(dims) * 0.003 + grid[0]).astype(np.float32)
+    seeds[rng.uniform(size=n) >= far] += np.float32(1.0)  # outside
+    sdirs = rng.normal(size=(n, 3)).astype(np.float32) if mode == 0 else None
+    kw = dict(seed_mode=mode, centre=(0.01, 0.0, -0.02), step=1e-3, max_steps=max_steps, min_coherence=0.5,
+              max_bend_cos=0.3, voxel_cap=4, batch=n)
+    busy = np.where(rng.uniform(size=occ.size) < 0.001, 4, 0).astype(np.uint32)  # at the cap
+    cr = _t(busy.view(np.int32).copy())
+    v, nv, last = nat.grow_strands(_t(occ.view(np.int32)), _t(d), _t(coh), *grid, _t(seeds), None if sdirs is None else _t(sdirs),
+                                   crossings=cr, **kw)
+    o = oracle.grow(dict(occ=occ, dir=d, coherence=coh), grid, seeds, sdirs, crossings=busy.copy(), **kw)
+    v, nv, last = v.cpu().numpy(), nv.cpu().numpy(), last.cpu().numpy()
+    assert (o["n_verts"] > 33).mean() > 0.2 * far or max_steps <= 33
+    assert np.array_equal(nv, o["n_verts"]) and np.array_equal(last, o["last_dir"])
+    on = np.arange(v.shape[1])[None] < nv[:, None]
+    assert np.array_equal(v[on], o["verts"][:, :v.shape[1]][on])
+    assert np.array_equal(cr.cpu().numpy().view(np.uint32), o["crossings"])

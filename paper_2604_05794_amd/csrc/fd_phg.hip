@@ -408,12 +408,16 @@ __global__ __launch_bounds__(256) void k_grow(
 // lane for all / a wave for all / this:
 //   68,000 interior seeds of a hairstyle, 12,000 of which grow  254 / 137 / 132
 //   65,536 in a smooth field, 103 steps   448 / 672 / 472; 21 steps  100 / 169 / 100
-//   65,536 in a noisy field, bend 45 deg   58 / 126 / 59
-//   65,536 in a field a sixth occupied     22 /  33 / 27 (two launches)
+//   65,536 in a noisy field, bend 45 deg   58 / 126 / 56
+//   65,536 in a field a sixth occupied     22 /  33 / 24 (two launches)
 //   131,072 in a noisy field, no bend limit, 176 steps  1802 / 4600 / 1804
 // First steps of 16: 134 for the interior seeds, and short traces longer (52
 // for 30 at 20 steps); 8: 244; 48: 131.
 constexpr int32_t kFewSeeds = 8192;
+// Above kFewSeeds, so that a sample of 256 does not take 8000 for more: 7354 of
+// 80,000 seeds, as waves 100 us, as lanes 160.  12,000 that take 176 steps each
+// would be 430 and 330.
+constexpr int32_t kFewFar = 12288;
 constexpr int kRestBlocks = kFewSeeds / 4;
 
 __global__ __launch_bounds__(256) void k_grow_first(
@@ -439,17 +443,13 @@ __global__ __launch_bounds__(256, 8) void k_grow_rest(
   const int lane = (int)(threadIdx.x & 63u);
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t n = (uint32_t)(b1 - b0);
-  uint32_t c = 0;
-#pragma unroll
-  for (uint32_t s = 0; s < 2; ++s) {  // multiples of the golden ratio, modulo 1, spread evenly
-    const uint32_t u = (threadIdx.x + 256u * s) * 0x9e3779b9u;
-    const uint32_t k = (uint32_t)(((uint64_t)u * n) >> 32);
-    c += (uint32_t)__builtin_popcountll(__ballot(n_verts[b0 + (int32_t)k] < 0));
-  }
+  // multiples of the golden ratio, modulo 1, are spread evenly
+  const uint32_t at = (uint32_t)(((uint64_t)(threadIdx.x * 0x9e3779b9u) * n) >> 32);
+  const uint32_t c = (uint32_t)__builtin_popcountll(__ballot(n_verts[b0 + (int32_t)at] < 0));
   if (lane == 0) part[w] = c;
   __syncthreads();
-  const uint32_t on = part[0] + part[1] + part[2] + part[3];  // of 512
-  if ((uint64_t)on * n > (uint64_t)kFewSeeds * 512u) {
+  const uint32_t on = part[0] + part[1] + part[2] + part[3];  // of 256
+  if ((uint64_t)on * n > (uint64_t)kFewFar * 256u) {
     for (uint32_t k = blockIdx.x * 256u + threadIdx.x; k < n; k += gridDim.x * 256u)
       if (n_verts[b0 + (int32_t)k] < 0)
         grow_lane(d, b0 + (int32_t)k, true, d.max_steps, seeds, seed_dirs, crossings, verts,

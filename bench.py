@@ -53,9 +53,9 @@ sys.path.insert(0, ROOT)
 
 METRIC = "fused points/s at ≤2° mean angular err; learned+batched vs plain, 1 MI355X"
 PEAK_FP32 = 157.3             # TFLOP/s: MI355X published fp32 vector peak
-# TFLOP/s of fp32 products split over the fp16 matrix cores: three of their
+# TFLOP/s of fp32 products split over the fp16 matrix cores: four of their
 # products (dense figure 2500) stand for one
-PEAK_SPLIT_MFMA = 2500.0 / 3
+PEAK_SPLIT_MFMA = 2500.0 / 4
 PEAK_HBM = 8000.0             # GB/s
 
 
@@ -74,25 +74,25 @@ _GABOR_SOURCES = ["fd_gabor.hip"]
 _VOLUME_SOURCES = ["fd_volume.hip", "fd_voxel.hpp"]
 _PHG_SOURCES = ["fd_phg.hip", "fd_voxel.hpp"]
 TRAFFIC = {
-    "k_fuse, realistic 500k": {"read": 409.9e6, "write": 37.6e6, "files": _SEARCH_SOURCES,
-                               "src": "f1cf612e32964315"},
-    "k_fuse, metric workload, per head": {"read": 135.8e6, "write": 8.5e6,
-                                          "files": _SEARCH_SOURCES, "src": "f1cf612e32964315"},
-    "k_b_learned, metric workload": {"read": 2258.3e6, "write": 160.7e6,
-                                     "files": _BATCHED_SOURCES, "src": "b9fe1b77b1dd8781"},
+    "k_fuse, realistic 500k": {"read": 381.3e6, "write": 37.7e6, "files": _SEARCH_SOURCES,
+                               "src": "533d983cb0a6d539"},
+    "k_fuse, metric workload, per head": {"read": 133.7e6, "write": 8.5e6,
+                                          "files": _SEARCH_SOURCES, "src": "533d983cb0a6d539"},
+    "k_b_learned, metric workload": {"read": 2135.9e6, "write": 160.6e6,
+                                     "files": _BATCHED_SOURCES, "src": "f324c54cdb7ae75c"},
     # the autotuned one-wave-per-tile form (the persistent form's traffic
     # depends on its queue shape)
-    "k_b_fuse_tiles, 16 hairstyles": {"read": 3812.9e6, "write": 348.6e6,
-                                      "files": _BATCHED_SOURCES, "src": "b9fe1b77b1dd8781"},
-    "k_gabor_mfma, 64 frames 1024^2": {"read": 1152.1e6, "write": 406.8e6,
-                                       "files": _GABOR_SOURCES, "src": "21a8f3739c8a0866"},
+    "k_b_fuse_tiles, 16 hairstyles": {"read": 3748.2e6, "write": 348.6e6,
+                                      "files": _BATCHED_SOURCES, "src": "f324c54cdb7ae75c"},
+    "gabor bank, 64 frames 1024^2": {"read": 2402.5e6, "write": 444.3e6,
+                                     "files": _GABOR_SOURCES, "src": "83697a0cb52accfe"},
     # the counting sort: keys and counts, the slots, the placement
-    "volume sort, realistic 2M points 2 mm": {"read": 319.8e6, "write": 237.4e6,
+    "volume sort, realistic 2M points 2 mm": {"read": 292.6e6, "write": 269.6e6,
                                               "files": _VOLUME_SOURCES,
-                                              "src": "b0b5904bb1ae7e7b"},
-    # per pass: the 5 guide batches and the 2 segment launches
-    "k_grow, phg workload": {"read": 201.9e6, "write": 30.7e6, "files": _PHG_SOURCES,
-                             "src": "4f42252c325b0cf8"},
+                                              "src": "256c6b8984d17f99"},
+    # per pass: the 5 guide batches and the 2 segment batches
+    "k_grow, phg workload": {"read": 832.7e6, "write": 38.0e6, "files": _PHG_SOURCES,
+                             "src": "73fae92abb103f5b"},
 }
 
 
@@ -774,10 +774,10 @@ def run_gabor(args):
                                f"{n_orient} orientations, radius {radius}",
                    "frames": V, "width": W, "height": H, "n_orient": n_orient,
                    "radius": radius},
-        "roofline": {"bound": "mfma", "kernel": "k_gabor_mfma", "achieved": achieved,
-                     "peak": PEAK_SPLIT_MFMA, "unit": "TFLOP/s",
+        "roofline": {"bound": "mfma", "kernel": "gabor bank (k_gabor_sort, _split, _f32)",
+                     "achieved": achieved, "peak": PEAK_SPLIT_MFMA, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_SPLIT_MFMA,
-                     "traffic": traffic_of("k_gabor_mfma, 64 frames 1024^2"),
+                     "traffic": traffic_of("gabor bank, 64 frames 1024^2"),
                      "avg_launch_ms": stages["gabor"], "flop_per_pixel": flop},
         "stages_ms_per_launch": stages,
         "pipeline_frames_maps_search": pipeline,
@@ -1227,10 +1227,10 @@ def run_pipeline(args):
                                f"{ng} roots + {ns} segment seeds -> linked strands",
                    "frames": V, "outer_points": n_out, "inner_points": len(pin),
                    "grid": dims.tolist(), "roots": ng, "segment_seeds": ns},
-        "roofline": {"bound": "mfma", "kernel": "k_gabor_mfma (the longest stage)",
+        "roofline": {"bound": "mfma", "kernel": "gabor bank (the longest stage)",
                      "achieved": achieved, "peak": PEAK_SPLIT_MFMA, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_SPLIT_MFMA,
-                     "traffic": traffic_of("k_gabor_mfma, 64 frames 1024^2"),
+                     "traffic": traffic_of("gabor bank, 64 frames 1024^2"),
                      "avg_launch_ms": stages["gabor"]},
         "stages_ms_per_step": per_step,
         "result": {"strand_vertices": int(off[-1]), "strands_with_segments":

@@ -131,7 +131,7 @@ struct LearnedDev {
   uint32_t* fb_count;      // [0] fallback list length, [1] points searched in place
 };
 
-// Per-call constants of the search in device memory (fd_fuse.hip, k_consts):
+// Per-call constants of the search in device memory (k_setup, or k_consts for a batch):
 // the lattice in binary32 and binary64 and the cos/sin tables of the plain
 // and learned refinement steps.
 struct ConstsDev {

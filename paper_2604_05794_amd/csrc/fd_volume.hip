@@ -53,8 +53,8 @@ constexpr uint32_t kOutside = 0xffffffffu;
 constexpr int kGroup = 8, kFew = 24;
 // A voxel with more than this many points for each of its lanes takes the whole
 // wave: few voxels far above the average would otherwise be all that runs (half
-// of 1M points in 100 voxels, the call: 3.0 ms -> 247 us, 1.3 ms with 48-byte records; points per
-// voxel by a power law of 1.2 up to 3000: 862 -> 130 us).
+// of 1M points in 100 voxels, the call: 3.0 ms -> 247 us, 1.3 ms with 48-byte
+// records; points per voxel by a power law of 1.2 up to 3000: 862 -> 130 us).
 constexpr int kHeavy = 128;
 constexpr int kRun = 1024;       // threads of k_vol_alloc
 constexpr int kRunVoxels = 4096;  // voxels of one of its blocks

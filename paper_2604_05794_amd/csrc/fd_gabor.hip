@@ -106,10 +106,15 @@ struct GaborDev {
   size_t plane;
 
   __device__ __forceinline__ void place(int tid, int* f, int* x0, int* y0) const {
-    const int per_frame = tiles_x * tiles_y;
+    place_of(tid, tiles_y, kTileRows, f, x0, y0);
+  }
+  // the same for tiles of `high` rows, n_y in a column
+  __device__ __forceinline__ void place_of(int tid, int n_y, int high, int* f, int* x0,
+                                           int* y0) const {
+    const int per_frame = tiles_x * n_y;
     *f = tid / per_frame;
     const int rem = tid - *f * per_frame, r = rem / tiles_x;
-    *y0 = (r + *f) % tiles_y * kTileRows;
+    *y0 = (r + *f) % n_y * high;
     *x0 = (rem - r * tiles_x + r + *f) % tiles_x * kTile;
   }
 };
@@ -265,8 +270,10 @@ __device__ __forceinline__ void sum_in_order(const GaborDev& d, const F& tap, co
   }
 }
 
-// All pixels of the listed tiles (from the list's end), or of every tile.
-// Persistent workgroups of four waves keep the bank in LDS and walk half tiles
+// All pixels of the listed tiles (from the list's end), or of all n_half half
+// tiles, half_y in a column (two for every tile would leave workgroups without
+// work where the last tiles are less than half full: 15 frames of 253 x 81 96 us
+// in place of 74).  Persistent workgroups of four waves keep the bank in LDS and walk half tiles
 // of 16 x 32, wave w owning rows 8w .. 8w + 7, so each bank read feeds 8 matrix
 // operations.  The tile rows are kTw
 // words apart for every radius: the 8 row reads of a step take immediate
@@ -282,11 +289,11 @@ constexpr int kTw = kTile + 2 * kMaxRadius;  // LDS tile row stride for every ra
 
 template <typename TO, int NT, bool FULL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_gabor_f32(
-    GaborDev d, const uint32_t* __restrict__ n_listed, const uint32_t* __restrict__ list,
-    GaborOut o) {
+    GaborDev d, int half_y, int n_half, const uint32_t* __restrict__ n_listed,
+    const uint32_t* __restrict__ list, GaborOut o) {
   extern __shared__ float lds_f32[];
   __shared__ float wmax[256 / 64];
-  const int n_half = 2 * (n_listed ? (int)*n_listed : d.n_tiles);
+  if (list) n_half = 2 * (int)*n_listed;
   if ((int)blockIdx.x >= n_half) return;
   constexpr int NJ = 16 * NT;
   const int W = d.W, H = d.H, R = d.R, NO = d.NO;
@@ -301,9 +308,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
   const int g = lane >> 4, c16 = lane & 15;
   for (int i = blockIdx.x; i < n_half; i += gridDim.x) {
     int f, x0, y0;
-    d.place(list ? (int)list[d.n_tiles - 1 - (i >> 1)] : i >> 1, &f, &x0, &y0);
-    y0 += kF32Rows * (i & 1);
-    if (y0 >= H) continue;  // uniform
+    if (list) {
+      d.place((int)list[d.n_tiles - 1 - (i >> 1)], &f, &x0, &y0);
+      y0 += kF32Rows * (i & 1);
+      if (y0 >= H) continue;  // uniform
+    } else {
+      d.place_of(i, half_y, kF32Rows, &f, &x0, &y0);
+    }
     const float* img = d.frames + d.plane * f;
     __syncthreads();  // the bank is in place; the previous tile is no longer read
     for (int e = threadIdx.x; e < kTw * th; e += blockDim.x) {
@@ -1056,9 +1067,11 @@ hipError_t launch_gabor(GaborDev d, const float* margin, uint32_t* cursor, uint3
   if (e != hipSuccess) return e;
   // persistent: each workgroup loads the bank once; several resident per CU
   const int per_cu = (int)std::max<size_t>(1, (160 * 1024) / (lds + 1024));
+  const int half_y = (d.H + kF32Rows - 1) / kF32Rows;
+  const int n_half = split ? 2 * d.n_tiles : d.n_tiles / d.tiles_y * half_y;
   hipLaunchKernelGGL((k_gabor_f32<TO, NT, FULL>),
-                     dim3((unsigned)std::min(2 * d.n_tiles, 256 * std::min(per_cu, 4))), dim3(256),
-                     lds, st, d, split ? cursor + 1 : nullptr, split ? list : nullptr, o);
+                     dim3((unsigned)std::min(n_half, 256 * std::min(per_cu, 4))), dim3(256), lds,
+                     st, d, half_y, n_half, split ? cursor + 1 : nullptr, split ? list : nullptr, o);
   return hipGetLastError();
 }
 

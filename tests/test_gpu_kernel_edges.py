@@ -647,3 +647,18 @@ def test_growing_large_batches(n, far, max_steps, mode):
     on = np.arange(v.shape[1])[None] < nv[:, None]
     assert np.array_equal(v[on], o["verts"][:, :v.shape[1]][on])
     assert np.array_equal(cr.cpu().numpy().view(np.uint32), o["crossings"])
+
+
+@pytest.mark.parametrize("n_orient,radius", [(32, 8), (16, 3), (8, 12)])
+@pytest.mark.parametrize("h", [1, 31, 32, 33, 64, 65, 81, 97, 129])
+def test_orientation_rows_of_half_tiles(h, n_orient, radius):
+    """Heights around the 32 rows of a half tile, in several small frames: each
+    frame within the bounds of the orientation-map tests."""
+    import test_gpu_gabor as G
+    rng = np.random.default_rng(h)
+    kw = dict(n_orient=n_orient, radius=radius)
+    frames = rng.uniform(0.0, 1.0, (4, h, 53)).astype(np.float32)
+    th, cf = G._gpu(frames, **kw)
+    bank = oracle.gabor_bank(**{k: v if k in kw else float(np.float32(v)) for k, v in G._bank_kw(kw).items()})
+    for v in range(4):
+        G._check_frame(frames[v], th[v], cf[v], bank, max_tie_frac=1.0)

@@ -84,8 +84,8 @@ TRAFFIC = {
     # depends on its queue shape)
     "k_b_fuse_tiles, 16 hairstyles": {"read": 3748.2e6, "write": 348.6e6,
                                       "files": _BATCHED_SOURCES, "src": "f324c54cdb7ae75c"},
-    "gabor bank, 64 frames 1024^2": {"read": 2402.5e6, "write": 444.3e6,
-                                     "files": _GABOR_SOURCES, "src": "83697a0cb52accfe"},
+    "gabor bank, 64 frames 1024^2": {"read": 2404.6e6, "write": 444.2e6,
+                                     "files": _GABOR_SOURCES, "src": "76b89271a3d605de"},
     # the counting sort: keys and counts, the slots, the placement
     "volume sort, realistic 2M points 2 mm": {"read": 292.6e6, "write": 269.6e6,
                                               "files": _VOLUME_SOURCES,
